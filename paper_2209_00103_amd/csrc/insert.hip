@@ -900,20 +900,79 @@ __global__ __launch_bounds__(256) void grow_store_rounds_kernel(ArrRef A, TileAr
   }
 }
 
+// Elements of LFVector v by one wave: the ones from local index i0 up to i1 (the
+// first one made by the producer's thread g0), one run per bucket; bucket(b) gives
+// the pointer of bucket b.
+template <typename T, class Prod, class Bucket>
+__device__ __forceinline__ void store_span(const ArrRef& A, const Prod& prod, uint64_t i0, uint64_t i1, uint64_t g0,
+                                           Bucket bucket) {
+  for (uint64_t idx = i0; idx < i1;) {
+    const uint32_t b = bucket_of(A.log2F, idx);
+    const uint64_t bs = bucket_start(A.log2F, b);
+    const uint64_t end = bs + bucket_len(A.log2F, b);
+    const uint32_t run = (uint32_t)((i1 < end ? i1 : end) - idx);
+    dense_store<T, Prod>(reinterpret_cast<T*>(bucket(b)) + (idx - bs), prod, g0 + (idx - i0), run);
+    idx += run;
+  }
+}
+
 // Segment append: LFVector v appends values[prefix[v] .. prefix[v + 1]).  A
 // decreasing pair, a segment past n_values or one of 2^32 elements or more sets
 // GGA_ERANGE and leaves the LFVector unchanged.
+__device__ __forceinline__ bool segment_of(const uint64_t* prefix, uint32_t v, uint64_t n_values, uint64_t& lo,
+                                           uint64_t& cnt) {
+  const uint64_t hi = prefix[v + 1];
+  lo = prefix[v];
+  cnt = hi - lo;
+  return hi >= lo && hi <= n_values && cnt < (1ull << 32);
+}
+
+// Short segments: one wave per LFVector grows and stores.
 template <typename T>
 __global__ __launch_bounds__(256) void segments_kernel(ArrRef A, TileArgs I, const T* values, const uint64_t* prefix,
                                                        uint64_t n_values) {
   const uint32_t v = blockIdx.x * 4u + (threadIdx.x >> 6);
   if (v >= A.V) return;
-  const uint64_t lo = prefix[v], hi = prefix[v + 1];
-  if (hi < lo || hi > n_values || hi - lo >= (1ull << 32)) {
+  uint64_t lo, cnt;
+  if (!segment_of(prefix, v, n_values, lo, cnt)) {
     if (lane_id() == 0) set_error(A.err, kErrRange);
     return;
   }
-  grow_store_range<T, ProdBuffer<T>>(A, I, ProdBuffer<T>{values, nullptr}, v, lo, hi - lo);
+  grow_store_range<T, ProdBuffer<T>>(A, I, ProdBuffer<T>{values, nullptr}, v, lo, cnt);
+}
+
+// Longer segments: one wave per LFVector grows it, then `parts` workgroups per
+// LFVector store its segment in pieces of 4 KiB that start on whole lines of the
+// bucket.  One wave copying a segment waits for a round trip to memory per 4 KiB
+// and the longest segment holds the launch (3.0e7 u32 elements in 512 segments of
+// lognormal lengths: 654 us as one wave each, 5 + 50 us, 4.8 TB/s, in this form).
+__global__ __launch_bounds__(256) void segments_grow_kernel(ArrRef A, TileArgs I, const uint64_t* prefix,
+                                                            uint64_t n_values) {
+  const uint32_t v = blockIdx.x * 4u + (threadIdx.x >> 6);
+  if (v >= A.V) return;
+  uint64_t lo, cnt;
+  if (!segment_of(prefix, v, n_values, lo, cnt)) {
+    if (lane_id() == 0) set_error(A.err, kErrRange);
+    return;
+  }
+  grow_vector_by(A, I.elem_log2, v, cnt);
+}
+
+constexpr uint32_t kSpanBytes = 4096;  // one round of dense_store's loads (64 lanes, 4 vectors)
+template <typename T>
+__global__ __launch_bounds__(kB) void segments_store_kernel(ArrRef A, const T* values, const uint64_t* prefix,
+                                                            uint64_t n_values, uint32_t parts) {
+  constexpr uint64_t kSpan = kSpanBytes / sizeof(T), kLine = 128 / sizeof(T);
+  const uint32_t v = blockIdx.x / parts;
+  uint64_t lo, cnt;
+  if (!segment_of(prefix, v, n_values, lo, cnt) || cnt == 0 || A.dead[v]) return;
+  const uint64_t s0 = A.rbase[v], s1 = s0 + cnt, al = s0 & ~(kLine - 1);
+  const uint64_t* row = A.bptr + (uint64_t)v * kMaxBuckets;
+  const uint64_t wave = (uint64_t)(blockIdx.x - v * parts) * kW + (threadIdx.x >> 6);
+  for (uint64_t a = al + wave * kSpan; a < s1; a += (uint64_t)parts * kW * kSpan) {
+    const uint64_t i0 = a < s0 ? s0 : a, i1 = a + kSpan < s1 ? a + kSpan : s1;
+    store_span<T>(A, ProdBuffer<T>{values, nullptr}, i0, i1, lo + (i0 - s0), [row](uint32_t b) { return row[b]; });
+  }
 }
 
 __global__ __launch_bounds__(256) void grow_kernel(ArrRef A, TileArgs I) {
@@ -2036,19 +2095,37 @@ int launch_insert(ggarray* a, const InsertDesc& d, hipStream_t s, uint32_t sh_nu
   return st;
 }
 
+template <typename T>
+static void queue_segments(const ArrRef& A, const TileArgs& I, const T* values, const uint64_t* prefix,
+                           uint64_t n_values, hipStream_t s) {
+  const dim3 grid((A.V + 3) / 4), block(256);
+  // One launch while the segments average at most one load round of a wave; the
+  // second launch costs about 5 us, more than it saves below that.
+  const uint64_t spans = n_values * sizeof(T) / kSpanBytes;
+  if (spans <= A.V) {
+    hipLaunchKernelGGL(segments_kernel<T>, grid, block, 0, s, A, I, values, prefix, n_values);
+    return;
+  }
+  // Twice the workgroups that equal segments would need, so that a segment of
+  // several times the average still finishes with the others, up to 32 per CU.
+  uint64_t parts = (2 * spans / kW + A.V - 1) / A.V;
+  const uint64_t most = (8192 + A.V - 1) / A.V;
+  if (parts > most) parts = most;
+  hipLaunchKernelGGL(segments_grow_kernel, grid, block, 0, s, A, I, prefix, n_values);
+  hipLaunchKernelGGL(segments_store_kernel<T>, dim3((uint32_t)(parts * A.V)), dim3(kB), 0, s, A, values, prefix,
+                     n_values, (uint32_t)parts);
+}
+
 int launch_insert_segments(ggarray* a, const void* values, const uint64_t* prefix, uint64_t n_values,
                            hipStream_t s) {
   TileArgs I{};
   I.elem_log2 = a->elem_log2;
   a->tev_set &= ~4u;  // not a timed round
   grow_bound(a, n_values);
-  const dim3 grid((a->V + 3) / 4), block(256);
   if (a->elem_bytes == 4)
-    hipLaunchKernelGGL(segments_kernel<uint32_t>, grid, block, 0, s, a->ref, I, static_cast<const uint32_t*>(values),
-                       prefix, n_values);
+    queue_segments<uint32_t>(a->ref, I, static_cast<const uint32_t*>(values), prefix, n_values, s);
   else
-    hipLaunchKernelGGL(segments_kernel<uint64_t>, grid, block, 0, s, a->ref, I, static_cast<const uint64_t*>(values),
-                       prefix, n_values);
+    queue_segments<uint64_t>(a->ref, I, static_cast<const uint64_t*>(values), prefix, n_values, s);
   const hipError_t e = hipGetLastError();
   if (e == hipSuccess) sizes_changed(a, s);
   return hip_status(e);
