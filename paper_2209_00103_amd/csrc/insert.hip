@@ -916,6 +916,59 @@ __device__ __forceinline__ void store_span(const ArrRef& A, const Prod& prod, ui
   }
 }
 
+constexpr uint32_t kSpanBytes = 4096;  // one round of dense_store's loads (64 lanes, 4 vectors)
+
+// A round from a buffer in which every thread inserts: one workgroup of W waves
+// per LFVector.  Wave 0 allocates the buckets the round reaches; then the waves
+// take the LFVector's share in pieces of 4 KiB that start on whole lines of the
+// bucket, W pieces at a time.  What bounds a copy here is the bytes in flight: a
+// single wave per LFVector (the generated rounds' form, which only stores) waits
+// for memory once per 4 KiB (V = 512, 2.0e7 u32 elements: 44 us a round as one
+// wave each, 3.6 TB/s; 28 us, 5.7 TB/s, in this form).
+template <typename T, uint32_t W>
+__global__ __launch_bounds__(64 * W) void grow_store_block_kernel(ArrRef A, TileArgs I, const T* values) {
+  constexpr uint64_t kSpan = kSpanBytes / sizeof(T), kLine = 128 / sizeof(T);
+  __shared__ uint64_t s_bp[kMaxBuckets];
+  __shared__ uint32_t s_fail;
+  const uint32_t v = blockIdx.x, tid = threadIdx.x, lane = tid & 63u;
+  const uint64_t c0 = (uint64_t)v * I.chunk;
+  const uint64_t cnt = c0 < I.n_threads ? (I.n_threads - c0 < I.chunk ? I.n_threads - c0 : I.chunk) : 0;
+  if (cnt == 0 || A.dead[v]) return;
+  const uint32_t log2F = A.log2F;
+  const uint64_t s0 = A.size[v], s1 = s0 + cnt;
+  if (tid < 64) {
+    uint64_t* row = A.bptr + (uint64_t)v * kMaxBuckets;
+    const uint32_t lo = nbuckets_for(log2F, s0), hi = nbuckets_for(log2F, s1), b = lo + lane;
+    bool failed = false;
+    if (b < hi) {
+      if (b >= (uint32_t)kMaxBuckets) {
+        failed = true;
+      } else {
+        uint8_t* q = pool_alloc(A.pool, bucket_class(log2F, I.elem_log2, b), pool_shard(v, b, A.salt));
+        s_bp[b] = row[b] = q ? (uint64_t)q : kFailedPtr;
+        failed = !q;
+      }
+    }
+    if (lane == 63 && lo) s_bp[lo - 1] = row[lo - 1];  // the bucket that earlier rounds left part full
+    const bool any = __ballot(failed) != 0;
+    if (lane == 0) s_fail = any ? 1u : 0u;
+  }
+  __syncthreads();  // every wave has read the size and the frozen flag
+  if (tid == 0) {
+    if (s_fail) {
+      set_error(A.err, kErrNoMem);
+      A.dead[v] = 1u;
+    } else {
+      A.size[v] = s1;
+    }
+  }
+  if (s_fail) return;
+  for (uint64_t a = (s0 & ~(kLine - 1)) + (tid >> 6) * kSpan; a < s1; a += W * kSpan) {
+    const uint64_t i0 = a < s0 ? s0 : a, i1 = a + kSpan < s1 ? a + kSpan : s1;
+    store_span<T>(A, ProdBuffer<T>{values, nullptr}, i0, i1, c0 + (i0 - s0), [](uint32_t b) { return s_bp[b]; });
+  }
+}
+
 // Segment append: LFVector v appends values[prefix[v] .. prefix[v + 1]).  A
 // decreasing pair, a segment past n_values or one of 2^32 elements or more sets
 // GGA_ERANGE and leaves the LFVector unchanged.
@@ -958,7 +1011,6 @@ __global__ __launch_bounds__(256) void segments_grow_kernel(ArrRef A, TileArgs I
   grow_vector_by(A, I.elem_log2, v, cnt);
 }
 
-constexpr uint32_t kSpanBytes = 4096;  // one round of dense_store's loads (64 lanes, 4 vectors)
 template <typename T>
 __global__ __launch_bounds__(kB) void segments_store_kernel(ArrRef A, const T* values, const uint64_t* prefix,
                                                             uint64_t n_values, uint32_t parts) {
@@ -1901,10 +1953,21 @@ int launch_dense(const ArrRef& A, const TileArgs& I, const InsertDesc& d, uint64
   if (wave_per_vector(I, A.V)) {
     const dim3 grid((A.V + 3) / 4), block(256);
     switch (d.mode) {
-      case kModeBuffer:
-        hipExtLaunchKernelGGL(grow_store_kernel<T, ProdBuffer<T>>, grid, block, 0, s, e0, e1, 0, A, I,
-                           ProdBuffer<T>{static_cast<const T*>(d.values), nullptr});
+      case kModeBuffer: {
+        // Shares of at most one load round (4 KiB): a wave each.  Longer ones: 16
+        // waves while that many LFVectors leave the chip short of waves (V <= 1024
+        // fills its 8192), else 4.
+        const T* values = static_cast<const T*>(d.values);
+        if (I.chunk * sizeof(T) <= kSpanBytes)
+          hipExtLaunchKernelGGL(grow_store_kernel<T, ProdBuffer<T>>, grid, block, 0, s, e0, e1, 0, A, I,
+                                ProdBuffer<T>{values, nullptr});
+        else if (A.V <= 1024)
+          hipExtLaunchKernelGGL((grow_store_block_kernel<T, 16>), dim3(A.V), dim3(1024), 0, s, e0, e1, 0, A, I,
+                                values);
+        else
+          hipExtLaunchKernelGGL((grow_store_block_kernel<T, 4>), dim3(A.V), block, 0, s, e0, e1, 0, A, I, values);
         break;
+      }
       case kModeRoundTag:
         hipExtLaunchKernelGGL(grow_store_kernel<T, ProdRoundTag<T>>, grid, block, 0, s, e0, e1, 0, A, I,
                            ProdRoundTag<T>{d.round, d.tag_shift});
