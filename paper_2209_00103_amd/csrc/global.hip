@@ -2,8 +2,15 @@
 // element i - P[v] of LFVector v, where P is the exclusive prefix of the
 // LFVector sizes (Sec. IV) and v the last LFVector with P[v] <= i; an empty
 // LFVector shares its offset with the next one, so this choice skips it.  Inside
-// the LFVector the closed form gives bucket and offset.  One thread per element:
-// a binary search over P, a bucket-pointer load, then the element itself.
+// the LFVector the closed form gives bucket and offset.
+//
+// A search of P for every element is a chain of dependent loads, and that chain,
+// not the elements' traffic, bounded both kernels here (V = 512, 2^24 u32
+// elements: an update of all 161 us, 0.83 TB/s; 2^22 random reads 99 us).  The
+// update therefore searches once per wave and span of consecutive indices and
+// streams the span's bucket runs (27 us, 5.0 TB/s); the gather keeps P (or a
+// sample of it) in LDS and runs several searches per thread side by side (84 us,
+// bound by the 128-byte line that each random read fetches: 541 MB, 6.4 TB/s).
 #include "gga_internal.h"
 
 namespace gga {
@@ -12,45 +19,149 @@ namespace {
 constexpr uint32_t kGlobalThreads = 256;
 constexpr uint32_t kGlobalBlocks = 8192;  // 32 workgroups per CU, grid-stride
 
-// Largest v < V with prefix[v] <= i, given i < prefix[V].
-__device__ __forceinline__ uint32_t vector_of(const uint64_t* prefix, uint32_t V, uint64_t i) {
-  uint32_t lo = 0, hi = V;  // prefix[lo] <= i < prefix[hi]
-  while (hi - lo > 1) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (prefix[mid] <= i) lo = mid;
-    else hi = mid;
-  }
-  return lo;
-}
-
+// Address of element j of LFVector v.
 template <typename T>
-__device__ __forceinline__ gptr<T> element_at(const ArrRef& A, uint64_t i) {
-  const uint32_t v = vector_of(A.prefix, A.V, i);
-  const uint64_t j = i - A.prefix[v];
+__device__ __forceinline__ gptr<T> element_of(const ArrRef& A, uint32_t v, uint64_t j) {
   const uint32_t b = bucket_of(A.log2F, j);
   return gmem(reinterpret_cast<T*>(A.bptr[(uint64_t)v * kMaxBuckets + b])) + offset_in(A.log2F, j, b);
 }
 
+// x = op(x) over n elements from p on, by one wave, kU vectors per lane in flight
+// (unconditional loads, clamped indices; only the lane that owns a vector stores it).
+template <typename T, uint32_t kU>
+__device__ __forceinline__ void wave_rw_run(gptr<T> p, uint32_t n, uint32_t op) {
+  constexpr uint32_t VPL = 16 / sizeof(T);
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t mis = (uint32_t)((reinterpret_cast<uintptr_t>((T*)p) / sizeof(T)) & (VPL - 1));
+  uint32_t head = mis ? VPL - mis : 0u;
+  if (head > n) head = n;
+  const uint32_t nv = (n - head) / VPL, tail = head + nv * VPL;
+  const gptr<u32x4> vp = reinterpret_cast<gptr<u32x4>>(p + head);
+  for (uint32_t q0 = 0; q0 < nv; q0 += kU * 64) {
+    u32x4 x[kU];
+#pragma unroll
+    for (uint32_t k = 0; k < kU; ++k) {
+      const uint32_t q = q0 + 64u * k + lane;
+      x[k] = vp[q < nv ? q : nv - 1];
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < kU; ++k) {
+      const uint32_t q = q0 + 64u * k + lane;
+      if (q < nv) __builtin_nontemporal_store(op_vec<T>(op, x[k]), vp + q);
+    }
+  }
+  if (lane < head) p[lane] = apply_op<T>(op, p[lane]);
+  if (tail + lane < n) p[tail + lane] = apply_op<T>(op, p[tail + lane]);
+}
+
+// One wave per span of 8 KiB of consecutive global indices.  The span's first
+// LFVector comes from one 64-way search of P; then, while the span reaches at
+// most kRunVectors LFVectors, its bucket runs are streamed in order.  A span over
+// more of them (short LFVectors) takes its elements one by one, each search
+// limited to the LFVectors that the span reaches.
+constexpr uint32_t kRunVectors = 8;
 template <typename T>
 __global__ __launch_bounds__(kGlobalThreads) void rw_global_kernel(ArrRef A, uint32_t op) {
+  constexpr uint32_t kU = 8, kSpan = 64 * kU * (16 / sizeof(T));
   const uint64_t n = A.prefix[A.V];
-  const uint64_t stride = (uint64_t)gridDim.x * kGlobalThreads;
-  for (uint64_t i = (uint64_t)blockIdx.x * kGlobalThreads + threadIdx.x; i < n; i += stride) {
-    const gptr<T> p = element_at<T>(A, i);
-    *p = apply_op<T>(op, *p);
+  const uint64_t waves = (uint64_t)gridDim.x * (kGlobalThreads / 64);
+  const uint32_t lane = threadIdx.x & 63u;
+  for (uint64_t w = (uint64_t)blockIdx.x * (kGlobalThreads / 64) + (threadIdx.x >> 6); w * kSpan < n; w += waves) {
+    const uint64_t i0 = w * kSpan, i1 = i0 + kSpan < n ? i0 + kSpan : n;
+    uint32_t v = wave_search(A.prefix, A.V, i0);
+    const uint32_t reach = A.prefix[v + 1] >= i1 ? 1u : wave_search(A.prefix + v, A.V - v, i1 - 1) + 1;
+    if (reach <= kRunVectors) {
+      uint64_t p0 = A.prefix[v], p1 = A.prefix[v + 1];
+      for (uint64_t i = i0; i < i1;) {
+        if (i >= p1) {  // the next LFVector (an empty one ends where it starts)
+          ++v;
+          p0 = p1;
+          p1 = A.prefix[v + 1];
+          continue;
+        }
+        const uint64_t j = i - p0;
+        const uint32_t b = bucket_of(A.log2F, j);
+        uint64_t end = p0 + bucket_start(A.log2F, b) + bucket_len(A.log2F, b);
+        if (end > p1) end = p1;
+        if (end > i1) end = i1;
+        const gptr<T> p = gmem(reinterpret_cast<T*>(A.bptr[(uint64_t)v * kMaxBuckets + b])) + offset_in(A.log2F, j, b);
+        wave_rw_run<T, kU>(p, (uint32_t)(end - i), op);
+        i = end;
+      }
+      continue;
+    }
+    const uint64_t* P = A.prefix + v;
+    for (uint64_t i = i0 + lane; i < i1; i += 64) {
+      uint32_t lo = 0, hi = reach;  // P[lo] <= i, and i < P[hi] or hi == reach
+      while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (P[mid] <= i) lo = mid;
+        else hi = mid;
+      }
+      const gptr<T> p = element_of<T>(A, v + lo, i - P[lo]);
+      *p = apply_op<T>(op, *p);
+    }
   }
 }
 
+// Every workgroup keeps P[0], P[2^k], P[2 2^k], ... in LDS, k the smallest that
+// leaves at most kSample entries (all of P up to 2048 LFVectors; 16 KiB keep eight
+// workgroups on a CU).  A thread searches for kReads indices side by side, first
+// there, then, for k > 0, in the 2^k entries of P after the one found.
+constexpr uint32_t kSample = 2048;
+constexpr uint32_t kReads = 4;
 template <typename T>
-__global__ __launch_bounds__(kGlobalThreads) void gather_kernel(ArrRef A, const uint64_t* idx, uint64_t n,
-                                                               T* out) {
+__global__ __launch_bounds__(kGlobalThreads) void gather_kernel(ArrRef A, const uint64_t* idx, uint64_t n, T* out,
+                                                               uint32_t k, uint32_t top) {
+  __shared__ uint64_t s_p[kSample];
+  const uint32_t tid = threadIdx.x;
   const uint64_t size = A.prefix[A.V];
-  const uint64_t stride = (uint64_t)gridDim.x * kGlobalThreads;
+  const uint32_t ns = (A.V + (1u << k) - 1) >> k;
+  for (uint32_t q = tid; q < ns; q += kGlobalThreads) s_p[q] = A.prefix[(uint64_t)q << k];
+  __syncthreads();
   bool bad = false;
-  for (uint64_t k = (uint64_t)blockIdx.x * kGlobalThreads + threadIdx.x; k < n; k += stride) {
-    const uint64_t i = idx[k];
-    if (i < size) out[k] = *element_at<T>(A, i);
-    else bad = true;
+  for (uint64_t c = (uint64_t)blockIdx.x * kGlobalThreads * kReads; c < n;
+       c += (uint64_t)gridDim.x * kGlobalThreads * kReads) {
+    uint64_t i[kReads];
+    uint32_t v[kReads];
+#pragma unroll
+    for (uint32_t u = 0; u < kReads; ++u) {
+      const uint64_t q = c + u * kGlobalThreads + tid;
+      i[u] = idx[q < n ? q : n - 1];
+      v[u] = 0;
+    }
+    for (uint32_t step = top; step; step >>= 1) {  // the last sample at or below i
+#pragma unroll
+      for (uint32_t u = 0; u < kReads; ++u) {
+        const uint32_t m = v[u] + step;
+        if (m < ns && s_p[m] <= i[u]) v[u] = m;
+      }
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kReads; ++u) v[u] <<= k;
+    for (uint32_t step = (1u << k) >> 1; step; step >>= 1) {
+#pragma unroll
+      for (uint32_t u = 0; u < kReads; ++u) {
+        const uint32_t m = v[u] + step;
+        if (m < A.V && A.prefix[m] <= i[u]) v[u] = m;
+      }
+    }
+    uint64_t p[kReads], off[kReads];
+#pragma unroll
+    for (uint32_t u = 0; u < kReads; ++u) {  // an index past the size reads the table's first word, unused
+      const bool in = i[u] < size;
+      const uint64_t j = in ? i[u] - (k ? A.prefix[v[u]] : s_p[v[u]]) : 0;
+      const uint32_t b = bucket_of(A.log2F, j);
+      p[u] = A.bptr[in ? (uint64_t)v[u] * kMaxBuckets + b : 0];
+      off[u] = offset_in(A.log2F, j, b);
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kReads; ++u) {
+      const uint64_t q = c + u * kGlobalThreads + tid;
+      if (q >= n) continue;
+      if (i[u] < size) out[q] = gmem(reinterpret_cast<T*>(p[u]))[off[u]];
+      else bad = true;
+    }
   }
   if (bad) set_error(A.err, kErrRange);
 }
@@ -58,23 +169,30 @@ __global__ __launch_bounds__(kGlobalThreads) void gather_kernel(ArrRef A, const 
 }  // namespace
 
 int launch_rw_global(ggarray* a, uint32_t op, hipStream_t s) {
+  // A wave per span of the host's bound of the size, looping beyond.
+  const uint64_t spans = (a->size_ub >> (13u - a->elem_log2)) + 1, per = kGlobalThreads / 64;
+  const dim3 grid((uint32_t)(spans < kGlobalBlocks * per ? (spans + per - 1) / per : kGlobalBlocks));
   if (a->elem_bytes == 4)
-    hipLaunchKernelGGL(rw_global_kernel<uint32_t>, dim3(kGlobalBlocks), dim3(kGlobalThreads), 0, s, a->ref, op);
+    hipLaunchKernelGGL(rw_global_kernel<uint32_t>, grid, dim3(kGlobalThreads), 0, s, a->ref, op);
   else
-    hipLaunchKernelGGL(rw_global_kernel<uint64_t>, dim3(kGlobalBlocks), dim3(kGlobalThreads), 0, s, a->ref, op);
+    hipLaunchKernelGGL(rw_global_kernel<uint64_t>, grid, dim3(kGlobalThreads), 0, s, a->ref, op);
   return hip_status(hipGetLastError());
 }
 
 int launch_gather(ggarray* a, const uint64_t* idx, uint64_t n, void* out, hipStream_t s) {
   if (n == 0) return GGA_OK;
-  uint64_t blocks = (n + kGlobalThreads - 1) / kGlobalThreads;
+  constexpr uint64_t kPer = kGlobalThreads * kReads;
+  uint64_t blocks = (n + kPer - 1) / kPer;
   if (blocks > kGlobalBlocks) blocks = kGlobalBlocks;
+  uint32_t k = 0, top = 1;
+  while (((a->V + (1u << k) - 1) >> k) > kSample) ++k;
+  while (2 * top < ((a->V + (1u << k) - 1) >> k)) top *= 2;
   if (a->elem_bytes == 4)
     hipLaunchKernelGGL(gather_kernel<uint32_t>, dim3((uint32_t)blocks), dim3(kGlobalThreads), 0, s, a->ref, idx, n,
-                       static_cast<uint32_t*>(out));
+                       static_cast<uint32_t*>(out), k, top);
   else
     hipLaunchKernelGGL(gather_kernel<uint64_t>, dim3((uint32_t)blocks), dim3(kGlobalThreads), 0, s, a->ref, idx, n,
-                       static_cast<uint64_t*>(out));
+                       static_cast<uint64_t*>(out), k, top);
   return hip_status(hipGetLastError());
 }
 
