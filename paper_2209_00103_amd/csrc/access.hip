@@ -671,7 +671,25 @@ __global__ __launch_bounds__(kRwThreads) void serve_stream_kernel(const ServeIte
   }
 }
 
+// Sizes of the arrays of a server, one workgroup per array.
+__global__ __launch_bounds__(256) void serve_sizes_kernel(const SizeItem* items, uint64_t* out) {
+  __shared__ uint64_t red[4];
+  const SizeItem it = items[blockIdx.x];
+  uint64_t s = 0;
+  for (uint32_t v = threadIdx.x; v < it.V; v += 256) s += it.size[v];
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d, 64);
+  if ((threadIdx.x & 63u) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) out[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+}
+
 }  // namespace
+
+int launch_serve_sizes(const SizeItem* items, uint32_t n, uint64_t* out, hipStream_t s) {
+  hipLaunchKernelGGL(serve_sizes_kernel, dim3(n), dim3(256), 0, s, items, out);
+  return hip_status(hipGetLastError());
+}
 
 int launch_serve_stream(const ServeItem* items, uint32_t n, uint64_t* tile_begin, uint64_t* elem_begin,
                         uint32_t* err, uint32_t elem_bytes, uint32_t grid, hipStream_t s) {

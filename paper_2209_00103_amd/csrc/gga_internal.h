@@ -241,6 +241,12 @@ struct ServeItem {
   uint32_t elem_log2;
 };
 
+// Where a server finds the sizes of one of its arrays.
+struct SizeItem {
+  const uint64_t* size;
+  uint64_t V;
+};
+
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // The r/w operation on the elements of one 16-byte vector.
@@ -454,6 +460,8 @@ constexpr uint32_t kServeFusedItems = 4096;
 int launch_serve_front(const BatchArr* items, const uint64_t* begins, uint32_t n_a, uint64_t blocks,
                        const ServeItem* sitems, uint32_t n_s, uint32_t elem_bytes, uint64_t seed, uint32_t round,
                        uint32_t shift, hipStream_t s);
+// launch_serve_sizes: the sizes of a server's n arrays into out (device), one launch.
+int launch_serve_sizes(const SizeItem* items, uint32_t n, uint64_t* out, hipStream_t s);
 int launch_serve_stream(const ServeItem* items, uint32_t n, uint64_t* tile_begin, uint64_t* elem_begin,
                         uint32_t* err, uint32_t elem_bytes, uint32_t grid, hipStream_t s);
 

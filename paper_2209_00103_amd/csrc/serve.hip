@@ -103,6 +103,8 @@ struct gga_server {
   std::vector<Lane> lanes;
   uint64_t table_bytes = 0;  // fixed part of a lane block: the largest step table
   uint64_t* h_sizes = nullptr;
+  SizeItem* d_size_items = nullptr;  // where each array's sizes are; the sums follow (n words)
+  uint64_t* d_sizes = nullptr;
   std::vector<hipEvent_t> rq_events;  // per-request mode
 };
 
@@ -131,6 +133,7 @@ void destroy_server(gga_server* sv) {
   }
   for (hipEvent_t e : sv->rq_events) hipEventDestroy(e);
   if (sv->h_sizes) hipHostFree(sv->h_sizes);
+  if (sv->d_size_items) hipFree(sv->d_size_items);
   delete sv;
 }
 
@@ -187,19 +190,19 @@ struct RunState {
   }
 };
 
+// The arrays' sizes at the start of a run: one launch and one copy for all of them
+// (a scan launch and a copy per array took 3.1 of a run's 5.4 ms with 512 arrays
+// and 8192 requests).
 int read_sizes(gga_server* sv, std::vector<uint64_t>& size) {
   hipStream_t s = sv->lanes[0].s;
+  const size_t n = sv->arrays.size();
   if (hipDeviceSynchronize() != hipSuccess) return GGA_EHIP;
-  for (size_t i = 0; i < sv->arrays.size(); ++i) {
-    ggarray* a = sv->arrays[i];
-    const int rc = launch_scan(a, s);
-    if (rc) return rc;
-    if (hipMemcpyAsync(sv->h_sizes + i, a->ref.prefix + a->V, sizeof(uint64_t), hipMemcpyDeviceToHost, s) !=
-        hipSuccess)
-      return GGA_EHIP;
-  }
-  if (hipStreamSynchronize(s) != hipSuccess) return GGA_EHIP;
-  for (size_t i = 0; i < sv->arrays.size(); ++i) size[i] = sv->h_sizes[i];
+  const int rc = launch_serve_sizes(sv->d_size_items, (uint32_t)n, sv->d_sizes, s);
+  if (rc) return rc;
+  if (hipMemcpyAsync(sv->h_sizes, sv->d_sizes, sizeof(uint64_t) * n, hipMemcpyDeviceToHost, s) != hipSuccess ||
+      hipStreamSynchronize(s) != hipSuccess)
+    return GGA_EHIP;
+  for (size_t i = 0; i < n; ++i) size[i] = sv->h_sizes[i];
   return GGA_OK;
 }
 
@@ -549,7 +552,15 @@ int gga_server_create(gga_server** out, ggarray* const* arrays, uint32_t n, void
   sv->table_bytes = align_up(L.used, kAlign);
   const uint64_t block = sv->table_bytes + 2ull * (m + 1) * sizeof(uint64_t) + kAlign;
   bool ok = hipHostMalloc(reinterpret_cast<void**>(&sv->h_sizes), sizeof(uint64_t) * n, hipHostMallocDefault) ==
+            hipSuccess &&
+            hipMalloc(reinterpret_cast<void**>(&sv->d_size_items), (sizeof(SizeItem) + sizeof(uint64_t)) * n) ==
             hipSuccess;
+  if (ok) {
+    sv->d_sizes = reinterpret_cast<uint64_t*>(sv->d_size_items + n);
+    std::vector<SizeItem> items(n);
+    for (uint32_t i = 0; i < n; ++i) items[i] = SizeItem{arrays[i]->ref.size, arrays[i]->V};
+    ok = hipMemcpy(sv->d_size_items, items.data(), sizeof(SizeItem) * n, hipMemcpyHostToDevice) == hipSuccess;
+  }
   sv->lanes.resize(nl);
   for (Lane& l : sv->lanes) {
     if (!ok) break;
