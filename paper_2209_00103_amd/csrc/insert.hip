@@ -1150,23 +1150,25 @@ __global__ __launch_bounds__(256) void static_atomic_kernel(StaticRef S, uint64_
 // across the wave (partial lines left by element-wise stores cost about 5% extra
 // HBM writes, measured), then the ragged tail.  Bucket and offset are computed
 // once per run, not per element.  The map covers 8192 outputs at a time.
-template <typename Prod>
+template <typename Prod, int K = kCountK>
 __device__ __forceinline__ uint32_t produce_counts(const Prod& prod, uint64_t gt, uint64_t gend,
                                                    uint32_t* cnt) {
   uint32_t c = 0;
 #pragma unroll
-  for (int j = 0; j < kCountK; ++j) {
+  for (int j = 0; j < K; ++j) {
     cnt[j] = (gt + j < gend) ? prod.count(gt + j) : 0u;
     c += cnt[j];
   }
   return c;
 }
 
-// Outputs own[0 .. n) of a run, stored at dst (element-aligned).
-template <typename T, class Prod>
+// Outputs own[0 .. n) of a run, stored at dst (element-aligned) by a workgroup of
+// kThreads threads.
+template <typename T, class Prod, uint32_t kThreads = kB>
 __device__ __forceinline__ void store_owned_run(T* dst_, const uint16_t* own, uint32_t n, const Prod& prod,
                                                 uint64_t g0) {
   constexpr uint32_t VPL = 16 / sizeof(T), kLine = 128 / sizeof(T);
+  static_assert(kLine <= kThreads, "head and tail in one store each");
   const uint32_t tid = threadIdx.x;
   const gptr<T> dst = gmem(dst_);
   const uint32_t mis = (uint32_t)((reinterpret_cast<uintptr_t>(dst_) & 127u) / sizeof(T));
@@ -1177,7 +1179,7 @@ __device__ __forceinline__ void store_owned_run(T* dst_, const uint16_t* own, ui
     __builtin_nontemporal_store(prod.value(g0 + (o >> 4), o & 15u), dst + tid);
   }
   const uint32_t nv = (n - head) / VPL;
-  for (uint32_t q = tid; q < nv; q += kB) {
+  for (uint32_t q = tid; q < nv; q += kThreads) {
     const uint32_t e = head + q * VPL;
     T tmp[VPL];
 #pragma unroll
@@ -1284,6 +1286,75 @@ __global__ __launch_bounds__(kB) void insert_count_kernel(ArrRef A, StaticRef S,
       i += run;
     }
   }
+}
+
+// Many LFVectors of one short tile each: one wave per LFVector, K logical threads
+// per lane, with nothing shared between waves.  The tile's own chain (counts, one
+// allocation after another, then the stores) takes about 12 us whatever its size,
+// so what counts is how many tiles a CU holds: 32 in this form, 8 as workgroups of
+// four waves, most of whose lanes a short tile leaves idle (V = 65536, Poisson(3),
+// 8-byte elements: 364 -> 140 us at 256 threads per LFVector, 416 -> 250 us at 512;
+// at 1024 the workgroup's four waves are all at work and measured 590 against
+// 720 us with 16 threads per lane).
+constexpr uint32_t kOwnWave = 2048;  // outputs per owner-map pass of a wave (4 KiB)
+template <typename T, class Prod, int K>
+__global__ __launch_bounds__(64) void insert_count_wave_kernel(ArrRef A, TileArgs I, Prod prod) {
+  static_assert(K <= 16, "owner entries: 10 bits of logical thread, 4 of element");
+  __shared__ uint16_t s_own[kOwnWave];
+  const uint32_t v = blockIdx.x, lane = lane_id();
+  uint64_t g0, gend;
+  tile_range(I, v, 0, 64 * K, g0, gend);
+  if (g0 >= gend || A.dead[v]) return;
+  const uint64_t size0 = A.size[v];
+  uint32_t cnt[K];
+  const uint32_t c = produce_counts<Prod, K>(prod, g0 + (uint64_t)lane * K, gend, cnt);
+  const uint32_t incl = wave_incl_scan(c), n_t = __shfl(incl, 63, 64);
+  const WaveRes r = resolve_wave(A, I, v, 0, 0, true, n_t, size0, 0);
+  const uint32_t log2F = A.log2F;
+  for (uint32_t w0 = 0; w0 < r.n_out; w0 += kOwnWave) {
+    const uint32_t w1 = r.n_out - w0 < kOwnWave ? r.n_out : w0 + kOwnWave;
+    uint32_t e = incl - c - w0;  // wraps for outputs before the window, which fail the test
+#pragma unroll
+    for (uint32_t j = 0; j < (uint32_t)K; ++j) {
+      const uint32_t ent = (lane * K + j) << 4;
+      for (uint32_t q = 0; q < cnt[j]; ++q, ++e)
+        if (e < kOwnWave) s_own[e] = (uint16_t)(ent | q);
+    }
+    __syncthreads();  // one wave: its LDS writes before its reads
+    for (uint32_t i = w0; i < w1;) {  // one run per bucket the window's outputs reach
+      const uint64_t idx = r.base + i;
+      const uint32_t b = bucket_of(log2F, idx);
+      const uint64_t bs = bucket_start(log2F, b);
+      const uint64_t room = bs + bucket_len(log2F, b) - idx;
+      const uint32_t run = (uint64_t)(w1 - i) < room ? w1 - i : (uint32_t)room;
+      const uint64_t p = __shfl(r.bp, (int)(b - r.b_lo), 64);
+      if (p > kFailedPtr)
+        store_owned_run<T, Prod, 64>(reinterpret_cast<T*>(p) + (idx - bs), s_own + (i - w0), run, prod, g0);
+      i += run;
+    }
+    __syncthreads();  // the window is read before the next one is written
+  }
+}
+
+// A multi-element round as insert_count_wave_kernel (K = 4 or 8 logical threads per
+// lane) or insert_count_kernel.  Fewer than 2048 LFVectors leave a CU short of
+// waves in the first form (512 threads per LFVector, workgroup against wave: 12.6
+// against 16.0 us at V = 512, 23.6 against 19.4 us at V = 2048; 256 threads: 11.2
+// against 10.7 us at V = 512, 22.0 against 13.3 us at V = 2048).
+constexpr uint32_t kCountWaveMinV = 2048;
+template <typename T, class Prod, bool kStatic>
+void launch_counts(const ArrRef& A, const StaticRef& S, const TileArgs& I, const Prod& p, uint64_t ntiles,
+                   hipStream_t s) {
+  if constexpr (!kStatic) {
+    if (I.tpv == 1 && I.chunk <= 512 && A.V >= kCountWaveMinV) {
+      if (I.chunk <= 256)
+        hipLaunchKernelGGL((insert_count_wave_kernel<T, Prod, 4>), dim3(A.V), dim3(64), 0, s, A, I, p);
+      else
+        hipLaunchKernelGGL((insert_count_wave_kernel<T, Prod, 8>), dim3(A.V), dim3(64), 0, s, A, I, p);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((insert_count_kernel<T, Prod, kStatic>), dim3((uint32_t)ntiles), dim3(kB), 0, s, A, S, I, p);
 }
 
 // ------------------------------------------- packed multi-element producer --
@@ -1899,7 +1970,7 @@ __global__ __launch_bounds__(64) void flag_copy_blocked_kernel(ArrRef A, TileArg
 template <typename T, bool kStatic>
 int dispatch(const ArrRef& A, const StaticRef& S, const TileArgs& I, const InsertDesc& d,
              uint64_t ntiles, hipStream_t s) {
-  const dim3 grid((uint32_t)ntiles), block(kB);
+  const dim3 grid((uint32_t)ntiles);
   switch (d.mode) {
     case kModeBuffer: {
       ProdBuffer<T> p{static_cast<const T*>(d.values), d.flags};
@@ -1923,7 +1994,7 @@ int dispatch(const ArrRef& A, const StaticRef& S, const TileArgs& I, const Inser
     }
     case kModeCounts: {
       ProdCounts<T> p{static_cast<const T*>(d.values), d.flags, d.max_count};
-      hipLaunchKernelGGL((insert_count_kernel<T, ProdCounts<T>, kStatic>), grid, block, 0, s, A, S, I, p);
+      launch_counts<T, ProdCounts<T>, kStatic>(A, S, I, p, ntiles, s);
       break;
     }
     case kModePoisson: {
@@ -1932,7 +2003,7 @@ int dispatch(const ArrRef& A, const StaticRef& S, const TileArgs& I, const Inser
       p.round = d.round;
       p.max_count = d.max_count;
       for (int k = 0; k < 16; ++k) p.thr[k] = d.thresholds[k];
-      hipLaunchKernelGGL((insert_count_kernel<T, ProdPoisson<T>, kStatic>), grid, block, 0, s, A, S, I, p);
+      launch_counts<T, ProdPoisson<T>, kStatic>(A, S, I, p, ntiles, s);
       break;
     }
     default:
