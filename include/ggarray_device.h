@@ -196,11 +196,13 @@ __device__ __forceinline__ uint32_t pool_shard(uint32_t v, uint32_t b, uint32_t 
   return (v + b + salt) & (uint32_t)(kFreeShards - 1);
 }
 __device__ __forceinline__ uint32_t arena_shard(uint32_t f) { return (f >> 4) & (uint32_t)(kArenaShards - 1); }
-// The statistics words a block is counted in: neighbouring free-list shards use
-// different lines (16 LFVectors that share an arena shard would otherwise meet on
-// one counter line in every allocation and release; a clear of configuration 4's
-// 81224 LFVectors measured 136 against 95 us).  Only their sum is ever read.
-__device__ __forceinline__ uint32_t stat_shard(uint32_t f) { return f & (uint32_t)(kArenaShards - 1); }
+// The statistics line that this workgroup's allocations and releases are counted
+// in.  It is the same for every lane, so the compiler adds a wave's counts up and
+// issues one atomic per word and wave: additions to one line are performed one
+// after another, some 45 ns each, and with a line chosen by bucket they held up a
+// clear of 65536 LFVectors of four buckets (82 -> 59 us).
+// Only the sums over all lines are ever read.
+__device__ __forceinline__ PoolShard* stat_line(PoolHdr* H) { return &H->shard[blockIdx.x & (uint32_t)(kArenaShards - 1)]; }
 
 __device__ __forceinline__ bool cas_rlx(uint64_t* p, uint64_t& expected, uint64_t desired) {
   return __hip_atomic_compare_exchange_strong(p, &expected, desired, __ATOMIC_RELAXED,
@@ -297,16 +299,21 @@ __device__ __forceinline__ uint8_t* pool_alloc(PoolRef P, uint32_t cls, uint32_t
     }
   }
   if (!q) return nullptr;
-  add_nr(&H->shard[stat_shard(fs)].in_use, bytes);
-  add_nr(&H->shard[stat_shard(fs)].n_alloc, 1ull);
+  add_nr(&stat_line(H)->in_use, bytes);
+  add_nr(&stat_line(H)->n_alloc, 1ull);
   return q;
 }
 
-__device__ __forceinline__ void pool_free(PoolRef P, uint8_t* ptr, uint32_t cls, uint32_t s) {
+// The free list's head for a release, read ahead of pool_free (any value it held is
+// good to start from: the swap fails on a stale one and brings the current).
+__device__ __forceinline__ uint64_t pool_head(PoolRef P, uint32_t cls, uint32_t s) {
+  return ld_rlx(&P.hdr->heads[(uint64_t)cls * kFreeShards + s]);
+}
+
+__device__ __forceinline__ void pool_free(PoolRef P, uint8_t* ptr, uint32_t cls, uint32_t s, uint64_t h) {
   PoolHdr* H = P.hdr;
   const uint64_t idx = ((uint64_t)(ptr - P.base) >> kMinClassLog2) + 1;
   uint64_t* head = &H->heads[(uint64_t)cls * kFreeShards + s];
-  uint64_t h = ld_rlx(head);
   for (;;) {
     const uint64_t prev = __hip_atomic_exchange(reinterpret_cast<uint64_t*>(ptr), h & kIdxMask,
                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -319,8 +326,11 @@ __device__ __forceinline__ void pool_free(PoolRef P, uint8_t* ptr, uint32_t cls,
   if ((h & kIdxMask) == 0)
     __hip_atomic_fetch_or(&H->nonempty[cls][s >> 6], 1ull << (s & 63), __ATOMIC_RELAXED,
                           __HIP_MEMORY_SCOPE_AGENT);
-  sub_nr(&H->shard[stat_shard(s)].in_use, 1ull << cls);
-  add_nr(&H->shard[stat_shard(s)].n_free, 1ull);
+  sub_nr(&stat_line(H)->in_use, 1ull << cls);
+  add_nr(&stat_line(H)->n_free, 1ull);
+}
+__device__ __forceinline__ void pool_free(PoolRef P, uint8_t* ptr, uint32_t cls, uint32_t s) {
+  pool_free(P, ptr, cls, s, pool_head(P, cls, s));
 }
 
 // A block of class cls taken for free-list shard s and given back to it in the
@@ -334,8 +344,8 @@ __device__ __forceinline__ bool pool_alloc_release(PoolRef P, uint32_t cls, uint
   PoolHdr* H = P.hdr;
   if (cls <= (uint32_t)kMaxClassLog2 && !H->fault_at &&
       (ld_rlx(&H->heads[(uint64_t)cls * kFreeShards + s]) & kIdxMask)) {
-    add_nr(&H->shard[stat_shard(s)].n_alloc, 1ull);
-    add_nr(&H->shard[stat_shard(s)].n_free, 1ull);
+    add_nr(&stat_line(H)->n_alloc, 1ull);
+    add_nr(&stat_line(H)->n_free, 1ull);
     return true;
   }
   uint8_t* p = pool_alloc(P, cls, s);
@@ -355,8 +365,8 @@ __device__ __forceinline__ bool pool_reuse(PoolRef P, uint32_t s) {
   PoolHdr* H = P.hdr;
   const uint64_t fault_at = H->fault_at;
   if (fault_at && fetch_add(&H->n_attempt, 1) + 1 == fault_at) return false;
-  add_nr(&H->shard[stat_shard(s)].n_alloc, 1ull);
-  add_nr(&H->shard[stat_shard(s)].n_free, 1ull);
+  add_nr(&stat_line(H)->n_alloc, 1ull);
+  add_nr(&stat_line(H)->n_free, 1ull);
   return true;
 }
 

@@ -189,12 +189,21 @@ __global__ __launch_bounds__(kScanThreads) void scan_fix_kernel(ArrRef A, const 
   }
 }
 
-constexpr uint32_t kVecPerBlock = 4;  // shrink: 256 threads = 4 waves = 4 LFVectors
+constexpr uint32_t kVecPerBlock = 4;  // one wave per LFVector: 256 threads = 4 LFVectors
 
+// kLanes lanes per LFVector.  A clear is a chain of dependent atomics per bucket.
+// While a wave per LFVector fits the chip's 8192 wave slots it is the shortest; a
+// few thousand LFVectors more come in turns, and four of them share a wave (V =
+// 8192, 13 buckets: 19.6 -> 16.6 us; V = 16384, 2 buckets: 24.1 -> 21.8 us).  From
+// 32768 on, the LFVectors that share a free list (every 4096th) would then be in
+// flight together and retry each other's swaps, so a wave each it is again (V =
+// 65536, 2 and 4 buckets: 48 and 59 us, against 52 and 89 us).
+inline bool shrink_shares_wave(uint64_t V) { return V >= 4096 && V < 32768; }
+template <uint32_t kLanes>
 __global__ __launch_bounds__(256) void shrink_kernel(ArrRef A, uint32_t num, uint32_t den,
                                                      uint32_t elem_log2) {
-  const uint32_t v = blockIdx.x * kVecPerBlock + (threadIdx.x >> 6);
-  if (v < A.V) shrink_vector(A, v, num, den, elem_log2);
+  const uint32_t v = (blockIdx.x * 256 + threadIdx.x) / kLanes;
+  if (v < A.V) shrink_vector<kLanes>(A, v, num, den, elem_log2);
 }
 
 // Returns every bucket of the array to the pool (destroy).
@@ -554,14 +563,16 @@ __global__ __launch_bounds__(kScanThreads) void batch_top_kernel(const Item* ite
   }
 }
 
-// Shrink of every array of the batch: one wave per LFVector; the waves of array
-// i are [vbegin[i], vbegin[i+1]).
+// Shrink of every array of the batch, kLanes lanes per LFVector as for one array;
+// LFVector w of the batch is w - vbegin[i] of array i = varr[w].
+template <uint32_t kLanes>
 __global__ __launch_bounds__(256) void batch_shrink_kernel(const BatchArr* items, const uint64_t* vbegin,
-                                                           uint32_t n, uint32_t num, uint32_t den) {
-  const uint64_t w = (uint64_t)blockIdx.x * kVecPerBlock + (threadIdx.x >> 6);
-  if (w >= vbegin[n]) return;
-  const uint32_t i = wave_search(vbegin, n, w);
-  shrink_vector(items[i].A, (uint32_t)(w - vbegin[i]), num, den, items[i].elem_log2);
+                                                           const uint32_t* varr, uint64_t total, uint32_t num,
+                                                           uint32_t den) {
+  const uint64_t w = ((uint64_t)blockIdx.x * 256 + threadIdx.x) / kLanes;
+  if (w >= total) return;
+  const uint32_t i = varr[w];
+  shrink_vector<kLanes>(items[i].A, (uint32_t)(w - vbegin[i]), num, den, items[i].elem_log2);
 }
 
 // r/w or flatten of every array of the batch.  With a tile table covering the
@@ -739,8 +750,10 @@ int launch_scan(ggarray* a, hipStream_t s, uint64_t* copy) {
 
 int launch_shrink(ggarray* a, uint32_t num, uint32_t den, hipStream_t s) {
   if (num == den) a->size_ub = 0;
-  const uint32_t blocks = (a->V + kVecPerBlock - 1) / kVecPerBlock;
-  hipLaunchKernelGGL(shrink_kernel, dim3(blocks), dim3(256), 0, s, a->ref, num, den, a->elem_log2);
+  if (shrink_shares_wave(a->V))
+    hipLaunchKernelGGL(shrink_kernel<16>, dim3((a->V + 15) / 16), dim3(256), 0, s, a->ref, num, den, a->elem_log2);
+  else
+    hipLaunchKernelGGL(shrink_kernel<64>, dim3((a->V + 3) / 4), dim3(256), 0, s, a->ref, num, den, a->elem_log2);
   sizes_changed(a, s);
   return hip_status(hipGetLastError());
 }
@@ -996,9 +1009,13 @@ static int ensure_batch_table(gga_batch* b, hipStream_t s, const uint64_t** tab,
 int launch_batch_shrink(gga_batch* b, uint32_t num, uint32_t den, hipStream_t s) {
   if (num == den)
     for (uint32_t i = 0; i < b->n; ++i) b->arrays[i]->size_ub = 0;
-  const uint64_t blocks = (b->total_vectors + kVecPerBlock - 1) / kVecPerBlock;
-  hipLaunchKernelGGL(batch_shrink_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b->d_arrays, b->d_vbegin,
-                     b->n, num, den);
+  const uint64_t V = b->total_vectors;
+  if (shrink_shares_wave(V))
+    hipLaunchKernelGGL(batch_shrink_kernel<16>, dim3((uint32_t)((V + 15) / 16)), dim3(256), 0, s, b->d_arrays,
+                       b->d_vbegin, b->d_varr, V, num, den);
+  else
+    hipLaunchKernelGGL(batch_shrink_kernel<64>, dim3((uint32_t)((V + 3) / 4)), dim3(256), 0, s, b->d_arrays,
+                       b->d_vbegin, b->d_varr, V, num, den);
   for (uint32_t i = 0; i < b->n; ++i) sizes_changed(b->arrays[i], s);
   return hip_status(hipGetLastError());
 }

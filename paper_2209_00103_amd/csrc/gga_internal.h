@@ -289,32 +289,36 @@ __host__ __device__ __forceinline__ uint64_t shrink_keep(uint64_t s, uint32_t nu
   return s - ((s / den) * num + ((s % den) * num) / den);
 }
 
-// Lane b of a wave releases bucket b of LFVector v when keep <= b < hi: a live
-// bucket goes back to the pool and its slot is cleared (a failed-allocation
-// marker is only cleared).  With `held` the caller passes the slot's value in
-// `cur` (a bucket it allocated itself), otherwise it is read.
+// Releases bucket b of LFVector v when keep <= b < hi: a live bucket goes back to
+// the pool and its slot is cleared (a failed-allocation marker is only cleared).
+// With `held` the caller passes the slot's value in `cur` (a bucket it allocated
+// itself), otherwise it is read, together with the head of the bucket's free list.
 __device__ __forceinline__ void release_bucket(const ArrRef& A, uint32_t v, uint32_t b, uint32_t keep, uint32_t hi,
                                                bool held, uint64_t cur, uint32_t elem_log2) {
   if (b < keep || b >= hi) return;
   uint64_t* slot = A.bptr + (uint64_t)v * kMaxBuckets + b;
+  const uint32_t cls = bucket_class(A.log2F, elem_log2, b), fs = pool_shard(v, b, A.salt);
+  const uint64_t h = pool_head(A.pool, cls < (uint32_t)kMaxClassLog2 ? cls : (uint32_t)kMaxClassLog2, fs);
   const uint64_t p = held ? cur : *slot;
-  if (p > kFailedPtr)
-    pool_free(A.pool, reinterpret_cast<uint8_t*>(p), bucket_class(A.log2F, elem_log2, b), pool_shard(v, b, A.salt));
+  if (p > kFailedPtr) pool_free(A.pool, reinterpret_cast<uint8_t*>(p), cls, fs, h);
   if (p) *slot = 0;
 }
 
-// Shrink (pop floor(s num / den) per LFVector) and bucket release: one wave per
-// LFVector, lane b looks after bucket b, so the releases of one LFVector run in
-// parallel and go to different pool shards.
+// Shrink (pop floor(s num / den) per LFVector) and bucket release by a group of
+// kLanes consecutive lanes of a wave, lane l of it looking after buckets l, l +
+// kLanes, ..., so that the releases of one LFVector run in parallel and go to
+// different pool shards.
+template <uint32_t kLanes = 64>
 __device__ __forceinline__ void shrink_vector(const ArrRef& A, uint32_t v, uint32_t num, uint32_t den,
                                               uint32_t elem_log2) {
-  const uint32_t b = threadIdx.x & 63u;
+  const uint32_t l = threadIdx.x & (kLanes - 1);
   const uint64_t s = A.size[v];
   const uint64_t ns = shrink_keep(s, num, den);
   uint32_t hi = A.dead[v] ? (uint32_t)kMaxBuckets : nbuckets_for(A.log2F, s);
   if (hi > (uint32_t)kMaxBuckets) hi = kMaxBuckets;
-  release_bucket(A, v, b, nbuckets_for(A.log2F, ns), hi, false, 0, elem_log2);
-  if (b == 0) A.size[v] = ns;  // every lane has read the old size: one wave, program order
+  const uint32_t keep = nbuckets_for(A.log2F, ns);
+  for (uint32_t b = l; b < hi; b += kLanes) release_bucket(A, v, b, keep, hi, false, 0, elem_log2);
+  if (l == 0) A.size[v] = ns;  // every lane has read the old size: one wave, program order
 }
 
 // Tiles of an LFVector of s elements: every bucket below s contributes
