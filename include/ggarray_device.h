@@ -38,13 +38,20 @@ constexpr uint32_t kErrStall = 4;   // a bounded wait expired; reported as GGA_E
 // waiting, far beyond any legitimate wait) it gives up and sets kErrStall, so a
 // logic error surfaces as a status instead of a kernel that never ends.
 constexpr uint32_t kSpinLimit = 1u << 22;
+constexpr uint64_t kNoChunk = 0xFFFFFFFFull;  // arena word's chunk id once the region has run out
+constexpr uint32_t kArenaPolls = 32;  // looks at an arena word whose next chunk another lane installs
 
-struct PoolShard {        // one 64-byte line per shard
+// One 128-byte line (an L2 line) each: atomics on one line are performed one after
+// another, so arena words and statistics do not share any.
+struct PoolShard {
   uint64_t arena;         // current chunk id (offset / 256 + 1) << 32 | used 256-byte units
-  uint64_t in_use;        // bytes handed out and not returned (may wrap per shard)
+  uint64_t pad[15];
+};
+struct PoolStat {
+  uint64_t in_use;        // bytes handed out and not returned (may wrap per line)
   uint64_t n_alloc;
   uint64_t n_free;
-  uint64_t pad[4];
+  uint64_t pad[13];
 };
 
 struct PoolHdr {
@@ -57,6 +64,7 @@ struct PoolHdr {
   uint64_t nonempty[kNumClasses][kFreeShards / 64];  // bit s: free list s of the class may hold blocks
   uint64_t heads[kNumClasses * kFreeShards];         // tagged Treiber-stack heads
   PoolShard shard[kArenaShards];
+  PoolStat stat[kArenaShards];
 };
 
 constexpr uint64_t kPoolHdrBytes = 2ull << 20;
@@ -181,8 +189,11 @@ __device__ __forceinline__ uint32_t bucket_class(uint32_t log2F, uint32_t elem_l
 //    carved from the global bump pointer, sub-allocated with one atomic add on
 //    the shard's arena word (chunk id << 32 | used 256-byte units).  The add that
 //    crosses the end of the chunk installs the next chunk; adds that land past
-//    the end in the meantime take their block from the global bump pointer
-//    instead of waiting.  Larger blocks always come from the global bump pointer.
+//    the end in the meantime look for it a few times (bounded) and only then take
+//    their block from the global bump pointer, one word that thousands of waves
+//    would otherwise meet on, some 45 ns each (the first round of 65536 LFVectors
+//    on a fresh pool, 310 -> 150 us; of 8192 with five buckets each, 257 -> 45 us).  Larger blocks always come from the global bump
+//    pointer.
 //  * Only when the region is exhausted does an allocation look through the other
 //    free lists (steal), guided by the hint masks.
 //
@@ -196,13 +207,21 @@ __device__ __forceinline__ uint32_t pool_shard(uint32_t v, uint32_t b, uint32_t 
   return (v + b + salt) & (uint32_t)(kFreeShards - 1);
 }
 __device__ __forceinline__ uint32_t arena_shard(uint32_t f) { return (f >> 4) & (uint32_t)(kArenaShards - 1); }
-// The statistics line that this workgroup's allocations and releases are counted
-// in.  It is the same for every lane, so the compiler adds a wave's counts up and
-// issues one atomic per word and wave: additions to one line are performed one
-// after another, some 45 ns each, and with a line chosen by bucket they held up a
-// clear of 65536 LFVectors of four buckets (82 -> 59 us).
-// Only the sums over all lines are ever read.
-__device__ __forceinline__ PoolShard* stat_line(PoolHdr* H) { return &H->shard[blockIdx.x & (uint32_t)(kArenaShards - 1)]; }
+// The statistics lines that blocks are counted in; only the sums over all lines are
+// ever read.  Additions to one line are performed one after another, some 45 ns
+// each.  Allocations count per block, on a line by free list: they do not wait for
+// the addition, and the few instructions keep short a path that every launch
+// fetches anew (counting per wave there cost a multi-element round of 256 LFVectors
+// 4 us of 34).  Releases count per workgroup: the line is the same for every
+// lane, so the compiler adds a wave's counts up and issues one atomic per word and
+// wave (a clear of 65536 LFVectors of four buckets 82 -> 57 us).
+__device__ __forceinline__ PoolStat* alloc_stat(PoolHdr* H, uint32_t fs) {
+  return &H->stat[fs & (uint32_t)(kArenaShards - 1)];
+}
+__device__ __forceinline__ PoolStat* free_stat(PoolHdr* H) {
+  return &H->stat[(blockIdx.x * 0x9E3779B1u) >> 24];  // spreads strided workgroups too
+}
+static_assert(kArenaShards == 256, "eight bits of the product");
 
 __device__ __forceinline__ bool cas_rlx(uint64_t* p, uint64_t& expected, uint64_t desired) {
   return __hip_atomic_compare_exchange_strong(p, &expected, desired, __ATOMIC_RELAXED,
@@ -249,19 +268,39 @@ __device__ __forceinline__ uint8_t* arena_alloc(PoolRef P, uint32_t s, uint64_t 
   const uint64_t units = bytes >> kMinClassLog2;
   const uint64_t cap = 1ull << (clog - kMinClassLog2);
   uint64_t* word = &H->shard[s].arena;
-  const uint64_t old = fetch_add(word, units);
-  const uint64_t cid = old >> 32, used = old & 0xFFFFFFFFull;
-  if (cid && used + units <= cap) return P.base + ((cid - 1) << kMinClassLog2) + (used << kMinClassLog2);
-  const bool installer = cid ? (used <= cap && used + units > cap) : (used == 0);
-  if (!installer) return nullptr;  // the caller takes the global bump pointer
-  uint8_t* c = global_bump(P, 1ull << clog);
-  if (!c) {
-    __hip_atomic_exchange(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return nullptr;
+  uint8_t* got = nullptr;
+  uint32_t open = 1;  // neither served nor refused yet
+  for (uint32_t turn = 0; turn < 4 && open; ++turn) {
+    const uint64_t old = fetch_add(word, units);
+    const uint64_t cid = old >> 32, used = old & 0xFFFFFFFFull;
+    if (cid == kNoChunk) {
+      open = 0;
+    } else if (cid && used + units <= cap) {
+      got = P.base + ((cid - 1) << kMinClassLog2) + (used << kMinClassLog2);
+      open = 0;
+    } else if (cid ? used <= cap : used == 0) {  // this add crossed the end: it installs the next chunk
+      got = global_bump(P, 1ull << clog);
+      // The region can only run out once (the bump pointer never goes back): then
+      // the word says so, past its end for every later add.
+      const uint64_t next = got ? ((((uint64_t)(got - P.base) >> kMinClassLog2) + 1) << 32) | units
+                                : (kNoChunk << 32) | (cap + 1);
+      __hip_atomic_exchange(word, next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      open = 0;
+    }
+    // Every lane passes here before any of them waits (inline assembly is
+    // convergent, so the branches above are not moved behind the loop below): the
+    // lane that installs the chunk may be one of this wave.
+    asm volatile("" : "+v"(open));
+    // The others look at the word now and then, a bounded number of times, and
+    // then take another turn.
+    bool fresh = false;
+    for (uint32_t n = 0; open && !fresh && n < kArenaPolls; ++n) {
+      __builtin_amdgcn_s_sleep(16);
+      fresh = (ld_rlx(word) >> 32) != cid;
+    }
+    if (open && !fresh) open = 0;  // the caller takes the global bump pointer
   }
-  const uint64_t ncid = ((uint64_t)(c - P.base) >> kMinClassLog2) + 1;
-  __hip_atomic_exchange(word, (ncid << 32) | units, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return c;
+  return got;
 }
 
 __device__ __forceinline__ uint8_t* pool_alloc(PoolRef P, uint32_t cls, uint32_t fs) {
@@ -271,7 +310,7 @@ __device__ __forceinline__ uint8_t* pool_alloc(PoolRef P, uint32_t cls, uint32_t
   // loads see them and can issue together with the first atomic.
   const uint64_t fault_at = H->fault_at;
   const uint32_t clog = (uint32_t)H->chunk_log2;
-  if (fault_at) {
+  if (__builtin_expect(fault_at != 0, 0)) {
     const uint64_t n = fetch_add(&H->n_attempt, 1) + 1;
     if (n == fault_at) return nullptr;
   }
@@ -299,8 +338,8 @@ __device__ __forceinline__ uint8_t* pool_alloc(PoolRef P, uint32_t cls, uint32_t
     }
   }
   if (!q) return nullptr;
-  add_nr(&stat_line(H)->in_use, bytes);
-  add_nr(&stat_line(H)->n_alloc, 1ull);
+  add_nr(&alloc_stat(H, fs)->in_use, bytes);
+  add_nr(&alloc_stat(H, fs)->n_alloc, 1ull);
   return q;
 }
 
@@ -326,8 +365,8 @@ __device__ __forceinline__ void pool_free(PoolRef P, uint8_t* ptr, uint32_t cls,
   if ((h & kIdxMask) == 0)
     __hip_atomic_fetch_or(&H->nonempty[cls][s >> 6], 1ull << (s & 63), __ATOMIC_RELAXED,
                           __HIP_MEMORY_SCOPE_AGENT);
-  sub_nr(&stat_line(H)->in_use, 1ull << cls);
-  add_nr(&stat_line(H)->n_free, 1ull);
+  sub_nr(&free_stat(H)->in_use, 1ull << cls);
+  add_nr(&free_stat(H)->n_free, 1ull);
 }
 __device__ __forceinline__ void pool_free(PoolRef P, uint8_t* ptr, uint32_t cls, uint32_t s) {
   pool_free(P, ptr, cls, s, pool_head(P, cls, s));
@@ -344,8 +383,8 @@ __device__ __forceinline__ bool pool_alloc_release(PoolRef P, uint32_t cls, uint
   PoolHdr* H = P.hdr;
   if (cls <= (uint32_t)kMaxClassLog2 && !H->fault_at &&
       (ld_rlx(&H->heads[(uint64_t)cls * kFreeShards + s]) & kIdxMask)) {
-    add_nr(&stat_line(H)->n_alloc, 1ull);
-    add_nr(&stat_line(H)->n_free, 1ull);
+    add_nr(&alloc_stat(H, s)->n_alloc, 1ull);
+    add_nr(&alloc_stat(H, s)->n_free, 1ull);
     return true;
   }
   uint8_t* p = pool_alloc(P, cls, s);
@@ -365,8 +404,8 @@ __device__ __forceinline__ bool pool_reuse(PoolRef P, uint32_t s) {
   PoolHdr* H = P.hdr;
   const uint64_t fault_at = H->fault_at;
   if (fault_at && fetch_add(&H->n_attempt, 1) + 1 == fault_at) return false;
-  add_nr(&stat_line(H)->n_alloc, 1ull);
-  add_nr(&stat_line(H)->n_free, 1ull);
+  add_nr(&alloc_stat(H, s)->n_alloc, 1ull);
+  add_nr(&alloc_stat(H, s)->n_free, 1ull);
   return true;
 }
 

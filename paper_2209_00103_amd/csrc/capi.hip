@@ -166,9 +166,9 @@ int gga_pool_stats(gga_pool* p, uint64_t out[7], gga_stream s) {
   }
   uint64_t in_use = 0, n_alloc = 0, n_free = 0;
   for (int k = 0; k < kArenaShards; ++k) {  // per-shard counters wrap individually; the sums do not
-    in_use += h->shard[k].in_use;
-    n_alloc += h->shard[k].n_alloc;
-    n_free += h->shard[k].n_free;
+    in_use += h->stat[k].in_use;
+    n_alloc += h->stat[k].n_alloc;
+    n_free += h->stat[k].n_free;
   }
   // Failed claims leave the bump pointer past the limit: carved bytes stop there.
   const uint64_t carved = h->bump < h->limit ? h->bump : h->limit;
