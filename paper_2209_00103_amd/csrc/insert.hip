@@ -1731,36 +1731,25 @@ __global__ __launch_bounds__(NT) void packed_grow_copy_kernel(ArrRef A, TileArgs
 }
 
 // ------------------------------------------- flagged rounds in two passes --
-// The mask pass holds nothing but the flags, so all of a lane's flag bytes are
-// loaded before the first is tested (64 loads in flight, against 16 in the
-// one-launch kernel, whose payload registers leave no room for more): the
-// configuration-2 mask pass drops from 71 to 56 us.
-__device__ __forceinline__ SlotMask mask_pass_flags(const uint8_t* flags, uint64_t g0, uint64_t gend) {
-  const uint32_t lane = lane_id();
-  SlotMask m;
-#pragma unroll
-  for (int k = 0; k < kMaskWords; ++k) m.w[k] = 0;
-  if (g0 >= gend) return m;
-  const uint64_t last = gend - 1;
-  uint8_t f[kWaveSlots];
-#pragma unroll
-  for (int j = 0; j < kWaveSlots; ++j) {
-    const uint64_t g = g0 + (uint64_t)j * 64 + lane;
-    f[j] = flags[g < gend ? g : last];  // clamped: slots past the tile read its last flag
-  }
-#pragma unroll
-  for (int j = 0; j < kWaveSlots; ++j)
-    if (f[j] && g0 + (uint64_t)j * 64 + lane < gend) m.w[j >> 6] |= 1ull << (j & 63);
-  return m;
-}
-
-// Lane-blocked masks.  When every tile of a round starts and ends on a whole
-// 16-byte payload vector (the LFVector chunk and the thread count multiples of
-// E = 16 / sizeof(T), the payloads 16-byte aligned, the flags E-byte aligned),
-// lane l of a tile owns threads g0 + 64 E c + E l + i (chunk c < 64 / E, i < E)
-// as bit E c + i of its mask word: the mask pass reads E flag bytes per load and
-// the copy pass one 16-byte payload vector per chunk, where the slot layout
-// reads one byte and one element per lane and load.
+// A round from buffers with flags, whose LFVectors span several 4096-thread
+// tiles, takes its positions from a prefix known before any element moves, instead
+// of one launch with per-LFVector tickets and the decoupled look-back:
+// flag_mask_kernel reads the flags once, one wave per tile, keeps one 64-bit mask
+// word per lane (512 bytes per tile) and the tile's count; flag_grow_kernel turns
+// the counts of an LFVector's tiles into their offsets in its round and grows it;
+// flag_copy_kernel then takes each tile's masks and payloads and stores the kept
+// payloads, with no waits.  Element order, sizes and buckets are those of the
+// one-launch kernel; the flags cost 1/8 byte per thread more (the masks written
+// and read back).
+//
+// Lane l of a tile owns threads g0 + 64 E c + E l + i (chunk c < 64 / E, i < E = 16
+// / sizeof(T)) as bit E c + i of its mask word, so the mask pass reads E flag bytes
+// per load and the copy pass one 16-byte payload vector per chunk.  Both load at
+// whatever alignment the tile starts with, for an LFVector's share of any size;
+// only the vector that would run past the end of the buffers is loaded E threads
+// before it and shifted.  (V = 512, 3.4e7 u32 threads, shares off the vector: one
+// byte and one element per lane and load took 22 and 44 us in the two passes, these
+// loads, with a wave per tile of the first instead of four tiles each, 11 and 40.)
 template <uint32_t E>
 __device__ __forceinline__ uint32_t nonzero_bytes(uint32_t x) {
   uint32_t b = 0;
@@ -1769,154 +1758,136 @@ __device__ __forceinline__ uint32_t nonzero_bytes(uint32_t x) {
   return b;
 }
 
-// One tile in lane-blocked masks, every flag word loaded before the first is
-// tested (batching a wave's four tiles of the mask pass into one set of loads
-// measured slower: 51 against 44 us).
+// Mask word of this lane for the tile [g0, te) of n threads, every flag word loaded
+// before the first is tested.
 template <uint32_t E>
-__device__ __forceinline__ uint64_t mask_pass_blocked(const uint8_t* flags, uint64_t g0, uint64_t gend) {
+__device__ __forceinline__ uint64_t mask_pass(const uint8_t* flags, uint64_t g0, uint64_t te, uint64_t n) {
   static_assert(E == 2 || E == 4, "16-byte vectors of 4- or 8-byte elements");
   typedef typename std::conditional<E == 4, uint32_t, uint16_t>::type W;
+  typedef W W_a1 __attribute__((aligned(1)));
   constexpr uint32_t C = 64 / E;
   const uint32_t lane = lane_id();
-  if (g0 >= gend) return 0;
+  const gptr<const uint8_t> src = gmem(flags);
+  if (g0 >= te) return 0;
   W f[C];
+  uint64_t m = 0;
+  if (te - g0 == (uint64_t)kWaveTile) {
+#pragma unroll
+    for (uint32_t c = 0; c < C; ++c) f[c] = *reinterpret_cast<gptr<const W_a1>>(src + g0 + c * 64 * E + lane * E);
+#pragma unroll
+    for (uint32_t c = 0; c < C; ++c) m |= (uint64_t)nonzero_bytes<E>(f[c]) << (c * E);
+    return m;
+  }
 #pragma unroll
   for (uint32_t c = 0; c < C; ++c) {
-    const uint64_t g = g0 + (uint64_t)c * 64 * E + lane * E;
-    f[c] = *reinterpret_cast<const W*>(flags + (g < gend ? g : gend - E));  // clamped to the tile's last E flags
+    const uint64_t g = g0 + c * 64 * E + lane * E;
+    f[c] = *reinterpret_cast<gptr<const W_a1>>(src + (g + E <= n ? g : n - E));
   }
-  uint64_t m = 0;
 #pragma unroll
-  for (uint32_t c = 0; c < C; ++c)
-    if (g0 + (uint64_t)c * 64 * E + lane * E < gend) m |= (uint64_t)nonzero_bytes<E>(f[c]) << (c * E);
+  for (uint32_t c = 0; c < C; ++c) {
+    const uint64_t g = g0 + c * 64 * E + lane * E;
+    uint32_t b = nonzero_bytes<E>(f[c]);
+    if (g < n && g + E > n) b >>= (uint32_t)(g + E - n);
+    if (g + E > te) b &= g < te ? (1u << (uint32_t)(te - g)) - 1u : 0u;
+    m |= (uint64_t)b << (c * E);
+  }
   return m;
 }
 
-// A round from buffers with flags, whose LFVectors span several 4096-thread
-// tiles, runs in the packed form instead of one launch with per-LFVector tickets
-// and the decoupled look-back: flag_mask_kernel reads the flags once (one wave
-// per tile, as the one-launch kernel does), keeps each lane's slot mask (512
-// bytes per tile) and writes the tile's count in the packed offset layout; the
-// group scan and the grow launch of the packed rounds follow; flag_copy_kernel
-// then takes each tile's masks and payloads and stores the kept payloads at
-// offsets known in advance, with no waits.  Element order, sizes and buckets are
-// those of the one-launch kernel; the flags cost 1/8 byte per thread more (the
-// masks written and read back).  E = 1: the slot layout; E = 2, 4: lane-blocked
-// masks (configuration-2 sparse rounds, 2^27 threads at V = 512: mask pass 56 ->
-// 44 us, copy pass 166 -> 161 us).
-template <uint32_t E>
-__global__ __launch_bounds__(kB) void flag_mask_kernel(TileArgs I, const uint8_t* flags, uint64_t* masks,
-                                                       uint64_t* off, uint64_t ntiles) {
-  __shared__ uint32_t s_sum[kPackGroup];
-  const uint32_t tid = threadIdx.x, lane = tid & 63u, w = tid >> 6;
-  const uint64_t first = (uint64_t)blockIdx.x * kPackGroup;
-  for (uint32_t j = w; j < kPackGroup; j += kW) {
-    const uint64_t tile = first + j;
-    uint32_t c = 0;
-    if (tile < ntiles) {
-      const uint32_t v = (uint32_t)(tile / I.tpv);
-      uint64_t g0, gend;
-      tile_range(I, v, tile - (uint64_t)v * I.tpv, kWaveTile, g0, gend);
-      if constexpr (E == 1) {
-        const SlotMask m = mask_pass_flags(flags, g0, gend);
-#pragma unroll
-        for (int k = 0; k < kMaskWords; ++k) masks[(tile * kMaskWords + k) * 64 + lane] = m.w[k];
-        c = (uint32_t)wave_sum64((uint64_t)m.count());
-      } else {
-        const uint64_t m = mask_pass_blocked<E>(flags, g0, gend);
-        masks[tile * 64 + lane] = m;
-        c = (uint32_t)wave_sum64((uint64_t)__popcll(m));
-      }
-    }
-    if (lane == 0) s_sum[j] = c;
-  }
-  __syncthreads();
-  if (tid < kPackGroup) {
-    uint64_t before = 0, all = 0;
-    for (uint32_t q = 0; q < kPackGroup; ++q) {
-      before += q < tid ? s_sum[q] : 0u;
-      all += s_sum[q];
-    }
-    if (first + tid < ntiles) off[first + tid] = before;
-    if (tid == 0) off[ntiles + blockIdx.x] = all;
-  }
+// End of tile t of LFVector v, whose share ends at gend.
+__device__ __forceinline__ uint64_t tile_end(uint64_t g0, uint64_t gend) {
+  return g0 + kWaveTile < gend ? g0 + kWaveTile : gend;
 }
 
-// One wave per tile: the tile's kept payloads go to the LFVector's elements
-// rbase[v] + (tile offset within the LFVector) on, in slot order (the logical
-// thread order), payloads loaded kValBatch slots ahead of their stores.  The
-// buckets were allocated by the grow launch; lane k holds the pointer of the
-// k-th bucket the tile reaches.
-template <typename T>
-__global__ __launch_bounds__(64) void flag_copy_kernel(ArrRef A, TileArgs I, const T* values,
-                                                       const uint64_t* masks, const uint64_t* off,
-                                                       uint64_t ntiles) {
-  const uint64_t tile = blockIdx.x;
+template <uint32_t E>
+__global__ __launch_bounds__(kB) void flag_mask_kernel(TileArgs I, const uint8_t* flags, uint64_t* masks,
+                                                       uint64_t* tiles, uint64_t ntiles) {
   const uint32_t lane = lane_id();
+  const uint64_t tile = (uint64_t)blockIdx.x * kW + (threadIdx.x >> 6);
+  if (tile >= ntiles) return;
   const uint32_t v = (uint32_t)(tile / I.tpv);
   uint64_t g0, gend;
   tile_range(I, v, tile - (uint64_t)v * I.tpv, kWaveTile, g0, gend);
-  if (g0 >= gend || A.dead[v]) return;
-  const uint64_t o0 = packed_offset(off, ntiles, tile);
-  const uint32_t n_t = (uint32_t)(packed_offset(off, ntiles, tile + 1) - o0);
-  if (n_t == 0) return;
-  const uint64_t base = A.rbase[v] + (o0 - packed_offset(off, ntiles, (uint64_t)v * I.tpv));
-  SlotMask bits;
+  const uint64_t m = mask_pass<E>(flags, g0, tile_end(g0, gend), I.n_threads);
+  masks[tile * 64 + lane] = m;
+  uint32_t c = (uint32_t)__popcll(m);
 #pragma unroll
-  for (int k = 0; k < kMaskWords; ++k) bits.w[k] = masks[(tile * kMaskWords + k) * 64 + lane];
-  const uint32_t log2F = A.log2F;
-  const uint32_t b_lo = bucket_of(log2F, base), b_hi = bucket_of(log2F, base + n_t - 1);
-  const uint64_t bp = b_lo + lane <= b_hi ? A.bptr[(uint64_t)v * kMaxBuckets + b_lo + lane] : 0;
-  const ProdBuffer<T> prod{values, nullptr};
-  uint32_t run = 0;
-  if (b_lo == b_hi) {
-    const gptr<T> dst = gmem(reinterpret_cast<T*>(__shfl(bp, 0, 64)) + offset_in(log2F, base, b_lo));
-    for (int j0 = 0; j0 < kWaveSlots; j0 += kValBatch) {
-      T val[kValBatch];
-      wave_values<T, ProdBuffer<T>>(prod, g0, gend, j0, val);
-#pragma unroll
-      for (int k = 0; k < kValBatch; ++k) {
-        const bool f = bits.get(j0 + k);
-        const uint64_t m = __ballot(f);
-        if (f) dst[run + mbcnt(m)] = val[k];
-        run += (uint32_t)__popcll(m);
-      }
-    }
-    return;
-  }
-  for (int j0 = 0; j0 < kWaveSlots; j0 += kValBatch) {
-    T val[kValBatch];
-    wave_values<T, ProdBuffer<T>>(prod, g0, gend, j0, val);
-#pragma unroll
-    for (int k = 0; k < kValBatch; ++k) {
-      const bool f = bits.get(j0 + k);
-      const uint64_t m = __ballot(f);
-      const uint64_t idx = base + run + mbcnt(m);
-      const uint32_t b = f ? bucket_of(log2F, idx) : b_lo;
-      const uint64_t p = __shfl(bp, (int)(b - b_lo), 64);
-      if (f) gmem(reinterpret_cast<T*>(p))[offset_in(log2F, idx, b)] = val[k];
-      run += (uint32_t)__popcll(m);
-    }
-  }
+  for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);
+  if (lane == 0) tiles[tile] = c;
 }
 
-// The copy pass over lane-blocked masks: chunk c of the tile is one 16-byte
-// payload vector per lane (kChunkBatch chunks loaded ahead of their stores); the
-// kept elements of a chunk take their places in thread order from E ballots
-// (bit i of every lane's E bits) and the lane's own rank, are gathered in LDS,
-// and leave it as contiguous runs (64 consecutive elements per store, as the
-// slot layout's ballots give: stores scattered over a lane-blocked chunk
-// measured 181 against 166 us).  kOne: the tile's elements all land in one
-// bucket, at dst1 on.
+// The tiles' words become offset in the LFVector's round << 16 | count, and the
+// LFVector grows by their sum.  Up to 256 tiles: one wave per LFVector, four tiles
+// per lane; more: one workgroup, in passes of 4096 tiles.
+constexpr uint32_t kGrowWaveTiles = 256;
+__global__ __launch_bounds__(256) void flag_grow_kernel(ArrRef A, TileArgs I, uint64_t* tiles) {
+  const uint32_t v = blockIdx.x * 4u + (threadIdx.x >> 6), lane = lane_id();
+  if (v >= A.V) return;
+  uint64_t* w = tiles + (uint64_t)v * I.tpv;
+  uint32_t c[4], sum = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < 4; ++k) {
+    c[k] = lane * 4 + k < I.tpv ? (uint32_t)w[lane * 4 + k] : 0u;
+    sum += c[k];
+  }
+  const uint32_t incl = wave_incl_scan(sum);
+  uint64_t at = incl - sum;
+#pragma unroll
+  for (uint32_t k = 0; k < 4; ++k) {
+    if (lane * 4 + k < I.tpv) w[lane * 4 + k] = at << 16 | c[k];
+    at += c[k];
+  }
+  grow_vector_by(A, I.elem_log2, v, __shfl(incl, 63, 64));
+}
+
+__global__ __launch_bounds__(1024) void flag_grow_long_kernel(ArrRef A, TileArgs I, uint64_t* tiles) {
+  __shared__ uint32_t s_sum[16];
+  const uint32_t v = blockIdx.x, tid = threadIdx.x, lane = tid & 63u, wv = tid >> 6;
+  uint64_t* w = tiles + (uint64_t)v * I.tpv;
+  uint64_t carry = 0;
+  for (uint64_t t0 = 0; t0 < I.tpv; t0 += 4096) {
+    uint32_t c[4], sum = 0;
+    const uint64_t t = t0 + tid * 4;
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+      c[k] = t + k < I.tpv ? (uint32_t)w[t + k] : 0u;
+      sum += c[k];
+    }
+    const uint32_t incl = wave_incl_scan(sum);
+    if (lane == 63) s_sum[wv] = incl;
+    __syncthreads();
+    uint64_t at = carry + incl - sum;
+    for (uint32_t q = 0; q < 16; ++q) {
+      at += q < wv ? s_sum[q] : 0u;
+      carry += s_sum[q];
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+      if (t + k < I.tpv) w[t + k] = at << 16 | c[k];
+      at += c[k];
+    }
+    __syncthreads();  // s_sum is rewritten by the next pass
+  }
+  if (tid < 64) grow_vector_by(A, I.elem_log2, v, carry);
+}
+
+// The copy pass: chunk c of the tile is one 16-byte payload vector per lane
+// (kChunkBatch chunks loaded ahead of their stores); the kept elements of a chunk
+// take their places in thread order from E ballots (bit i of every lane's E bits)
+// and the lane's own rank, are gathered in LDS, and leave it as contiguous runs of
+// 64 consecutive elements per store (stores scattered over a lane-blocked chunk
+// measured 181 against 166 us on 2^27 threads at V = 512).  kOne: the tile's
+// elements all land in one bucket, at dst1 on.
 constexpr uint32_t kChunkBatch = 8;
 template <typename T, bool kOne>
-__device__ __forceinline__ void copy_blocked(const T* values, uint64_t g0, uint64_t gend, uint64_t word,
-                                             gptr<T> dst1, uint64_t base, uint32_t log2F, uint32_t b_lo,
-                                             uint64_t bp, T* s_keep) {
+__device__ __forceinline__ void copy_blocked(const T* values, uint64_t g0, uint64_t n, uint64_t word, gptr<T> dst1,
+                                             uint64_t base, uint32_t log2F, uint32_t b_lo, uint64_t bp, T* s_keep) {
+  typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
   constexpr uint32_t E = 16 / sizeof(T), C = 64 / E;
   static_assert(kMaskWords == 1 && C % kChunkBatch == 0, "one 64-bit mask word per lane");
   const uint32_t lane = lane_id();
   const gptr<const T> src = gmem(values);
+  const bool at_end = g0 + kWaveTile > n;  // some vector would run past the buffer
   uint32_t run = 0;
 #pragma unroll 1
   for (uint32_t c0 = 0; c0 < C; c0 += kChunkBatch) {
@@ -1924,7 +1895,7 @@ __device__ __forceinline__ void copy_blocked(const T* values, uint64_t g0, uint6
 #pragma unroll
     for (uint32_t u = 0; u < kChunkBatch; ++u) {
       const uint64_t g = g0 + (uint64_t)(c0 + u) * 64 * E + lane * E;
-      x[u] = *reinterpret_cast<gptr<const u32x4>>(src + (g < gend ? g : gend - E));  // clamped to the tile's last vector
+      x[u] = *reinterpret_cast<gptr<const u32x4_a4>>(src + (g + E <= n ? g : n - E));
     }
     const uint32_t first = run;  // the batch's first position in the tile
 #pragma unroll
@@ -1939,6 +1910,15 @@ __device__ __forceinline__ void copy_blocked(const T* values, uint64_t g0, uint6
       }
       T el[E];
       __builtin_memcpy(el, &x[u], 16);
+      if (at_end) {  // wave-uniform: undo the shift of the buffer's last vector
+        const uint64_t g = g0 + (uint64_t)(c0 + u) * 64 * E + lane * E;
+        const uint32_t d = g < n && g + E > n ? (uint32_t)(g + E - n) : 0u;
+#pragma unroll
+        for (uint32_t i = 0; i < E; ++i)
+#pragma unroll
+          for (uint32_t k = i + 1; k < E; ++k)
+            if (d == k - i) el[i] = el[k];
+      }
 #pragma unroll
       for (uint32_t i = 0; i < E; ++i) {
         if ((bits >> i) & 1u) s_keep[pos++] = el[i];
@@ -1963,30 +1943,29 @@ __device__ __forceinline__ void copy_blocked(const T* values, uint64_t g0, uint6
   }
 }
 
+// One wave per tile.  The buckets were allocated by the grow launch; lane k holds
+// the pointer of the k-th bucket the tile reaches.
 template <typename T>
-__global__ __launch_bounds__(64) void flag_copy_blocked_kernel(ArrRef A, TileArgs I, const T* values,
-                                                               const uint64_t* masks, const uint64_t* off,
-                                                               uint64_t ntiles) {
+__global__ __launch_bounds__(64) void flag_copy_kernel(ArrRef A, TileArgs I, const T* values, const uint64_t* masks,
+                                                       const uint64_t* tiles) {
   __shared__ T s_keep[kChunkBatch * 64 * (16 / sizeof(T))];
   const uint64_t tile = blockIdx.x;
   const uint32_t lane = lane_id();
   const uint32_t v = (uint32_t)(tile / I.tpv);
   uint64_t g0, gend;
   tile_range(I, v, tile - (uint64_t)v * I.tpv, kWaveTile, g0, gend);
-  if (g0 >= gend || A.dead[v]) return;
-  const uint64_t o0 = packed_offset(off, ntiles, tile);
-  const uint32_t n_t = (uint32_t)(packed_offset(off, ntiles, tile + 1) - o0);
-  if (n_t == 0) return;
-  const uint64_t base = A.rbase[v] + (o0 - packed_offset(off, ntiles, (uint64_t)v * I.tpv));
-  const uint64_t word = masks[tile * 64 + lane];
+  const uint64_t at = tiles[tile], word = masks[tile * 64 + lane];
+  const uint32_t n_t = (uint32_t)at & 0xFFFFu;
+  if (n_t == 0 || A.dead[v]) return;
+  const uint64_t base = A.rbase[v] + (at >> 16);
   const uint32_t log2F = A.log2F;
   const uint32_t b_lo = bucket_of(log2F, base), b_hi = bucket_of(log2F, base + n_t - 1);
   const uint64_t bp = b_lo + lane <= b_hi ? A.bptr[(uint64_t)v * kMaxBuckets + b_lo + lane] : 0;
   if (b_lo == b_hi) {
     const gptr<T> dst1 = gmem(reinterpret_cast<T*>(__shfl(bp, 0, 64)) + offset_in(log2F, base, b_lo));
-    copy_blocked<T, true>(values, g0, gend, word, dst1, base, log2F, b_lo, bp, s_keep);
+    copy_blocked<T, true>(values, g0, I.n_threads, word, dst1, base, log2F, b_lo, bp, s_keep);
   } else {
-    copy_blocked<T, false>(values, g0, gend, word, gptr<T>{}, base, log2F, b_lo, bp, s_keep);
+    copy_blocked<T, false>(values, g0, I.n_threads, word, gptr<T>{}, base, log2F, b_lo, bp, s_keep);
   }
 }
 
@@ -2348,10 +2327,8 @@ static int queue_packed(ggarray* a, uint64_t* off, const void* values, const uin
   return hip_status(e);
 }
 
-// Words of a flagged round in two passes: the slot masks, then the packed offsets.
-static uint64_t flag_round_words(uint64_t ntiles) {
-  return ntiles * kMaskWords * 64 + ntiles + packed_groups(ntiles) + 1;
-}
+// Words of a flagged round in two passes: the masks, then a word per tile.
+static uint64_t flag_round_words(uint64_t ntiles) { return ntiles * 64 + ntiles; }
 
 // Whether the two-pass form can run: its buffer is large enough or can be grown
 // (not while the stream is capturing; a captured round then takes the one-launch
@@ -2361,41 +2338,28 @@ static bool flag_rounds_fit(const ggarray* a, uint64_t ntiles, hipStream_t s) {
 }
 
 // A buffer round with flags over LFVectors of several tiles: masks and tile
-// counts, their prefix, the growth of every LFVector, then the copy.
-static int queue_flag_rounds(ggarray* a, const InsertDesc& d, const TileArgs& I, uint64_t ntiles, hipStream_t s) {
-  int rc = ensure_packed_offsets(a, flag_round_words(ntiles), s);
-  if (rc) return rc;
-  uint64_t* masks = a->pk_off;
-  uint64_t* off = masks + ntiles * kMaskWords * 64;
-  const uint64_t ngroups = packed_groups(ntiles);
-  // Lane-blocked masks when every tile starts and ends on a whole 16-byte payload
-  // vector and the buffers are aligned for the vector loads; else the slot layout.
-  const uint32_t E = 16u / a->elem_bytes;
-  const bool blocked = I.chunk % E == 0 && I.n_threads % E == 0 &&
-                       (reinterpret_cast<uintptr_t>(d.values) & 15u) == 0 &&
-                       (reinterpret_cast<uintptr_t>(d.flags) & (E - 1)) == 0;
-  const dim3 mgrid((uint32_t)ngroups), mblock(kB), cgrid((uint32_t)ntiles), cblock(64);
-  if (!blocked)
-    hipLaunchKernelGGL(flag_mask_kernel<1>, mgrid, mblock, 0, s, I, d.flags, masks, off, ntiles);
-  else if (E == 4)
-    hipLaunchKernelGGL(flag_mask_kernel<4>, mgrid, mblock, 0, s, I, d.flags, masks, off, ntiles);
+// counts, offsets and growth of every LFVector, then the copy.
+template <typename T>
+static void queue_flag_kernels(const ArrRef& A, const InsertDesc& d, const TileArgs& I, uint64_t* masks,
+                               uint64_t ntiles, hipStream_t s) {
+  uint64_t* tiles = masks + ntiles * 64;
+  hipLaunchKernelGGL(flag_mask_kernel<16 / sizeof(T)>, dim3((uint32_t)((ntiles + kW - 1) / kW)), dim3(kB), 0, s, I,
+                     d.flags, masks, tiles, ntiles);
+  if (I.tpv <= kGrowWaveTiles)
+    hipLaunchKernelGGL(flag_grow_kernel, dim3((A.V + 3) / 4), dim3(256), 0, s, A, I, tiles);
   else
-    hipLaunchKernelGGL(flag_mask_kernel<2>, mgrid, mblock, 0, s, I, d.flags, masks, off, ntiles);
-  hipLaunchKernelGGL(packed_tile_scan_kernel, dim3(1), dim3(1024), 0, s, off + ntiles, ngroups);
-  hipLaunchKernelGGL(packed_grow_kernel, dim3((a->V + 3) / 4), dim3(256), 0, s, a->ref, I, off, ntiles, ~0ull);
-  if (a->elem_bytes == 4) {
-    const uint32_t* vals = static_cast<const uint32_t*>(d.values);
-    if (blocked)
-      hipLaunchKernelGGL(flag_copy_blocked_kernel<uint32_t>, cgrid, cblock, 0, s, a->ref, I, vals, masks, off, ntiles);
-    else
-      hipLaunchKernelGGL(flag_copy_kernel<uint32_t>, cgrid, cblock, 0, s, a->ref, I, vals, masks, off, ntiles);
-  } else {
-    const uint64_t* vals = static_cast<const uint64_t*>(d.values);
-    if (blocked)
-      hipLaunchKernelGGL(flag_copy_blocked_kernel<uint64_t>, cgrid, cblock, 0, s, a->ref, I, vals, masks, off, ntiles);
-    else
-      hipLaunchKernelGGL(flag_copy_kernel<uint64_t>, cgrid, cblock, 0, s, a->ref, I, vals, masks, off, ntiles);
-  }
+    hipLaunchKernelGGL(flag_grow_long_kernel, dim3(A.V), dim3(1024), 0, s, A, I, tiles);
+  hipLaunchKernelGGL(flag_copy_kernel<T>, dim3((uint32_t)ntiles), dim3(64), 0, s, A, I,
+                     static_cast<const T*>(d.values), masks, tiles);
+}
+
+static int queue_flag_rounds(ggarray* a, const InsertDesc& d, const TileArgs& I, uint64_t ntiles, hipStream_t s) {
+  const int rc = ensure_packed_offsets(a, flag_round_words(ntiles), s);
+  if (rc) return rc;
+  if (a->elem_bytes == 4)
+    queue_flag_kernels<uint32_t>(a->ref, d, I, a->pk_off, ntiles, s);
+  else
+    queue_flag_kernels<uint64_t>(a->ref, d, I, a->pk_off, ntiles, s);
   const hipError_t e = hipGetLastError();
   if (e == hipSuccess) sizes_changed(a, s);
   return hip_status(e);
