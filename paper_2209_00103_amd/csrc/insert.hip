@@ -639,6 +639,120 @@ __global__ __launch_bounds__(64) void insert_wave_kernel(ArrRef A, StaticRef S, 
   wave_tile<T, Prod, kStatic>(A, S, I, prod, blockIdx.x);
 }
 
+// One tile per LFVector: a workgroup of W waves per LFVector, S logical threads per
+// lane (slot j of thread t is logical thread 64 W j + t, so the order (slot, wave,
+// lane) is the logical order), every flag and payload loaded or computed at once
+// and kept in registers.  Wave 0 turns the slots' counts into offsets and
+// allocates; nothing waits outside the workgroup.  insert_wave_kernel's single
+// wave goes through 64 slots in order, past the end of a short share too (us a
+// round, wave against this form: 256 LFVectors of 1024 Bernoulli threads 14 and
+// 5.7, 512 of 3906 flagged u32 threads 18 and 7, 65536 of 64 flagged ones 170 and
+// 33, 4096 of 3906 34 and 28.5).
+template <typename T, class Prod, uint32_t W, uint32_t S>
+__global__ __launch_bounds__(64 * W) void insert_block_kernel(ArrRef A, TileArgs I, Prod prod) {
+  static_assert(W * S <= 64, "one count per lane of wave 0");
+  __shared__ uint64_t s_bp[kMaxBuckets];
+  __shared__ uint32_t s_cnt[64];
+  __shared__ uint32_t s_fail;
+  const uint32_t v = blockIdx.x, tid = threadIdx.x, lane = tid & 63u, w = tid >> 6;
+  uint64_t g0, gend;
+  tile_range(I, v, 0, 64 * W * S, g0, gend);
+  if (g0 >= gend || A.dead[v]) return;
+  const uint64_t s0 = A.size[v];
+  const uint32_t log2F = A.log2F;
+  T val[S];
+  uint32_t keep = 0;
+  if constexpr (Prod::kLoads) {
+    bool f[S];
+#pragma unroll
+    for (uint32_t j = 0; j < S; ++j) {  // clamped: slots past the share read its last thread
+      const uint64_t g = g0 + j * (64 * W) + tid, c = g < gend ? g : gend - 1;
+      f[j] = prod.flag(c);
+      val[j] = prod.value(c);
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < S; ++j) keep |= (uint32_t)(f[j] && g0 + j * (64 * W) + tid < gend) << j;
+  } else {
+#pragma unroll
+    for (uint32_t j = 0; j < S; ++j) {
+      const uint64_t g = g0 + j * (64 * W) + tid;
+      val[j] = 0;
+      keep |= (uint32_t)(g < gend && prod.take(g, val[j])) << j;
+    }
+  }
+  uint32_t rank[S];
+#pragma unroll
+  for (uint32_t j = 0; j < S; ++j) {
+    const uint64_t m = __ballot((keep >> j) & 1u);
+    rank[j] = mbcnt(m);
+    if (lane == 0) s_cnt[j * W + w] = (uint32_t)__popcll(m);
+  }
+  __syncthreads();
+  uint64_t s1 = s0;
+  if (tid < 64) {
+    const uint32_t c = lane < W * S ? s_cnt[lane] : 0u, incl = wave_incl_scan(c);
+    s1 = s0 + __shfl(incl, 63, 64);
+    if (lane < W * S) s_cnt[lane] = incl - c;
+    uint64_t* row = A.bptr + (uint64_t)v * kMaxBuckets;
+    const uint32_t lo = nbuckets_for(log2F, s0), hi = nbuckets_for(log2F, s1), b = lo + lane;
+    bool failed = false;
+    if (b < hi) {
+      if (b >= (uint32_t)kMaxBuckets) {
+        failed = true;
+      } else {
+        uint8_t* q = pool_alloc(A.pool, bucket_class(log2F, I.elem_log2, b), pool_shard(v, b, A.salt));
+        s_bp[b] = row[b] = q ? (uint64_t)q : kFailedPtr;
+        failed = !q;
+      }
+    }
+    if (lane == 63 && lo) s_bp[lo - 1] = row[lo - 1];  // the bucket that earlier rounds left part full
+    const bool any = __ballot(failed) != 0;
+    if (lane == 0) {
+      s_fail = any ? 1u : 0u;
+      if (any) {
+        set_error(A.err, kErrNoMem);
+        A.dead[v] = 1u;
+      } else {
+        A.size[v] = s1;  // every wave has read the old one: the barrier above
+      }
+    }
+  }
+  __syncthreads();
+  if (s_fail) return;
+#pragma unroll
+  for (uint32_t j = 0; j < S; ++j) {
+    if (!((keep >> j) & 1u)) continue;
+    const uint64_t idx = s0 + s_cnt[j * W + w] + rank[j];
+    const uint32_t b = bucket_of(log2F, idx);
+    gmem(reinterpret_cast<T*>(s_bp[b]))[offset_in(log2F, idx, b)] = val[j];
+  }
+}
+
+// A 0/1 round of the single-launch kernels.  Few LFVectors take the widest
+// workgroup their share fills.  From 2048 on the CUs are full of workgroups, and
+// what counts is how many fit: one wave for shares of up to 256 threads (16384
+// LFVectors of 256: 35 us with four waves, 18 with one), four for the longest (4096
+// of 3906: 40 us with sixteen, 28.5 with four).
+template <typename T, class Prod, bool kStatic>
+void launch_flags(const ArrRef& A, const StaticRef& S, const TileArgs& I, const Prod& p, uint64_t ntiles,
+                  hipStream_t s) {
+  if constexpr (!kStatic) {
+    if (I.tpv == 1) {
+      const bool many = A.V >= 2048;
+      if (I.chunk <= 256 && many)
+        hipLaunchKernelGGL((insert_block_kernel<T, Prod, 1, 4>), dim3(A.V), dim3(64), 0, s, A, I, p);
+      else if (I.chunk <= 1024)
+        hipLaunchKernelGGL((insert_block_kernel<T, Prod, 4, 4>), dim3(A.V), dim3(256), 0, s, A, I, p);
+      else if (many)
+        hipLaunchKernelGGL((insert_block_kernel<T, Prod, 4, 16>), dim3(A.V), dim3(256), 0, s, A, I, p);
+      else
+        hipLaunchKernelGGL((insert_block_kernel<T, Prod, 16, 4>), dim3(A.V), dim3(1024), 0, s, A, I, p);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((insert_wave_kernel<T, Prod, kStatic>), dim3((uint32_t)ntiles), dim3(64), 0, s, A, S, I, p);
+}
+
 // Batch launch: one insertion round of many arrays.  The waves of array i are
 // the blocks [begins[i], begins[i+1]); each wave finds its array with a 64-way
 // search and then runs exactly as in a single-array launch.
@@ -1977,12 +2091,12 @@ int dispatch(const ArrRef& A, const StaticRef& S, const TileArgs& I, const Inser
   switch (d.mode) {
     case kModeBuffer: {
       ProdBuffer<T> p{static_cast<const T*>(d.values), d.flags};
-      hipLaunchKernelGGL((insert_wave_kernel<T, ProdBuffer<T>, kStatic>), grid, dim3(64), 0, s, A, S, I, p);
+      launch_flags<T, ProdBuffer<T>, kStatic>(A, S, I, p, ntiles, s);
       break;
     }
     case kModeBernoulli: {
       ProdBernoulli<T> p{d.seed, d.round};
-      hipLaunchKernelGGL((insert_wave_kernel<T, ProdBernoulli<T>, kStatic>), grid, dim3(64), 0, s, A, S, I, p);
+      launch_flags<T, ProdBernoulli<T>, kStatic>(A, S, I, p, ntiles, s);
       break;
     }
     case kModeRoundTag: {

@@ -30,7 +30,7 @@ def test_flag_rounds_any_share(elem, V, F, n):
     for r, (p, so, fo) in enumerate([(0.5, 0, 0), (1.0, 1, 3), (0.03, 0, 1), (0.9, 1, 2)]):
         vals, flags = wl.random_round(rng, n, p, elem)
         dv = dev(np.concatenate([vals[:1], vals]))[1:] if so else dev(vals)  # element-aligned only
-        df = dev(np.concatenate([flags[:fo], flags * np.uint8(r + 1)]))[fo:]  # any byte, any value but 0
+        df = dev(np.concatenate([np.ones(fo, np.uint8), flags * np.uint8(r + 1)]))[fo:]  # any byte, any value but 0
         a.insert(dv, df)
         o.insert(vals, flags)
         assert_same(a, o, f"round {r}")
