@@ -4,13 +4,15 @@
 // LFVector shares its offset with the next one, so this choice skips it.  Inside
 // the LFVector the closed form gives bucket and offset.
 //
-// A search of P for every element is a chain of dependent loads, and that chain,
-// not the elements' traffic, bounded both kernels here (V = 512, 2^24 u32
-// elements: an update of all 161 us, 0.83 TB/s; 2^22 random reads 99 us).  The
-// update therefore searches once per wave and span of consecutive indices and
-// streams the span's bucket runs (27 us, 5.0 TB/s); the gather keeps P (or a
-// sample of it) in LDS and runs several searches per thread side by side (84 us,
-// bound by the 128-byte line that each random read fetches: 541 MB, 6.4 TB/s).
+// One thread per element, each with a search of P of its own, is the shortest path
+// while every element can be in flight at once.  With more of them the searches'
+// chains of dependent loads, not the elements' traffic, bound it (V = 512, 2^24
+// u32 elements: an update of all 161 us, 0.83 TB/s; 2^22 random reads 99 us), so the
+// update of a larger array searches once per wave and span of consecutive indices
+// and streams the span's bucket runs (24-27 us, 5.0-5.6 TB/s), and a larger gather
+// keeps P (or a sample of it) in LDS and runs several searches per thread side by
+// side (84 us, bound by the 128-byte line that each random read fetches: 541 MB,
+// 6.4 TB/s).
 #include "gga_internal.h"
 
 namespace gga {
@@ -19,11 +21,39 @@ namespace {
 constexpr uint32_t kGlobalThreads = 256;
 constexpr uint32_t kGlobalBlocks = 8192;  // 32 workgroups per CU, grid-stride
 
-// Address of element j of LFVector v.
+// Address of global element i < P[V], by a binary search of P.
 template <typename T>
-__device__ __forceinline__ gptr<T> element_of(const ArrRef& A, uint32_t v, uint64_t j) {
+__device__ __forceinline__ gptr<T> element_at(const ArrRef& A, uint64_t i) {
+  uint32_t lo = 0, hi = A.V;  // P[lo] <= i < P[hi]
+  while (hi - lo > 1) {
+    const uint32_t mid = (lo + hi) >> 1;
+    if (A.prefix[mid] <= i) lo = mid;
+    else hi = mid;
+  }
+  const uint64_t j = i - A.prefix[lo];
   const uint32_t b = bucket_of(A.log2F, j);
-  return gmem(reinterpret_cast<T*>(A.bptr[(uint64_t)v * kMaxBuckets + b])) + offset_in(A.log2F, j, b);
+  return gmem(reinterpret_cast<T*>(A.bptr[(uint64_t)lo * kMaxBuckets + b])) + offset_in(A.log2F, j, b);
+}
+
+// One thread per element (small arrays, few reads).
+template <typename T>
+__global__ __launch_bounds__(kGlobalThreads) void rw_element_kernel(ArrRef A, uint32_t op) {
+  const uint64_t n = A.prefix[A.V];
+  const uint64_t stride = (uint64_t)gridDim.x * kGlobalThreads;
+  for (uint64_t i = (uint64_t)blockIdx.x * kGlobalThreads + threadIdx.x; i < n; i += stride) {
+    const gptr<T> p = element_at<T>(A, i);
+    *p = apply_op<T>(op, *p);
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kGlobalThreads) void gather_element_kernel(ArrRef A, const uint64_t* idx, uint64_t n,
+                                                                       T* out) {
+  const uint64_t k = (uint64_t)blockIdx.x * kGlobalThreads + threadIdx.x;
+  if (k >= n) return;
+  const uint64_t i = idx[k];
+  if (i < A.prefix[A.V]) out[k] = *element_at<T>(A, i);
+  else set_error(A.err, kErrRange);
 }
 
 // x = op(x) over n elements from p on, by one wave, kU vectors per lane in flight
@@ -54,15 +84,15 @@ __device__ __forceinline__ void wave_rw_run(gptr<T> p, uint32_t n, uint32_t op) 
   if (tail + lane < n) p[tail + lane] = apply_op<T>(op, p[tail + lane]);
 }
 
-// One wave per span of 8 KiB of consecutive global indices.  The span's first
+// One wave per span of kU KiB of consecutive global indices.  The span's first
 // LFVector comes from one 64-way search of P; then, while the span reaches at
 // most kRunVectors LFVectors, its bucket runs are streamed in order.  A span over
-// more of them (short LFVectors) takes its elements one by one, each search
-// limited to the LFVectors that the span reaches.
-constexpr uint32_t kRunVectors = 8;
-template <typename T>
+// more of them (short LFVectors) takes its elements one by one, kE per lane side by
+// side, each search limited to the LFVectors that the span reaches.
+constexpr uint32_t kRunVectors = 4;
+template <typename T, uint32_t kU>
 __global__ __launch_bounds__(kGlobalThreads) void rw_global_kernel(ArrRef A, uint32_t op) {
-  constexpr uint32_t kU = 8, kSpan = 64 * kU * (16 / sizeof(T));
+  constexpr uint32_t kPer = kU * (16 / sizeof(T)), kSpan = 64 * kPer, kE = kPer < 8 ? kPer : 8;
   const uint64_t n = A.prefix[A.V];
   const uint64_t waves = (uint64_t)gridDim.x * (kGlobalThreads / 64);
   const uint32_t lane = threadIdx.x & 63u;
@@ -91,15 +121,34 @@ __global__ __launch_bounds__(kGlobalThreads) void rw_global_kernel(ArrRef A, uin
       continue;
     }
     const uint64_t* P = A.prefix + v;
-    for (uint64_t i = i0 + lane; i < i1; i += 64) {
-      uint32_t lo = 0, hi = reach;  // P[lo] <= i, and i < P[hi] or hi == reach
-      while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (P[mid] <= i) lo = mid;
-        else hi = mid;
+    uint32_t top = 1;
+    while (2 * top < reach) top *= 2;
+    for (uint64_t i = i0 + lane; i < i1; i += 64 * kE) {  // lanes past the end redo the span's last element, unstored
+      uint32_t at[kE];
+#pragma unroll
+      for (uint32_t u = 0; u < kE; ++u) at[u] = 0;
+      for (uint32_t step = top; step; step >>= 1) {  // the last P at or below the index
+#pragma unroll
+        for (uint32_t u = 0; u < kE; ++u) {
+          const uint32_t m = at[u] + step;
+          const uint64_t iu = i + 64 * u < i1 ? i + 64 * u : i1 - 1;
+          if (m < reach && P[m] <= iu) at[u] = m;
+        }
       }
-      const gptr<T> p = element_of<T>(A, v + lo, i - P[lo]);
-      *p = apply_op<T>(op, *p);
+      uint64_t row[kE], off[kE];
+#pragma unroll
+      for (uint32_t u = 0; u < kE; ++u) {
+        const uint64_t j = (i + 64 * u < i1 ? i + 64 * u : i1 - 1) - P[at[u]];
+        const uint32_t b = bucket_of(A.log2F, j);
+        row[u] = A.bptr[(uint64_t)(v + at[u]) * kMaxBuckets + b];
+        off[u] = offset_in(A.log2F, j, b);
+      }
+      T x[kE];
+#pragma unroll
+      for (uint32_t u = 0; u < kE; ++u) x[u] = gmem(reinterpret_cast<T*>(row[u]))[off[u]];
+#pragma unroll
+      for (uint32_t u = 0; u < kE; ++u)
+        if (i + 64 * u < i1) gmem(reinterpret_cast<T*>(row[u]))[off[u]] = apply_op<T>(op, x[u]);
     }
   }
 }
@@ -168,31 +217,59 @@ __global__ __launch_bounds__(kGlobalThreads) void gather_kernel(ArrRef A, const 
 
 }  // namespace
 
-int launch_rw_global(ggarray* a, uint32_t op, hipStream_t s) {
-  // A wave per span of the host's bound of the size, looping beyond.
-  const uint64_t spans = (a->size_ub >> (13u - a->elem_log2)) + 1, per = kGlobalThreads / 64;
+// Where one thread per element gives way to the kernels above (us, element against
+// span or LDS form): updates at V = 512 of 1.0e5 elements 4.3 against 6.7, at V =
+// 4096 of 5.0e5 9.3 against 9.4, at V = 512 of 3.0e6 26 against 12; reads at V = 4096,
+// 1.6e5 7.8 against 10.7, 2.0e6 60 against 44, at V = 32, 2.0e6 40 against 36.
+constexpr uint64_t kSpanMinElems = 1ull << 19;
+constexpr uint64_t kGatherMinReads = 1ull << 20;
+
+template <typename T>
+static void queue_rw_global(const ggarray* a, uint32_t op, hipStream_t s) {
+  const dim3 block(kGlobalThreads);
+  if (a->size_ub < kSpanMinElems) {
+    const uint64_t blocks = a->size_ub / kGlobalThreads + 1;
+    hipLaunchKernelGGL(rw_element_kernel<T>, dim3((uint32_t)blocks), block, 0, s, a->ref, op);
+    return;
+  }
+  // A wave per span of the host's bound of the size, looping beyond.  Spans of 8
+  // KiB once they fill the chip's 8192 wave slots (64 MiB of elements), 2 KiB below.
+  const bool wide = a->size_ub >> (26u - a->elem_log2) != 0;
+  const uint64_t spans = (a->size_ub >> ((wide ? 13u : 11u) - a->elem_log2)) + 1, per = kGlobalThreads / 64;
   const dim3 grid((uint32_t)(spans < kGlobalBlocks * per ? (spans + per - 1) / per : kGlobalBlocks));
-  if (a->elem_bytes == 4)
-    hipLaunchKernelGGL(rw_global_kernel<uint32_t>, grid, dim3(kGlobalThreads), 0, s, a->ref, op);
+  if (wide)
+    hipLaunchKernelGGL((rw_global_kernel<T, 8>), grid, block, 0, s, a->ref, op);
   else
-    hipLaunchKernelGGL(rw_global_kernel<uint64_t>, grid, dim3(kGlobalThreads), 0, s, a->ref, op);
+    hipLaunchKernelGGL((rw_global_kernel<T, 2>), grid, block, 0, s, a->ref, op);
+}
+
+int launch_rw_global(ggarray* a, uint32_t op, hipStream_t s) {
+  if (a->elem_bytes == 4) queue_rw_global<uint32_t>(a, op, s);
+  else queue_rw_global<uint64_t>(a, op, s);
   return hip_status(hipGetLastError());
 }
 
-int launch_gather(ggarray* a, const uint64_t* idx, uint64_t n, void* out, hipStream_t s) {
-  if (n == 0) return GGA_OK;
+template <typename T>
+static void queue_gather(const ggarray* a, const uint64_t* idx, uint64_t n, T* out, hipStream_t s) {
+  const dim3 block(kGlobalThreads);
+  if (n < kGatherMinReads) {
+    hipLaunchKernelGGL(gather_element_kernel<T>, dim3((uint32_t)((n + kGlobalThreads - 1) / kGlobalThreads)), block,
+                       0, s, a->ref, idx, n, out);
+    return;
+  }
   constexpr uint64_t kPer = kGlobalThreads * kReads;
   uint64_t blocks = (n + kPer - 1) / kPer;
   if (blocks > kGlobalBlocks) blocks = kGlobalBlocks;
   uint32_t k = 0, top = 1;
   while (((a->V + (1u << k) - 1) >> k) > kSample) ++k;
   while (2 * top < ((a->V + (1u << k) - 1) >> k)) top *= 2;
-  if (a->elem_bytes == 4)
-    hipLaunchKernelGGL(gather_kernel<uint32_t>, dim3((uint32_t)blocks), dim3(kGlobalThreads), 0, s, a->ref, idx, n,
-                       static_cast<uint32_t*>(out), k, top);
-  else
-    hipLaunchKernelGGL(gather_kernel<uint64_t>, dim3((uint32_t)blocks), dim3(kGlobalThreads), 0, s, a->ref, idx, n,
-                       static_cast<uint64_t*>(out), k, top);
+  hipLaunchKernelGGL(gather_kernel<T>, dim3((uint32_t)blocks), block, 0, s, a->ref, idx, n, out, k, top);
+}
+
+int launch_gather(ggarray* a, const uint64_t* idx, uint64_t n, void* out, hipStream_t s) {
+  if (n == 0) return GGA_OK;
+  if (a->elem_bytes == 4) queue_gather<uint32_t>(a, idx, n, static_cast<uint32_t*>(out), s);
+  else queue_gather<uint64_t>(a, idx, n, static_cast<uint64_t*>(out), s);
   return hip_status(hipGetLastError());
 }
 

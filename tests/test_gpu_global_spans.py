@@ -24,6 +24,9 @@ pytestmark = pytest.mark.gpu
     (2048, 16, 2048 * 9 + 5),  # the whole offset array in LDS
     (2049, 16, 2049 * 9),      # every second offset
     (70000, 4, 70000 * 3),     # every 64th
+    (600, 1024, 700000),       # the span form from here on (2 KiB spans)
+    (20000, 16, 600000),       # short LFVectors: elements one by one within a span
+    (300, 1024, 18000000),     # 8 KiB spans
 ])
 def test_global_access(elem, V, F, n):
     print(f"case global elem={elem} V={V} F={F} n={n}", flush=True)
@@ -46,7 +49,7 @@ def test_global_access(elem, V, F, n):
     assert_same(a, o, "rw by global index")
     size = o.size()
     flat = o.flatten()
-    for reads in (1, 1023, 1025, 30000):
+    for reads in (1, 1023, 1025, 30000, (1 << 20) - 1, (1 << 20) + 5):
         idx = rng.integers(0, size, reads, dtype=np.uint64)
         idx[0], idx[-1] = 0, size - 1
         got = G.as_unsigned(a.gather(torch.from_numpy(idx.view(np.int64)).cuda()))
