@@ -1032,21 +1032,19 @@ __device__ __forceinline__ void store_span(const ArrRef& A, const Prod& prod, ui
 
 constexpr uint32_t kSpanBytes = 4096;  // one round of dense_store's loads (64 lanes, 4 vectors)
 
-// A round from a buffer in which every thread inserts: one workgroup of W waves
-// per LFVector.  Wave 0 allocates the buckets the round reaches; then the waves
-// take the LFVector's share in pieces of 4 KiB that start on whole lines of the
-// bucket, W pieces at a time.  What bounds a copy here is the bytes in flight: a
-// single wave per LFVector (the generated rounds' form, which only stores) waits
-// for memory once per 4 KiB (V = 512, 2.0e7 u32 elements: 44 us a round as one
-// wave each, 3.6 TB/s; 28 us, 5.7 TB/s, in this form).
+// LFVector v appends values[c0 .. c0 + cnt), by a workgroup of W waves: wave 0
+// allocates the buckets; then the waves take the share in pieces of 4 KiB that
+// start on whole lines of the bucket, W pieces at a time.  What bounds a copy here
+// is the bytes in flight: a single wave per LFVector (the generated rounds' form,
+// which only stores) waits for memory once per 4 KiB (V = 512, 2.0e7 u32 elements:
+// 44 us a round as one wave each, 3.6 TB/s; 28 us, 5.7 TB/s, in this form).
 template <typename T, uint32_t W>
-__global__ __launch_bounds__(64 * W) void grow_store_block_kernel(ArrRef A, TileArgs I, const T* values) {
+__device__ __forceinline__ void grow_store_block(const ArrRef& A, uint32_t elem_log2, const T* values, uint32_t v,
+                                                 uint64_t c0, uint64_t cnt) {
   constexpr uint64_t kSpan = kSpanBytes / sizeof(T), kLine = 128 / sizeof(T);
   __shared__ uint64_t s_bp[kMaxBuckets];
   __shared__ uint32_t s_fail;
-  const uint32_t v = blockIdx.x, tid = threadIdx.x, lane = tid & 63u;
-  const uint64_t c0 = (uint64_t)v * I.chunk;
-  const uint64_t cnt = c0 < I.n_threads ? (I.n_threads - c0 < I.chunk ? I.n_threads - c0 : I.chunk) : 0;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u;
   if (cnt == 0 || A.dead[v]) return;
   const uint32_t log2F = A.log2F;
   const uint64_t s0 = A.size[v], s1 = s0 + cnt;
@@ -1058,7 +1056,7 @@ __global__ __launch_bounds__(64 * W) void grow_store_block_kernel(ArrRef A, Tile
       if (b >= (uint32_t)kMaxBuckets) {
         failed = true;
       } else {
-        uint8_t* q = pool_alloc(A.pool, bucket_class(log2F, I.elem_log2, b), pool_shard(v, b, A.salt));
+        uint8_t* q = pool_alloc(A.pool, bucket_class(log2F, elem_log2, b), pool_shard(v, b, A.salt));
         s_bp[b] = row[b] = q ? (uint64_t)q : kFailedPtr;
         failed = !q;
       }
@@ -1081,6 +1079,15 @@ __global__ __launch_bounds__(64 * W) void grow_store_block_kernel(ArrRef A, Tile
     const uint64_t i0 = a < s0 ? s0 : a, i1 = a + kSpan < s1 ? a + kSpan : s1;
     store_span<T>(A, ProdBuffer<T>{values, nullptr}, i0, i1, c0 + (i0 - s0), [](uint32_t b) { return s_bp[b]; });
   }
+}
+
+// A round from a buffer in which every thread inserts, a workgroup per LFVector.
+template <typename T, uint32_t W>
+__global__ __launch_bounds__(64 * W) void grow_store_block_kernel(ArrRef A, TileArgs I, const T* values) {
+  const uint32_t v = blockIdx.x;
+  const uint64_t c0 = (uint64_t)v * I.chunk;
+  const uint64_t cnt = c0 < I.n_threads ? (I.n_threads - c0 < I.chunk ? I.n_threads - c0 : I.chunk) : 0;
+  grow_store_block<T, W>(A, I.elem_log2, values, v, c0, cnt);
 }
 
 // Segment append: LFVector v appends values[prefix[v] .. prefix[v + 1]).  A
@@ -1108,7 +1115,21 @@ __global__ __launch_bounds__(256) void segments_kernel(ArrRef A, TileArgs I, con
   grow_store_range<T, ProdBuffer<T>>(A, I, ProdBuffer<T>{values, nullptr}, v, lo, cnt);
 }
 
-// Longer segments: one wave per LFVector grows it, then `parts` workgroups per
+// Longer ones: one workgroup per LFVector (one launch; 9.5e5 8-byte elements in 256
+// segments of lognormal lengths: 37 us as one wave each, 9 this way).
+template <typename T, uint32_t W>
+__global__ __launch_bounds__(64 * W) void segments_block_kernel(ArrRef A, TileArgs I, const T* values,
+                                                                const uint64_t* prefix, uint64_t n_values) {
+  const uint32_t v = blockIdx.x;
+  uint64_t lo, cnt;
+  if (!segment_of(prefix, v, n_values, lo, cnt)) {
+    if (threadIdx.x == 0) set_error(A.err, kErrRange);
+    return;
+  }
+  grow_store_block<T, W>(A, I.elem_log2, values, v, lo, cnt);
+}
+
+// The longest: one wave per LFVector grows it, then `parts` workgroups per
 // LFVector store its segment in pieces of 4 KiB that start on whole lines of the
 // bucket.  One wave copying a segment waits for a round trip to memory per 4 KiB
 // and the longest segment holds the launch (3.0e7 u32 elements in 512 segments of
@@ -2350,17 +2371,24 @@ template <typename T>
 static void queue_segments(const ArrRef& A, const TileArgs& I, const T* values, const uint64_t* prefix,
                            uint64_t n_values, hipStream_t s) {
   const dim3 grid((A.V + 3) / 4), block(256);
-  // One launch while the segments average at most one load round of a wave; the
-  // second launch costs about 5 us, more than it saves below that.
+  // One launch, with a wave per LFVector while the segments average at most one load
+  // round of a wave, or a workgroup per LFVector up to eight; above that, and with
+  // too many LFVectors for workgroups of sixteen waves, the store launch is worth
+  // its 5 us for the balance (lognormal segments, workgroups against two launches:
+  // 8.0e6 u32 elements in 512 26.6 and 21 us, 1.5e7 in 4096 45 and 39 us).
   const uint64_t spans = n_values * sizeof(T) / kSpanBytes;
   if (spans <= A.V) {
     hipLaunchKernelGGL(segments_kernel<T>, grid, block, 0, s, A, I, values, prefix, n_values);
     return;
   }
+  if (A.V <= 1024 && spans <= 8ull * A.V) {
+    hipLaunchKernelGGL((segments_block_kernel<T, 16>), dim3(A.V), dim3(1024), 0, s, A, I, values, prefix, n_values);
+    return;
+  }
   // Twice the workgroups that equal segments would need, so that a segment of
-  // several times the average still finishes with the others, up to 32 per CU.
+  // several times the average still finishes with the others, up to 128 per CU.
   uint64_t parts = (2 * spans / kW + A.V - 1) / A.V;
-  const uint64_t most = (8192 + A.V - 1) / A.V;
+  const uint64_t most = (32768 + A.V - 1) / A.V;
   if (parts > most) parts = most;
   hipLaunchKernelGGL(segments_grow_kernel, grid, block, 0, s, A, I, prefix, n_values);
   hipLaunchKernelGGL(segments_store_kernel<T>, dim3((uint32_t)(parts * A.V)), dim3(kB), 0, s, A, values, prefix,

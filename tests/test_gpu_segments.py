@@ -30,6 +30,10 @@ def _lens(rng, V, total, shape):
 @pytest.mark.parametrize("V,F,total,shape", [
     (1, 1024, 1024, "even"),            # the last size of the one-launch form
     (1, 1024, 2049, "even"),            # just past it
+    (1, 16, 8 * 1024, "even"),          # u32: the last size of the workgroup form, u64: past it
+    (1, 16, 9 * 1024, "even"),
+    (40, 1024, 40 * 4 * 1024, "one"),
+    (1030, 64, 1030 * 1500, "uneven"),  # too many LFVectors for it
     (6, 1, 70001, "uneven"),
     (32, 1024, 300007, "uneven"),
     (64, 16, 200003, "one"),
