@@ -434,6 +434,37 @@ __device__ __forceinline__ uint64_t K(uint64_t seed, uint64_t a, uint64_t b) {
   return splitmix64((seed << 56) ^ (a << 8) ^ b);
 }
 
+// SplitMix64 outputs for the states first .. first + span - 1 of one wave.  The
+// generated payloads are bound by the six quarter-rate multiplications of an output.
+// States so close together nearly always share their upper half, so its part of the
+// first product is one number for the whole run, and an output takes five, after
+// one addition instead of the shifts and xors that put a state together (512
+// arrays, a keyed round of 2.4e8 u32 elements: 246 -> 207 us, 4.6 TB/s).
+struct MixRun {
+  static constexpr uint32_t kLo = 0x1CE4E5B9u, kHi = 0xBF58476Du;  // the first multiplier
+  uint64_t z0;
+  uint32_t hi, c1;
+  bool flat;
+  __device__ __forceinline__ MixRun(uint64_t first, uint64_t span) : z0(first + 0x9E3779B97F4A7C15ull) {
+    hi = (uint32_t)(z0 >> 32);
+    c1 = (hi ^ (hi >> 30)) * kLo;
+    flat = (z0 & 0xFFFFFFFFull) + span <= 0x100000000ull;
+  }
+  __device__ __forceinline__ uint64_t operator()(uint64_t off) const {  // off < span
+    uint64_t z;
+    if (__builtin_expect(flat, 1)) {
+      uint32_t lo = (uint32_t)z0 + (uint32_t)off;
+      lo ^= __builtin_amdgcn_alignbit(hi, lo, 30);  // z ^ (z >> 30), lower half
+      z = (uint64_t)lo * kLo + ((uint64_t)c1 << 32) + ((uint64_t)(lo * kHi) << 32);
+    } else {
+      z = z0 + off;
+      z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    }
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    return z ^ (z >> 31);
+  }
+};
+
 // r/w operations.
 template <typename T>
 __device__ __forceinline__ T apply_op(uint32_t op, T x) {

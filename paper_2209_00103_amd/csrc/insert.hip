@@ -404,11 +404,12 @@ __device__ __forceinline__ SlotMask wave_take(const Prod& prod, uint64_t g0, uin
   SlotMask m;
 #pragma unroll
   for (int k = 0; k < kMaskWords; ++k) m.w[k] = 0;
+  const typename Prod::Run run = prod.run(g0, kWaveTile);
 #pragma unroll
   for (int j = 0; j < kWaveSlots; ++j) {
     const uint64_t g = g0 + (uint64_t)j * 64 + lane;
     T v = 0;
-    const bool f = g < gend && prod.take(g, v);
+    const bool f = g < gend && run.take(j * 64 + lane, v);
     vals[j] = v;
     if (f) m.w[j >> 6] |= 1ull << (j & 63);
   }
@@ -443,19 +444,20 @@ template <typename T, class Prod>
 __device__ __forceinline__ void dense_store(T* dst, const Prod& prod, uint64_t g0, uint32_t n) {
   constexpr uint32_t VPL = 16 / sizeof(T);
   const uint32_t lane = lane_id();
+  const typename Prod::Run run = prod.run(g0, n);
   constexpr uint32_t kLine = 128 / sizeof(T);
   const uint32_t mis = (uint32_t)((reinterpret_cast<uintptr_t>(dst) & 127u) / sizeof(T));
   uint32_t head = mis ? kLine - mis : 0u;
   if (head > n) head = n;
   const gptr<T> d = gmem(dst);
-  if (lane < head) d[lane] = prod.value(g0 + lane);
+  if (lane < head) d[lane] = run(lane);
   const uint32_t nv = (n - head) / VPL;
   if constexpr (Prod::kDense) {  // generated payloads: no loads in the loop
     for (uint32_t q = lane; q < nv; q += 64) {
       const uint32_t e = head + q * VPL;
       T tmp[VPL];
 #pragma unroll
-      for (uint32_t k = 0; k < VPL; ++k) tmp[k] = prod.value(g0 + e + k);
+      for (uint32_t k = 0; k < VPL; ++k) tmp[k] = run(e + k);
       u32x4 x;
       __builtin_memcpy(&x, tmp, 16);
       store_nt_sc1(reinterpret_cast<gptr<u32x4>>(d + e), x);
@@ -472,7 +474,7 @@ __device__ __forceinline__ void dense_store(T* dst, const Prod& prod, uint64_t g
         const uint32_t e = head + (q < nv ? q : nv - 1) * VPL;
         T tmp[VPL];
 #pragma unroll
-        for (uint32_t k = 0; k < VPL; ++k) tmp[k] = prod.value(g0 + e + k);
+        for (uint32_t k = 0; k < VPL; ++k) tmp[k] = run(e + k);
         __builtin_memcpy(&x[u], tmp, 16);
       }
 #pragma unroll
@@ -483,7 +485,7 @@ __device__ __forceinline__ void dense_store(T* dst, const Prod& prod, uint64_t g
     }
   }
   const uint32_t tail = head + nv * VPL + lane;
-  if (tail < n) d[tail] = prod.value(g0 + tail);
+  if (tail < n) d[tail] = run(tail);
 }
 
 // One wave, one tile; `block` is the wave's index among the launch's waves for
@@ -673,11 +675,12 @@ __global__ __launch_bounds__(64 * W) void insert_block_kernel(ArrRef A, TileArgs
 #pragma unroll
     for (uint32_t j = 0; j < S; ++j) keep |= (uint32_t)(f[j] && g0 + j * (64 * W) + tid < gend) << j;
   } else {
+    const typename Prod::Run run = prod.run(g0, 64 * W * S);
 #pragma unroll
     for (uint32_t j = 0; j < S; ++j) {
-      const uint64_t g = g0 + j * (64 * W) + tid;
+      const uint32_t d = j * (64 * W) + tid;
       val[j] = 0;
-      keep |= (uint32_t)(g < gend && prod.take(g, val[j])) << j;
+      keep |= (uint32_t)(g0 + d < gend && run.take(d, val[j])) << j;
     }
   }
   uint32_t rank[S];
@@ -1285,13 +1288,14 @@ __global__ __launch_bounds__(256) void static_atomic_kernel(StaticRef S, uint64_
 // across the wave (partial lines left by element-wise stores cost about 5% extra
 // HBM writes, measured), then the ragged tail.  Bucket and offset are computed
 // once per run, not per element.  The map covers 8192 outputs at a time.
-template <typename Prod, int K = kCountK>
-__device__ __forceinline__ uint32_t produce_counts(const Prod& prod, uint64_t gt, uint64_t gend,
-                                                   uint32_t* cnt) {
+// Counts of this thread's K logical threads, the first of them first threads after
+// the tile's; live: threads of the tile.
+template <class Tile, int K = kCountK>
+__device__ __forceinline__ uint32_t produce_counts(const Tile& tile, uint32_t first, uint64_t live, uint32_t* cnt) {
   uint32_t c = 0;
 #pragma unroll
   for (int j = 0; j < K; ++j) {
-    cnt[j] = (gt + j < gend) ? prod.count(gt + j) : 0u;
+    cnt[j] = first + j < live ? tile.count(first + j) : 0u;
     c += cnt[j];
   }
   return c;
@@ -1299,9 +1303,8 @@ __device__ __forceinline__ uint32_t produce_counts(const Prod& prod, uint64_t gt
 
 // Outputs own[0 .. n) of a run, stored at dst (element-aligned) by a workgroup of
 // kThreads threads.
-template <typename T, class Prod, uint32_t kThreads = kB>
-__device__ __forceinline__ void store_owned_run(T* dst_, const uint16_t* own, uint32_t n, const Prod& prod,
-                                                uint64_t g0) {
+template <typename T, class Tile, uint32_t kThreads = kB>
+__device__ __forceinline__ void store_owned_run(T* dst_, const uint16_t* own, uint32_t n, const Tile& tile) {
   constexpr uint32_t VPL = 16 / sizeof(T), kLine = 128 / sizeof(T);
   static_assert(kLine <= kThreads, "head and tail in one store each");
   const uint32_t tid = threadIdx.x;
@@ -1311,7 +1314,7 @@ __device__ __forceinline__ void store_owned_run(T* dst_, const uint16_t* own, ui
   if (head > n) head = n;
   if (tid < head) {
     const uint32_t o = own[tid];
-    __builtin_nontemporal_store(prod.value(g0 + (o >> 4), o & 15u), dst + tid);
+    __builtin_nontemporal_store(tile.value(o >> 4, o & 15u), dst + tid);
   }
   const uint32_t nv = (n - head) / VPL;
   for (uint32_t q = tid; q < nv; q += kThreads) {
@@ -1320,7 +1323,7 @@ __device__ __forceinline__ void store_owned_run(T* dst_, const uint16_t* own, ui
 #pragma unroll
     for (uint32_t k = 0; k < VPL; ++k) {
       const uint32_t o = own[e + k];
-      tmp[k] = prod.value(g0 + (o >> 4), o & 15u);
+      tmp[k] = tile.value(o >> 4, o & 15u);
     }
     u32x4 x;
     __builtin_memcpy(&x, tmp, 16);
@@ -1329,7 +1332,7 @@ __device__ __forceinline__ void store_owned_run(T* dst_, const uint16_t* own, ui
   const uint32_t tail = head + nv * VPL + tid;
   if (tail < n) {
     const uint32_t o = own[tail];
-    __builtin_nontemporal_store(prod.value(g0 + (o >> 4), o & 15u), dst + tail);
+    __builtin_nontemporal_store(tile.value(o >> 4, o & 15u), dst + tail);
   }
 }
 
@@ -1352,8 +1355,8 @@ __global__ __launch_bounds__(kB) void insert_count_kernel(ArrRef A, StaticRef S,
     tile_range(I, v, t, kCountTile, g0, gend);
   }
   uint32_t cnt[kCountK];
-  uint64_t gt = g0 + (uint64_t)tid * kCountK;
-  uint32_t c = produce_counts<Prod>(prod, gt, gend, cnt);
+  typename Prod::Tile tile = prod.tile(g0);
+  uint32_t c = produce_counts(tile, tid * kCountK, g0 < gend ? gend - g0 : 0, cnt);
   if (ticketed && tid == 0) {
     sh.tile = k;
     settle_ticket(A, v, k, I.tpv);
@@ -1363,8 +1366,8 @@ __global__ __launch_bounds__(kB) void insert_count_kernel(ArrRef A, StaticRef S,
   if (ticketed && (sh.tile & 0xFFFFFFFFull) != t) {  // dispatched out of order: produce for the ticket
     t = sh.tile & 0xFFFFFFFFull;
     tile_range(I, v, t, kCountTile, g0, gend);
-    gt = g0 + (uint64_t)tid * kCountK;
-    c = produce_counts<Prod>(prod, gt, gend, cnt);
+    tile = prod.tile(g0);
+    c = produce_counts(tile, tid * kCountK, g0 < gend ? gend - g0 : 0, cnt);
   }
   if (g0 >= gend) return;
   const bool is_last = g0 + kCountTile >= gend;
@@ -1407,7 +1410,7 @@ __global__ __launch_bounds__(kB) void insert_count_kernel(ArrRef A, StaticRef S,
     }
     __syncthreads();
     if (kStatic) {
-      store_owned_run<T, Prod>(reinterpret_cast<T*>(S.data) + base + w0, s_own, w1 - w0, prod, g0);
+      store_owned_run<T>(reinterpret_cast<T*>(S.data) + base + w0, s_own, w1 - w0, tile);
       continue;
     }
     for (uint32_t i = w0; i < w1;) {  // one run per bucket the window's outputs reach
@@ -1417,7 +1420,7 @@ __global__ __launch_bounds__(kB) void insert_count_kernel(ArrRef A, StaticRef S,
       const uint64_t room = bs + bucket_len(log2F, b) - idx;
       const uint32_t run = (uint64_t)(w1 - i) < room ? w1 - i : (uint32_t)room;
       const uint64_t p = sh.bp[b - sh.b_lo];
-      if (p > kFailedPtr) store_owned_run<T, Prod>(reinterpret_cast<T*>(p) + (idx - bs), s_own + (i - w0), run, prod, g0);
+      if (p > kFailedPtr) store_owned_run<T>(reinterpret_cast<T*>(p) + (idx - bs), s_own + (i - w0), run, tile);
       i += run;
     }
   }
@@ -1442,7 +1445,8 @@ __global__ __launch_bounds__(64) void insert_count_wave_kernel(ArrRef A, TileArg
   if (g0 >= gend || A.dead[v]) return;
   const uint64_t size0 = A.size[v];
   uint32_t cnt[K];
-  const uint32_t c = produce_counts<Prod, K>(prod, g0 + (uint64_t)lane * K, gend, cnt);
+  const typename Prod::Tile tile = prod.tile(g0);
+  const uint32_t c = produce_counts<typename Prod::Tile, K>(tile, lane * K, gend - g0, cnt);
   const uint32_t incl = wave_incl_scan(c), n_t = __shfl(incl, 63, 64);
   const WaveRes r = resolve_wave(A, I, v, 0, 0, true, n_t, size0, 0);
   const uint32_t log2F = A.log2F;
@@ -1464,7 +1468,7 @@ __global__ __launch_bounds__(64) void insert_count_wave_kernel(ArrRef A, TileArg
       const uint32_t run = (uint64_t)(w1 - i) < room ? w1 - i : (uint32_t)room;
       const uint64_t p = __shfl(r.bp, (int)(b - r.b_lo), 64);
       if (p > kFailedPtr)
-        store_owned_run<T, Prod, 64>(reinterpret_cast<T*>(p) + (idx - bs), s_own + (i - w0), run, prod, g0);
+        store_owned_run<T, typename Prod::Tile, 64>(reinterpret_cast<T*>(p) + (idx - bs), s_own + (i - w0), run, tile);
       i += run;
     }
     __syncthreads();  // the window is read before the next one is written

@@ -2,6 +2,10 @@
 // inserts and what (the synthetic workloads of the benchmark configurations and
 // the buffer inputs of the C ABI).  Shared by the round kernels and the
 // persistent step kernel, so every path produces the same elements.
+//
+// run(g0, n) gives the elements of the n consecutive threads from g0 on by their
+// distance from g0 (K's argument grows by 256 per thread, seed and round occupying
+// the bits above and below the thread's, so xor and sum agree).
 #pragma once
 
 #include "gga_internal.h"
@@ -21,6 +25,11 @@ struct ProdBuffer {
   const uint8_t* flags;
   __device__ __forceinline__ bool flag(uint64_t g) const { return flags[g] != 0; }
   __device__ __forceinline__ T value(uint64_t g) const { return values[g]; }
+  struct Run {
+    const T* p;
+    __device__ __forceinline__ T operator()(uint32_t d) const { return p[d]; }
+  };
+  __device__ __forceinline__ Run run(uint64_t g0, uint64_t) const { return {values + g0}; }
 };
 template <typename T>
 struct ProdBernoulli {  // h = K(seed, gid, round); insert (T)h iff top bit
@@ -35,6 +44,18 @@ struct ProdBernoulli {  // h = K(seed, gid, round); insert (T)h iff top bit
     const uint64_t h = K(seed, g, round);
     v = (T)h;
     return (h >> 63) != 0;
+  }
+  struct Run {
+    MixRun mix;
+    __device__ __forceinline__ T operator()(uint32_t d) const { return (T)mix((uint64_t)d << 8); }
+    __device__ __forceinline__ bool take(uint32_t d, T& v) const {
+      const uint64_t h = mix((uint64_t)d << 8);
+      v = (T)h;
+      return (h >> 63) != 0;
+    }
+  };
+  __device__ __forceinline__ Run run(uint64_t g0, uint64_t n) const {
+    return {MixRun((seed << 56) + (g0 << 8) + round, n << 8)};
   }
   __device__ __forceinline__ void bind(const BatchArr&) {}
 };
@@ -51,6 +72,13 @@ struct ProdRoundTag {  // insert (round << shift) | gid
     v = value(g);
     return true;
   }
+  struct Run {
+    ProdRoundTag prod;
+    uint64_t g0;
+    __device__ __forceinline__ T operator()(uint32_t d) const { return prod.value(g0 + d); }
+    __device__ __forceinline__ bool take(uint32_t d, T& v) const { return prod.take(g0 + d, v); }
+  };
+  __device__ __forceinline__ Run run(uint64_t g0, uint64_t) const { return {*this, g0}; }
   __device__ __forceinline__ void bind(const BatchArr&) {}
 };
 template <typename T>
@@ -68,6 +96,17 @@ struct ProdKeyed {  // every thread inserts K(seed, (tag << shift) | gid, round)
     v = value(g);
     return true;
   }
+  struct Run {
+    MixRun mix;
+    __device__ __forceinline__ T operator()(uint32_t d) const { return (T)mix((uint64_t)d << 8); }
+    __device__ __forceinline__ bool take(uint32_t d, T& v) const {
+      v = (T)mix((uint64_t)d << 8);
+      return true;
+    }
+  };
+  __device__ __forceinline__ Run run(uint64_t g0, uint64_t n) const {
+    return {MixRun((seed << 56) + (((tag << shift) | g0) << 8) + round, n << 8)};
+  }
   __device__ __forceinline__ void bind(const BatchArr& it) { tag = it.tag; }  // each array its own key
 };
 template <typename T>
@@ -80,9 +119,17 @@ struct ProdCounts {  // insert values[gid * max + j], j < counts[gid]
     const uint32_t c = counts[g];
     return c < max_count ? c : max_count;
   }
-  __device__ __forceinline__ T value(uint64_t g, uint32_t r) const {
-    return values[g * max_count + r];
-  }
+  // The counts and elements of a tile's threads by their distance from its first
+  // thread g0 (at most 1024 of them).
+  struct Tile {
+    ProdCounts prod;
+    uint64_t g0;
+    __device__ __forceinline__ uint32_t count(uint32_t d) const { return prod.count(g0 + d); }
+    __device__ __forceinline__ T value(uint32_t d, uint32_t r) const {
+      return prod.values[(g0 + d) * prod.max_count + r];
+    }
+  };
+  __device__ __forceinline__ Tile tile(uint64_t g0) const { return {*this, g0}; }
 };
 template <typename T>
 struct ProdPoisson {  // c = #{k : K(seed,gid,0x80|round) >= thr[k]}; insert K(seed,gid,16 round + j)
@@ -91,15 +138,21 @@ struct ProdPoisson {  // c = #{k : K(seed,gid,0x80|round) >= thr[k]}; insert K(s
   uint32_t round;
   uint32_t max_count;
   uint64_t thr[16];
-  __device__ __forceinline__ uint32_t count(uint64_t g) const {
-    const uint64_t u = K(seed, g, 0x80u | round);
-    uint32_t c = 0;
+  struct Tile {
+    const ProdPoisson* prod;
+    MixRun draws, mix;
+    __device__ __forceinline__ uint32_t count(uint32_t d) const {
+      const uint64_t u = draws((uint64_t)d << 8);
+      uint32_t c = 0;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) c += (k < (int)max_count && u >= thr[k]) ? 1u : 0u;
-    return c;
-  }
-  __device__ __forceinline__ T value(uint64_t g, uint32_t r) const {
-    return (T)K(seed, g, 16u * round + r);
+      for (int k = 0; k < 16; ++k) c += (k < (int)prod->max_count && u >= prod->thr[k]) ? 1u : 0u;
+      return c;
+    }
+    __device__ __forceinline__ T value(uint32_t d, uint32_t r) const { return (T)mix(((uint64_t)d << 8) + r); }
+  };
+  __device__ __forceinline__ Tile tile(uint64_t g0) const {
+    const uint64_t first = (seed << 56) + (g0 << 8);
+    return {this, MixRun(first + (0x80u | round), 1024u << 8), MixRun(first + 16u * round, 1024u << 8)};
   }
 };
 

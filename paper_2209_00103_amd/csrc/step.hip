@@ -621,8 +621,11 @@ __device__ void wave_copy(T* dst_, const T* src_, uint64_t n) {
 
 }  // namespace
 
+// Three waves per SIMD for 4-byte elements: one more than the 168 registers that
+// allow them leaves two (512 arrays of configuration 4's sizes, a whole step: 4026
+// against 4140 us).
 template <typename T>
-__global__ __launch_bounds__(kSB) void step_wave_kernel(const BatchArr* arrs, const uint32_t* varr,
+__global__ __launch_bounds__(kSB, sizeof(T) == 4 ? 3 : 2) void step_wave_kernel(const BatchArr* arrs, const uint32_t* varr,
                                                         const uint64_t* vbegin, uint64_t total_v, StepDesc D,
                                                         const uint64_t* counts, uint32_t n_arr, uint32_t op, T* out,
                                                         uint64_t out_cap, uint32_t* sync, uint64_t* chunk_sum,
