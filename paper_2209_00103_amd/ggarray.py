@@ -156,9 +156,13 @@ def _check(status: int, what: str) -> None:
         raise GGAError(status, what)
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+def _stream(stream):
+    """The hipStream_t (an integer) of `stream`, or of the current device's current
+    stream, asked for without building a Stream object (3.1 -> 0.4 us of a call that
+    takes 4 us in the library)."""
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _dtype(elem_bytes: int) -> torch.dtype:
