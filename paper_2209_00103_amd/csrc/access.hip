@@ -229,6 +229,13 @@ __global__ void capacity_kernel(ArrRef A, uint64_t* out) {
   if (c) fetch_add(out, c);
 }
 
+// The words that a synchronising call returns, straight into the array's pinned
+// host memory: *word (if any) and the sticky error.
+__global__ void report_kernel(const uint64_t* word, const uint32_t* err, uint64_t* host) {
+  if (word) host[0] = *word;
+  host[1] = *err;
+}
+
 // One tile: cnt (<= te) elements at src (16-byte aligned); rw in place, or copy
 // to dst (element aligned) for flatten.  Lane i of slot k handles the 16 bytes
 // at element k * (256 * VPL) + i * VPL.  Every byte is touched once, so stores
@@ -861,6 +868,11 @@ int launch_rw(ggarray* a, uint32_t op, hipStream_t s) {
                        (uint64_t*)nullptr, (uint64_t)0, te_log2);
   }
   a->last_rw_gen = a->sizes_gen + 1;
+int launch_report(ggarray* a, const uint64_t* word, uint64_t* host, hipStream_t s) {
+  hipLaunchKernelGGL(report_kernel, dim3(1), dim3(1), 0, s, word, a->ref.err, host);
+  return hip_status(hipGetLastError());
+}
+
   return hip_status(hipGetLastError());
 }
 

@@ -426,7 +426,14 @@ int launch_insert_rounds(ggarray* a, const InsertDesc* ds, uint32_t n, hipStream
                          uint32_t sh_den, bool clear);
 int launch_static_insert(gga_static* st, const InsertDesc& d, hipStream_t s);
 int launch_static_insert_atomic(gga_static* st, const InsertDesc& d, hipStream_t s);
-int launch_scan(ggarray* a, hipStream_t s, uint64_t* copy = nullptr);
+// The prefix scan (copy: also write the prefix there), with the tile table in the
+// same launch where the array streams through one and has few enough LFVectors:
+// grown for an r/w or flatten that follows, only if it is large enough already for
+// other readers of the prefix.
+enum ScanTable : uint32_t { kScanOnly = 0, kScanKeepTable = 1, kScanGrowTable = 2 };
+int launch_scan(ggarray* a, hipStream_t s, uint64_t* copy = nullptr, ScanTable table = kScanOnly);
+// *word (may be null) and the sticky error into host[0] and host[1] (pinned).
+int launch_report(ggarray* a, const uint64_t* word, uint64_t* host, hipStream_t s);
 int launch_insert_packed(ggarray* a, const void* values, const uint8_t* counts, uint64_t n_threads,
                          uint64_t n_values, hipStream_t s);
 // The same round with its per-call buffers in the library's static scratch.
