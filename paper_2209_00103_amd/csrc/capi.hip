@@ -408,13 +408,14 @@ int ggarray_shrink(ggarray* a, uint32_t num, uint32_t den, gga_stream s) {
 // A prefix is reused only where it was built: eagerly for eager calls, in the
 // same capture for captured calls, so that a replay never reads a prefix left
 // over from before its capture.
-static int ensure_prefix(ggarray* a, hipStream_t s) {
-  return a->prefix_valid && capture_reuse(a, a->scan_tag, stream_capture_tag(s)) ? GGA_OK : launch_scan(a, s);
+static int ensure_prefix(ggarray* a, hipStream_t s, ScanTable table = kScanOnly) {
+  return a->prefix_valid && capture_reuse(a, a->scan_tag, stream_capture_tag(s)) ? GGA_OK
+                                                                                 : launch_scan(a, s, nullptr, table);
 }
 
 int ggarray_rw(ggarray* a, uint32_t op, gga_stream s) {
   if (!a || op > GGA_ADD1_X30) return GGA_EINVAL;
-  int rc = ensure_prefix(a, S(s));
+  int rc = ensure_prefix(a, S(s), kScanGrowTable);
   return rc ? rc : launch_rw(a, op, S(s));
 }
 
@@ -432,13 +433,13 @@ int ggarray_gather(ggarray* a, const uint64_t* idx, uint64_t n, void* out, gga_s
 
 int ggarray_flatten(ggarray* a, void* out, uint64_t out_cap_elems, gga_stream s) {
   if (!a || (!out && out_cap_elems)) return GGA_EINVAL;
-  int rc = ensure_prefix(a, S(s));
+  int rc = ensure_prefix(a, S(s), kScanGrowTable);
   return rc ? rc : launch_flatten(a, out, out_cap_elems, S(s));
 }
 
-static int read_back(ggarray* a, const uint64_t* dev_word, uint64_t* out_host, hipStream_t s) {
 // One kernel writes both words into the array's pinned memory (two copies before it:
 // 16.3 us for a size that nothing else waits for, 12.1 this way).
+static int read_back(ggarray* a, const uint64_t* dev_word, uint64_t* out_host, hipStream_t s) {
   ggarray_full* f = reinterpret_cast<ggarray_full*>(a);
   volatile uint64_t* h = f->x.pin.p;
   const int rc = launch_report(a, dev_word, f->x.pin.p, s);
@@ -477,7 +478,7 @@ int ggarray_vector_sizes(ggarray* a, uint64_t* dev_out, gga_stream s) {
 int ggarray_prefix(ggarray* a, uint64_t* dev_out, gga_stream s) {
   if (!a || !dev_out) return GGA_EINVAL;
   if (!a->prefix_valid || !capture_reuse(a, a->scan_tag, stream_capture_tag(S(s))))
-    return launch_scan(a, S(s), dev_out);  // the scan writes both
+    return launch_scan(a, S(s), dev_out, kScanKeepTable);  // the scan writes both
   return hip_status(hipMemcpyAsync(dev_out, a->ref.prefix, 8ull * (a->V + 1), hipMemcpyDeviceToDevice, S(s)));
 }
 

@@ -440,7 +440,7 @@ int launch_insert_packed(ggarray* a, const void* values, const uint8_t* counts, 
 int launch_insert_packed_noalloc(ggarray* a, const void* values, const uint8_t* counts, uint64_t n_threads,
                                  uint64_t n_values, hipStream_t s);
 int launch_insert_segments(ggarray* a, const void* values, const uint64_t* prefix, uint64_t n_values,
-                           hipStream_t s);  // copy: also write the prefix there
+                           hipStream_t s);
 int launch_shrink(ggarray* a, uint32_t num, uint32_t den, hipStream_t s);
 int launch_rw(ggarray* a, uint32_t op, hipStream_t s);
 int launch_flatten(ggarray* a, void* out, uint64_t cap, hipStream_t s);
