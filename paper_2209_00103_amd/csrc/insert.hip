@@ -1545,16 +1545,21 @@ struct CountLoad {
       x.x = counts[g0 + lane];
     }
   }
-  __device__ __forceinline__ uint32_t wave_sum() const {
+  // The lane's counts, zero in place of those that are not its own.
+  __device__ __forceinline__ u32x4 own() const {
     uint64_t lo = ((uint64_t)x.y << 32) | x.x, hi = ((uint64_t)x.w << 32) | x.z;
     if (drop) {
       hi = drop >= 16 ? 0 : drop > 8 ? hi >> (8 * (drop - 8)) : hi;
       lo = drop >= 8 ? 0 : lo >> (8 * drop);
     }
-    uint32_t c = __builtin_amdgcn_sad_u8((uint32_t)lo, 0u, 0u);  // sum of the four bytes
-    c = __builtin_amdgcn_sad_u8((uint32_t)(lo >> 32), 0u, c);
-    c = __builtin_amdgcn_sad_u8((uint32_t)hi, 0u, c);
-    c = __builtin_amdgcn_sad_u8((uint32_t)(hi >> 32), 0u, c);
+    return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+  }
+  __device__ __forceinline__ uint32_t wave_sum() const {
+    const u32x4 y = own();
+    uint32_t c = __builtin_amdgcn_sad_u8(y.x, 0u, 0u);  // sum of the four bytes
+    c = __builtin_amdgcn_sad_u8(y.y, 0u, c);
+    c = __builtin_amdgcn_sad_u8(y.z, 0u, c);
+    c = __builtin_amdgcn_sad_u8(y.w, 0u, c);
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);
     return c;
@@ -2108,6 +2113,93 @@ __global__ __launch_bounds__(64) void flag_copy_kernel(ArrRef A, TileArgs I, con
   }
 }
 
+// ---------------------------------------- padded counts rounds in two passes --
+// A round of counts over a padded buffer whose LFVectors span several 1024-thread
+// tiles runs as the flagged rounds do: the tiles' sums, their offsets and the growth
+// of every LFVector (flag_grow_kernel), then a copy through the owner map of
+// insert_count_kernel with every offset known, in place of tickets and a look-back.
+// (Reading a tile's rows whole in 16-byte vectors and compacting them in LDS
+// measured slower: 28 against 23 us at two of four elements a row, 206 against 56 us
+// at 0.3 of sixteen 8-byte ones.)  The one launch is shorter while all its
+// workgroups fit the chip at once: V = 512, 7.0e5 threads, 1024 tiles, 9-12 against
+// 15 us; V = 256, 4.0e6, 4096 tiles, 36-44 against 33 us; V = 4096, 2.0e7, 20480
+// tiles, 122 against 84 us.
+constexpr uint64_t kCountsOneLaunch = 2048;
+__device__ __forceinline__ uint32_t clamped_sum(u32x4 x, uint32_t max_count) {
+  uint32_t c = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < 16; ++k) {
+    const uint32_t b = (x[k / 4] >> (8 * (k & 3))) & 0xFFu;
+    c += b < max_count ? b : max_count;
+  }
+  return c;
+}
+
+__global__ __launch_bounds__(kB) void counts_sum_kernel(TileArgs I, const uint8_t* counts, uint32_t max_count,
+                                                        uint64_t* tiles, uint64_t ntiles) {
+  const uint64_t tile = (uint64_t)blockIdx.x * kW + (threadIdx.x >> 6);
+  if (tile >= ntiles) return;
+  const uint32_t v = (uint32_t)(tile / I.tpv);
+  uint64_t g0, gend;
+  tile_range(I, v, tile - (uint64_t)v * I.tpv, kCountTile, g0, gend);
+  if (gend > g0 + kCountTile) gend = g0 + kCountTile;
+  CountLoad ld;
+  ld.load(counts, g0, gend);
+  uint32_t c = clamped_sum(ld.own(), max_count);
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);
+  if (lane_id() == 0) tiles[tile] = c;
+}
+
+template <typename T>
+__global__ __launch_bounds__(kB) void counts_copy_kernel(ArrRef A, TileArgs I, ProdCounts<T> prod,
+                                                         const uint64_t* tiles) {
+  __shared__ uint16_t s_own[kOwnWindow];
+  __shared__ uint64_t s_bp[64];
+  __shared__ uint32_t s_wave[kW];
+  const uint64_t t = blockIdx.x;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, w = tid >> 6;
+  const uint32_t v = (uint32_t)(t / I.tpv);
+  uint64_t g0, gend;
+  tile_range(I, v, t - (uint64_t)v * I.tpv, kCountTile, g0, gend);
+  const uint64_t at = tiles[t];
+  const uint32_t n_t = (uint32_t)at & 0xFFFFu;
+  if (n_t == 0 || A.dead[v]) return;
+  const uint64_t base = A.rbase[v] + (at >> 16);
+  const uint32_t log2F = A.log2F;
+  const uint32_t b_lo = bucket_of(log2F, base), b_hi = bucket_of(log2F, base + n_t - 1);
+  if (tid < 64 && b_lo + lane <= b_hi) s_bp[lane] = A.bptr[(uint64_t)v * kMaxBuckets + b_lo + lane];
+  uint32_t cnt[kCountK];
+  const typename ProdCounts<T>::Tile tile = prod.tile(g0);
+  const uint32_t c = produce_counts(tile, tid * kCountK, gend - g0, cnt);
+  const uint32_t incl = wave_incl_scan(c);
+  if (lane == 63) s_wave[w] = incl;
+  __syncthreads();
+  uint32_t excl = incl - c;
+  for (uint32_t q = 0; q < w; ++q) excl += s_wave[q];
+  for (uint32_t w0 = 0; w0 < n_t; w0 += kOwnWindow) {
+    const uint32_t w1 = n_t - w0 < kOwnWindow ? n_t : w0 + kOwnWindow;
+    if (w0) __syncthreads();  // the previous window has been read
+    uint32_t e = excl - w0;   // wraps for outputs before the window, which fail the test
+#pragma unroll
+    for (uint32_t j = 0; j < (uint32_t)kCountK; ++j) {
+      const uint32_t ent = (tid << 6) | (j << 4);
+      for (uint32_t r = 0; r < cnt[j]; ++r, ++e)
+        if (e < kOwnWindow) s_own[e] = (uint16_t)(ent | r);
+    }
+    __syncthreads();
+    for (uint32_t i = w0; i < w1;) {  // one run per bucket the window's outputs reach
+      const uint64_t idx = base + i;
+      const uint32_t b = bucket_of(log2F, idx);
+      const uint64_t bs = bucket_start(log2F, b);
+      const uint64_t room = bs + bucket_len(log2F, b) - idx;
+      const uint32_t run = (uint64_t)(w1 - i) < room ? w1 - i : (uint32_t)room;
+      store_owned_run<T>(reinterpret_cast<T*>(s_bp[b - b_lo]) + (idx - bs), s_own + (i - w0), run, tile);
+      i += run;
+    }
+  }
+}
+
 // ---------------------------------------------------------------- dispatch --
 template <typename T, bool kStatic>
 int dispatch(const ArrRef& A, const StaticRef& S, const TileArgs& I, const InsertDesc& d,
@@ -2241,7 +2333,17 @@ int ensure_status(ggarray* a, uint64_t ntiles, hipStream_t s) {
 }  // namespace
 
 static int queue_flag_rounds(ggarray* a, const InsertDesc& d, const TileArgs& I, uint64_t ntiles, hipStream_t s);
-static bool flag_rounds_fit(const ggarray* a, uint64_t ntiles, hipStream_t s);
+static int queue_counts_rounds(ggarray* a, const InsertDesc& d, const TileArgs& I, uint64_t ntiles, hipStream_t s);
+
+// Words of a flagged round in two passes: the masks, then a word per tile.  (A round
+// of counts: a word per tile.)
+static uint64_t flag_round_words(uint64_t ntiles) { return ntiles * 64 + ntiles; }
+
+// Whether a two-pass form can run: its buffer is large enough or can be grown (not
+// while the stream is capturing; a captured round then takes the one-launch form).
+static bool two_pass_fits(const ggarray* a, uint64_t words, hipStream_t s) {
+  return words <= a->pk_cap || !stream_capturing(s);
+}
 
 // Rounds ds[0..n) of one generated producer, each followed by the shrink
 // sh_num / sh_den (0: none).  One launch when every round is dense (round-tag or
@@ -2354,8 +2456,9 @@ int launch_insert(ggarray* a, const InsertDesc& d, hipStream_t s, uint32_t sh_nu
     return st;
   }
 
-  if (d.mode == kModeBuffer && d.flags && tpv > 1 && flag_rounds_fit(a, ntiles, s)) {
-    int st = queue_flag_rounds(a, d, I, ntiles, s);
+  if (tpv > 1 && ((d.mode == kModeBuffer && d.flags && two_pass_fits(a, flag_round_words(ntiles), s)) ||
+                  (d.mode == kModeCounts && ntiles > kCountsOneLaunch && two_pass_fits(a, ntiles, s)))) {
+    int st = d.mode == kModeBuffer ? queue_flag_rounds(a, d, I, ntiles, s) : queue_counts_rounds(a, d, I, ntiles, s);
     if (sh_den && st == GGA_OK) st = launch_shrink(a, sh_num, sh_den, s);
     return st;
   }
@@ -2473,14 +2576,11 @@ static int queue_packed(ggarray* a, uint64_t* off, const void* values, const uin
   return hip_status(e);
 }
 
-// Words of a flagged round in two passes: the masks, then a word per tile.
-static uint64_t flag_round_words(uint64_t ntiles) { return ntiles * 64 + ntiles; }
-
-// Whether the two-pass form can run: its buffer is large enough or can be grown
-// (not while the stream is capturing; a captured round then takes the one-launch
-// form).
-static bool flag_rounds_fit(const ggarray* a, uint64_t ntiles, hipStream_t s) {
-  return flag_round_words(ntiles) <= a->pk_cap || !stream_capturing(s);
+static void queue_flag_grow(const ArrRef& A, const TileArgs& I, uint64_t* tiles, hipStream_t s) {
+  if (I.tpv <= kGrowWaveTiles)
+    hipLaunchKernelGGL(flag_grow_kernel, dim3((A.V + 3) / 4), dim3(256), 0, s, A, I, tiles);
+  else
+    hipLaunchKernelGGL(flag_grow_long_kernel, dim3(A.V), dim3(1024), 0, s, A, I, tiles);
 }
 
 // A buffer round with flags over LFVectors of several tiles: masks and tile
@@ -2491,10 +2591,7 @@ static void queue_flag_kernels(const ArrRef& A, const InsertDesc& d, const TileA
   uint64_t* tiles = masks + ntiles * 64;
   hipLaunchKernelGGL(flag_mask_kernel<16 / sizeof(T)>, dim3((uint32_t)((ntiles + kW - 1) / kW)), dim3(kB), 0, s, I,
                      d.flags, masks, tiles, ntiles);
-  if (I.tpv <= kGrowWaveTiles)
-    hipLaunchKernelGGL(flag_grow_kernel, dim3((A.V + 3) / 4), dim3(256), 0, s, A, I, tiles);
-  else
-    hipLaunchKernelGGL(flag_grow_long_kernel, dim3(A.V), dim3(1024), 0, s, A, I, tiles);
+  queue_flag_grow(A, I, tiles, s);
   hipLaunchKernelGGL(flag_copy_kernel<T>, dim3((uint32_t)ntiles), dim3(64), 0, s, A, I,
                      static_cast<const T*>(d.values), masks, tiles);
 }
@@ -2506,6 +2603,30 @@ static int queue_flag_rounds(ggarray* a, const InsertDesc& d, const TileArgs& I,
     queue_flag_kernels<uint32_t>(a->ref, d, I, a->pk_off, ntiles, s);
   else
     queue_flag_kernels<uint64_t>(a->ref, d, I, a->pk_off, ntiles, s);
+  const hipError_t e = hipGetLastError();
+  if (e == hipSuccess) sizes_changed(a, s);
+  return hip_status(e);
+}
+
+// A round of padded counts over LFVectors of several tiles: tile sums, offsets and
+// growth of every LFVector, then the copy.
+template <typename T>
+static void queue_counts_kernels(const ArrRef& A, const InsertDesc& d, const TileArgs& I, uint64_t* tiles,
+                                 uint64_t ntiles, hipStream_t s) {
+  hipLaunchKernelGGL(counts_sum_kernel, dim3((uint32_t)((ntiles + kW - 1) / kW)), dim3(kB), 0, s, I, d.flags,
+                     d.max_count, tiles, ntiles);
+  queue_flag_grow(A, I, tiles, s);
+  hipLaunchKernelGGL(counts_copy_kernel<T>, dim3((uint32_t)ntiles), dim3(kB), 0, s, A, I,
+                     ProdCounts<T>{static_cast<const T*>(d.values), d.flags, d.max_count}, tiles);
+}
+
+static int queue_counts_rounds(ggarray* a, const InsertDesc& d, const TileArgs& I, uint64_t ntiles, hipStream_t s) {
+  const int rc = ensure_packed_offsets(a, ntiles, s);
+  if (rc) return rc;
+  if (a->elem_bytes == 4)
+    queue_counts_kernels<uint32_t>(a->ref, d, I, a->pk_off, ntiles, s);
+  else
+    queue_counts_kernels<uint64_t>(a->ref, d, I, a->pk_off, ntiles, s);
   const hipError_t e = hipGetLastError();
   if (e == hipSuccess) sizes_changed(a, s);
   return hip_status(e);
