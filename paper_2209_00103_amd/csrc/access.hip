@@ -194,10 +194,10 @@ constexpr uint32_t kVecPerBlock = 4;  // one wave per LFVector: 256 threads = 4 
 // kLanes lanes per LFVector.  A clear is a chain of dependent atomics per bucket.
 // While a wave per LFVector fits the chip's 8192 wave slots it is the shortest; a
 // few thousand LFVectors more come in turns, and four of them share a wave (V =
-// 8192, 13 buckets: 19.6 -> 16.6 us; V = 16384, 2 buckets: 24.1 -> 21.8 us).  From
-// 32768 on, the LFVectors that share a free list (every 4096th) would then be in
-// flight together and retry each other's swaps, so a wave each it is again (V =
-// 65536, 2 and 4 buckets: 48 and 59 us, against 52 and 89 us).
+// 8192, 13 buckets: 19.6 -> 16.6 us).  Arrays of 16384 LFVectors and more release
+// chains (below); of such a batch, whose arrays' lists differ, LFVectors of one list
+// would be in flight together from 32768 on and retry each other's swaps, so a wave
+// each it is again (V = 65536, 4 buckets: 59 us, against 89 us).
 inline bool shrink_shares_wave(uint64_t V) { return V >= 4096 && V < 32768; }
 template <uint32_t kLanes>
 __global__ __launch_bounds__(256) void shrink_kernel(ArrRef A, uint32_t num, uint32_t den,
@@ -205,6 +205,109 @@ __global__ __launch_bounds__(256) void shrink_kernel(ArrRef A, uint32_t num, uin
   const uint32_t v = (blockIdx.x * 256 + threadIdx.x) / kLanes;
   if (v < A.V) shrink_vector<kLanes>(A, v, num, den, elem_log2);
 }
+
+// The shrink of many LFVectors (more than the pool has free lists per class).  Every
+// 4096th LFVector's bucket b goes to the same free list, so 16 lanes take residue r:
+// lane l links bucket l (then l + 16, ...) of LFVectors r, r + 4096, ..., 16 at a
+// time, into one chain and pushes it with one swap of the list's head.  One swap per
+// bucket makes the LFVectors of a list wait for each other (V = 65536, 2 and 4
+// buckets, a wave per LFVector: 47 and 57 us; 24 and 31 us this way).  What is left
+// is the serial chain: sizes, pointers, links, swap, each one trip to memory.  With
+// fewer LFVectors there is little to link (V = 16384, 2 buckets: 21.8 us with 16 lanes
+// per LFVector, 16.0 us this way; V = 8192, 6 buckets: 18.2 us either way).
+constexpr uint32_t kChainLanes = 16;
+constexpr uint64_t kChainStep = (uint64_t)kFreeShards * kChainLanes;
+
+__device__ __forceinline__ uint64_t exchange_link(uint8_t* block, uint64_t next) {
+  return __hip_atomic_exchange(gmem(reinterpret_cast<uint64_t*>(block)), next, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Buckets [lo, hi) of LFVector v are to go, as lo << 8 | hi (0: none).
+__device__ __forceinline__ uint32_t shrink_range(const ArrRef& A, uint64_t v, uint32_t num, uint32_t den) {
+  const bool in = v < A.V;
+  uint32_t dead = A.dead[in ? v : 0];
+  uint64_t s = A.size[in ? v : 0];
+  asm volatile("" : "+v"(dead), "+v"(s));  // both loads in flight before either is looked at
+  const uint32_t hi = dead ? (uint32_t)kMaxBuckets : nbuckets_for(A.log2F, s);
+  const uint32_t lo = nbuckets_for(A.log2F, shrink_keep(s, num, den));
+  return in ? lo << 8 | (hi < (uint32_t)kMaxBuckets ? hi : (uint32_t)kMaxBuckets) : 0;
+}
+
+__global__ __launch_bounds__(256) void shrink_chain_kernel(ArrRef A, uint32_t num, uint32_t den, uint32_t elem_log2) {
+  const uint32_t l = threadIdx.x & (kChainLanes - 1);
+  const uint64_t r = ((uint64_t)blockIdx.x * 256 + threadIdx.x) / kChainLanes;
+  if (r >= (uint64_t)kFreeShards || r >= A.V) return;
+  PoolHdr* H = A.pool.hdr;
+  uint32_t range = 0, most = 0;  // most: buckets of the residue's longest LFVector
+  for (uint64_t v0 = r; v0 < A.V; v0 += kChainStep) {
+    range = shrink_range(A, v0 + (uint64_t)l * kFreeShards, num, den);
+    most = (range & 255u) > most ? range & 255u : most;
+  }
+#pragma unroll
+  for (uint32_t d = 1; d < kChainLanes; d <<= 1) {
+    const uint32_t o = (uint32_t)__shfl_xor((int)most, (int)d, (int)kChainLanes);
+    most = o > most ? o : most;
+  }
+  for (uint32_t b0 = 0; b0 < most; b0 += kChainLanes) {
+    const uint32_t b = b0 + l;
+    uint64_t* const row = A.bptr + (b < (uint32_t)kMaxBuckets ? b : 0);
+    uint64_t first = 0;  // index word of the chain's top block
+    uint32_t n = 0;
+    uint8_t* last = nullptr;
+    for (uint64_t v0 = r; v0 < A.V; v0 += kChainStep) {
+      if (A.V > kChainStep) range = shrink_range(A, v0 + (uint64_t)l * kFreeShards, num, den);
+      uint64_t p[kChainLanes];
+#pragma unroll
+      for (uint32_t u = 0; u < kChainLanes; ++u) {
+        const uint64_t v = v0 + u * kFreeShards;
+        p[u] = row[(v < A.V ? v : r) * kMaxBuckets];
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < kChainLanes; ++u) {
+        asm volatile("" : "+v"(p[u]));  // all of them in flight before the first is looked at
+        const uint32_t g = (uint32_t)__shfl((int)range, (int)u, (int)kChainLanes);
+        if (b < (g >> 8) || b >= (g & 255u)) p[u] = 0;
+      }
+      uint64_t landed[kChainLanes];  // what the links' exchanges returned
+#pragma unroll
+      for (uint32_t u = 0; u < kChainLanes; ++u) {
+        landed[u] = 0;
+        if (p[u] == 0) continue;
+        row[(v0 + u * kFreeShards) * kMaxBuckets] = 0;
+        if (p[u] <= kFailedPtr) continue;
+        uint8_t* const block = reinterpret_cast<uint8_t*>(p[u]);
+        const uint64_t idx = ((uint64_t)(block - A.pool.base) >> kMinClassLog2) + 1;
+        if (n)
+          landed[u] = exchange_link(last, idx);
+        else
+          first = idx;
+        last = block;
+        ++n;
+      }
+      // Consuming the results makes the wave wait until every link has landed before
+      // the swap below can publish the chain.
+#pragma unroll
+      for (uint32_t u = 0; u < kChainLanes; ++u) asm volatile("" ::"v"(landed[u]) : "memory");
+    }
+    if (n == 0) continue;
+    const uint32_t cls = bucket_class(A.log2F, elem_log2, b), f = pool_shard((uint32_t)r, b, A.salt);
+    uint64_t* const head = &H->heads[(uint64_t)cls * kFreeShards + f];
+    uint64_t h = ld_rlx(head);
+    for (;;) {
+      asm volatile("" ::"v"(exchange_link(last, h & kIdxMask)) : "memory");
+      if (cas_rlx(head, h, (((h >> 40) + 1) << 40) | first)) break;
+    }
+    if ((h & kIdxMask) == 0)
+      __hip_atomic_fetch_or(&H->nonempty[cls][f >> 6], 1ull << (f & 63), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    sub_nr(&free_stat(H)->in_use, (uint64_t)n << cls);
+    add_nr(&free_stat(H)->n_free, (uint64_t)n);
+  }
+  // Every lane of the residue has read the old sizes: one wave, program order.
+  for (uint64_t v = r + (uint64_t)l * kFreeShards; v < A.V; v += kChainStep)
+    A.size[v] = shrink_keep(A.size[v], num, den);
+}
+constexpr uint64_t kChainMinV = 16384;
 
 // Returns every bucket of the array to the pool (destroy).
 __global__ __launch_bounds__(256) void free_all_kernel(ArrRef A, uint32_t elem_log2) {
@@ -875,7 +978,10 @@ int launch_report(ggarray* a, const uint64_t* word, uint64_t* host, hipStream_t 
 
 int launch_shrink(ggarray* a, uint32_t num, uint32_t den, hipStream_t s) {
   if (num == den) a->size_ub = 0;
-  if (shrink_shares_wave(a->V))
+  if (a->V >= kChainMinV)
+    hipLaunchKernelGGL(shrink_chain_kernel, dim3(kFreeShards * kChainLanes / 256), dim3(256), 0, s, a->ref, num, den,
+                       a->elem_log2);
+  else if (shrink_shares_wave(a->V))
     hipLaunchKernelGGL(shrink_kernel<16>, dim3((a->V + 15) / 16), dim3(256), 0, s, a->ref, num, den, a->elem_log2);
   else
     hipLaunchKernelGGL(shrink_kernel<64>, dim3((a->V + 3) / 4), dim3(256), 0, s, a->ref, num, den, a->elem_log2);

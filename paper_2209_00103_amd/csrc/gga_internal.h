@@ -286,6 +286,7 @@ __device__ __forceinline__ void store_nt_sc1(gptr<u32x4> p, u32x4 x) {
 // Elements an LFVector of s elements keeps when a shrink pops floor(s num / den)
 // of them (num <= den; the product is split so that it cannot overflow).
 __host__ __device__ __forceinline__ uint64_t shrink_keep(uint64_t s, uint32_t num, uint32_t den) {
+  if (num == den) return 0;  // a clear: no divisions (64-bit ones, some 150 instructions each)
   return s - ((s / den) * num + ((s % den) * num) / den);
 }
 

@@ -1,6 +1,6 @@
 """Clears and partial shrinks at the edges of the release kernel's forms (a wave per
-LFVector below 4096 LFVectors and from 32768 on, 16 lanes each between), single array
-and batch, with more buckets than a group has lanes; sizes, contents, capacity and the
+LFVector below 4096 LFVectors, 16 lanes each up to 16383, from there on one chain per
+free list; batches: 16 lanes from 4096 to 32767), single array and batch, with more buckets than a group has lanes; sizes, contents, capacity and the
 pool's counts against the CPU oracle."""
 import numpy as np
 import pytest
@@ -32,6 +32,35 @@ def test_shrink_group_edges(elem, V, F, n):
     a.close()
     st = pool.stats()
     assert st["in_use"] == 0 and st["allocs"] == st["frees"]
+    pool.close()
+
+
+@pytest.mark.parametrize("elem,V,F", [(4, 16383, 2), (4, 16384, 1), (8, 40001, 2), (4, 70001, 1)])
+def test_shrink_chains_uneven(elem, V, F):
+    """Uneven LFVectors (empty ones, one of 17 or more buckets), partial shrinks and clears;
+    the next rounds take the released blocks again."""
+    rng = np.random.default_rng(V + elem)
+    G = gg()
+    pool = G.Pool(1 << 30)
+    a, o = both(elem, V, F, pool)
+    a2, o2 = both(elem, V, F, pool)
+    dt = np.uint32 if elem == 4 else np.uint64
+    for k, (num, den) in enumerate(((1, 3), (1, 1), (2, 3), (1, 1))):
+        for g, q in ((a, o), (a2, o2)):
+            n = rng.integers(0, 9, V) * (rng.random(V) < 0.8)
+            n[(k * 7919) % V] += 200_000
+            pre = np.concatenate([[0], np.cumsum(n)]).astype(np.uint64)
+            vals = rng.integers(0, 1 << 31, int(pre[-1])).astype(dt)
+            g.insert_segments(dev(vals), dev(pre))
+            q.insert_segments(vals, pre)
+        for g, q in ((a, o), (a2, o2)):
+            g.shrink(num, den)
+            q.shrink(num, den)
+            assert_same(g, q, f"shrink {num}/{den}")
+    st = pool.stats()
+    assert st["in_use"] == 0 and st["allocs"] == st["frees"]
+    a.close()
+    a2.close()
     pool.close()
 
 
