@@ -2335,9 +2335,10 @@ int ensure_status(ggarray* a, uint64_t ntiles, hipStream_t s) {
 static int queue_flag_rounds(ggarray* a, const InsertDesc& d, const TileArgs& I, uint64_t ntiles, hipStream_t s);
 static int queue_counts_rounds(ggarray* a, const InsertDesc& d, const TileArgs& I, uint64_t ntiles, hipStream_t s);
 
-// Words of a flagged round in two passes: the masks, then a word per tile.  (A round
-// of counts: a word per tile.)
-static uint64_t flag_round_words(uint64_t ntiles) { return ntiles * 64 + ntiles; }
+// Words of a flagged round in two passes: the masks, then a word per tile; never fewer
+// than a packed round of as many tiles, so that one runs in a graph after the other.
+// (A round of counts: a word per tile.)
+static uint64_t flag_round_words(uint64_t ntiles) { return ntiles * 64 + ntiles + packed_groups(ntiles) + 1; }
 
 // Whether a two-pass form can run: its buffer is large enough or can be grown (not
 // while the stream is capturing; a captured round then takes the one-launch form).
@@ -2456,15 +2457,19 @@ int launch_insert(ggarray* a, const InsertDesc& d, hipStream_t s, uint32_t sh_nu
     return st;
   }
 
-  if (tpv > 1 && ((d.mode == kModeBuffer && d.flags && two_pass_fits(a, flag_round_words(ntiles), s)) ||
-                  (d.mode == kModeCounts && ntiles > kCountsOneLaunch && two_pass_fits(a, ntiles, s)))) {
+  const bool flag_passes =
+      tpv > 1 && d.mode == kModeBuffer && d.flags && two_pass_fits(a, flag_round_words(ntiles), s);
+  // A round of counts in two passes uses no look-back words, but a smaller one or a
+  // generated one that is captured later does, and relies on them being there.
+  if (tpv > 1 && !flag_passes) {
+    const int rc = ensure_status(a, ntiles, s);
+    if (rc) return rc;
+  }
+  if (flag_passes ||
+      (tpv > 1 && d.mode == kModeCounts && ntiles > kCountsOneLaunch && two_pass_fits(a, ntiles, s))) {
     int st = d.mode == kModeBuffer ? queue_flag_rounds(a, d, I, ntiles, s) : queue_counts_rounds(a, d, I, ntiles, s);
     if (sh_den && st == GGA_OK) st = launch_shrink(a, sh_num, sh_den, s);
     return st;
-  }
-  if (tpv > 1) {
-    const int rc = ensure_status(a, ntiles, s);
-    if (rc) return rc;
   }
   StaticRef S{};
   int st = a->elem_bytes == 4 ? dispatch<uint32_t, false>(a->ref, S, I, d, ntiles, s)

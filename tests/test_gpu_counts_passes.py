@@ -55,3 +55,41 @@ def test_counts_passes_failed_growth_freezes_one_lfvector():
     pool.set_fault(0)
     assert pool.stats()["in_use"] == 0
     pool.close()
+
+
+def test_smaller_counts_and_generated_rounds_in_a_graph_after_one_in_two_passes():
+    """Only the eager two-pass round came before: the captured rounds' look-back words are there."""
+    import torch
+
+    import oracle
+
+    G = gg()
+    rng = np.random.default_rng(9)
+    pool = G.Pool(1 << 30)
+    V, mc = 300, 2
+    a, o = both(4, V, 64, pool)
+    big, small = V * 8 * TILE, V * 3 * TILE - 11
+    vals, _ = wl.random_round(rng, big * mc, 1.0, 4)
+    counts = rng.integers(0, mc + 1, size=big, dtype=np.uint8)
+    dv, dc = dev(vals), dev(counts)
+    a.insert_counts(dv, dc, mc)
+    o.insert_counts(vals, counts, mc)
+    gen = G.make_gen(G.GEN_BERNOULLI, seed=5, round=1)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        a.insert_counts(dv[:small * mc], dc[:small], mc)
+        a.insert_gen(gen, big)
+        a.insert_counts(dv, dc, mc)
+        a.shrink(3, 4)
+    for k in range(3):
+        graph.replay()
+        o.insert_counts(vals[:small * mc], counts[:small], mc)
+        o.insert_gen(oracle.GEN_BERNOULLI, big, seed=5, round=1)
+        o.insert_counts(vals, counts, mc)
+        o.shrink(3, 4)
+        assert_same(a, o, f"replay {k}")
+    a.close()
+    o.close()
+    pool.close()
