@@ -464,11 +464,13 @@ int launch_batch_stream(gga_batch* b, uint32_t op, void* out, uint64_t cap, bool
 // uses them) and returns its tiles.
 int prepare_round_item(ggarray* a, uint64_t n, uint64_t tag, uint32_t index, BatchArr* item, uint64_t* ntiles,
                        hipStream_t s, bool lookback);
-// launch_serve_front: the step's append rounds (keyed payloads) and the size
-// scans of the n_s arrays in sitems, one launch.  launch_serve_stream: the r/w
+// launch_serve_front: the step's append rounds (keyed payloads; item i has blocks
+// [begins[i], begins[i + 1]), serve_blocks of them) and the size scans of the n_s
+// arrays in sitems, one launch.  launch_serve_stream: the r/w
 // and flatten requests of sitems (scanned before), one streaming launch (plus one
 // prefix launch when n_s exceeds kServeFusedItems).
 constexpr uint32_t kServeFusedItems = 4096;
+uint64_t serve_blocks(const BatchArr& it, uint64_t ntiles);
 int launch_serve_front(const BatchArr* items, const uint64_t* begins, uint32_t n_a, uint64_t blocks,
                        const ServeItem* sitems, uint32_t n_s, uint32_t elem_bytes, uint64_t seed, uint32_t round,
                        uint32_t shift, hipStream_t s);

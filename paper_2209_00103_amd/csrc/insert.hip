@@ -780,21 +780,6 @@ __global__ __launch_bounds__(64) void batch_insert_kernel(const BatchArr* items,
   batch_wave<T, Prod>(items, begins, n, prod, blockIdx.x);
 }
 
-// Front half of a served step in one launch: waves [0, blocks) run the step's
-// append rounds exactly as batch_insert_kernel; the next waves, one per array,
-// scan the sizes of the arrays that the step's r/w and flatten requests read.
-template <typename T>
-__global__ __launch_bounds__(64) void serve_front_kernel(const BatchArr* items, const uint64_t* begins, uint32_t n_a,
-                                                         uint64_t blocks, const ServeItem* sitems, uint32_t te_log2,
-                                                         ProdKeyed<T> prod) {
-  const uint64_t blk = blockIdx.x;
-  if (blk >= blocks) {
-    scan_array_wave(sitems[blk - blocks].A, te_log2);
-    return;
-  }
-  batch_wave<T, ProdKeyed<T>>(items, begins, n_a, prod, blk);
-}
-
 // ------------------------------------------ dense rounds: grow, then store --
 // When every logical thread of a round inserts exactly one element, LFVector v
 // receives exactly the threads of its chunk, so its growth is known before any
@@ -1041,10 +1026,10 @@ constexpr uint32_t kSpanBytes = 4096;  // one round of dense_store's loads (64 l
 // is the bytes in flight: a single wave per LFVector (the generated rounds' form,
 // which only stores) waits for memory once per 4 KiB (V = 512, 2.0e7 u32 elements:
 // 44 us a round as one wave each, 3.6 TB/s; 28 us, 5.7 TB/s, in this form).
-template <typename T, uint32_t W>
-__device__ __forceinline__ void grow_store_block(const ArrRef& A, uint32_t elem_log2, const T* values, uint32_t v,
+template <typename T, uint32_t W, uint32_t kPiece = kSpanBytes, class Prod>
+__device__ __forceinline__ void grow_store_block(const ArrRef& A, uint32_t elem_log2, const Prod& prod, uint32_t v,
                                                  uint64_t c0, uint64_t cnt) {
-  constexpr uint64_t kSpan = kSpanBytes / sizeof(T), kLine = 128 / sizeof(T);
+  constexpr uint64_t kSpan = kPiece / sizeof(T), kLine = 128 / sizeof(T);
   __shared__ uint64_t s_bp[kMaxBuckets];
   __shared__ uint32_t s_fail;
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
@@ -1080,7 +1065,7 @@ __device__ __forceinline__ void grow_store_block(const ArrRef& A, uint32_t elem_
   if (s_fail) return;
   for (uint64_t a = (s0 & ~(kLine - 1)) + (tid >> 6) * kSpan; a < s1; a += W * kSpan) {
     const uint64_t i0 = a < s0 ? s0 : a, i1 = a + kSpan < s1 ? a + kSpan : s1;
-    store_span<T>(A, ProdBuffer<T>{values, nullptr}, i0, i1, c0 + (i0 - s0), [](uint32_t b) { return s_bp[b]; });
+    store_span<T>(A, prod, i0, i1, c0 + (i0 - s0), [](uint32_t b) { return s_bp[b]; });
   }
 }
 
@@ -1090,7 +1075,51 @@ __global__ __launch_bounds__(64 * W) void grow_store_block_kernel(ArrRef A, Tile
   const uint32_t v = blockIdx.x;
   const uint64_t c0 = (uint64_t)v * I.chunk;
   const uint64_t cnt = c0 < I.n_threads ? (I.n_threads - c0 < I.chunk ? I.n_threads - c0 : I.chunk) : 0;
-  grow_store_block<T, W>(A, I.elem_log2, values, v, c0, cnt);
+  grow_store_block<T, W>(A, I.elem_log2, ProdBuffer<T>{values, nullptr}, v, c0, cnt);
+}
+
+constexpr uint32_t kServeWaves = 8;
+// Front half of a served step in one launch, in workgroups of kServeWaves waves.  An
+// append of at most 8 tiles per LFVector to at most 64 LFVectors has a workgroup per
+// LFVector that allocates and stores (pieces of 1 KiB: the payloads are hashed, not
+// read); a larger one has a wave per tile, as in batch_insert_kernel.  The last waves, one per array, scan the
+// sizes of the arrays that the step's r/w and flatten requests read.  Some hundred
+// LFVectors leave the chip nearly empty, so the launch takes as long as its longest
+// serial chain (steps of some 90 appends of 1024 elements and 60 scans: 18.4 us as a
+// wave per tile with tickets, 9.3 us this way; 10.1 us with 4 waves, 9.0 with 16).
+inline __host__ __device__ bool serve_block_form(uint64_t tpv, uint32_t V) { return tpv <= 8 && V <= 64; }
+template <typename T>
+__global__ __launch_bounds__(64 * kServeWaves) void serve_front_kernel(const BatchArr* items, const uint64_t* begins,
+                                                                       uint32_t n_a, uint64_t blocks,
+                                                                       const ServeItem* sitems, uint32_t n_s,
+                                                                       uint32_t te_log2, ProdKeyed<T> prod) {
+  const uint64_t blk = blockIdx.x;
+  const uint32_t wave = threadIdx.x >> 6;
+  if (blk >= blocks) {
+    const uint64_t k = (blk - blocks) * kServeWaves + wave;
+    if (k < n_s) scan_array_wave(sitems[k].A, te_log2);
+    return;
+  }
+  const uint32_t i = wave_search(begins, n_a, blk);
+  const BatchArr it = items[i];
+  ProdKeyed<T> p = prod;
+  p.bind(it);
+  if (serve_block_form(it.tpv, it.A.V)) {
+    const uint32_t v = (uint32_t)(blk - begins[i]);
+    const uint64_t c0 = (uint64_t)v * it.chunk;
+    const uint64_t cnt =
+        c0 < it.n_threads ? (it.n_threads - c0 < it.chunk ? it.n_threads - c0 : it.chunk) : 0;
+    grow_store_block<T, kServeWaves, 1024>(it.A, it.elem_log2, p, v, c0, cnt);
+    return;
+  }
+  const uint64_t tile = (blk - begins[i]) * kServeWaves + wave;
+  if (tile >= it.tpv * it.A.V) return;
+  TileArgs I;
+  I.n_threads = it.n_threads;
+  I.chunk = it.chunk;
+  I.tpv = it.tpv;
+  I.elem_log2 = it.elem_log2;
+  wave_tile<T, ProdKeyed<T>, false>(it.A, StaticRef{}, I, p, tile);
 }
 
 // Segment append: LFVector v appends values[prefix[v] .. prefix[v + 1]).  A
@@ -1129,7 +1158,7 @@ __global__ __launch_bounds__(64 * W) void segments_block_kernel(ArrRef A, TileAr
     if (threadIdx.x == 0) set_error(A.err, kErrRange);
     return;
   }
-  grow_store_block<T, W>(A, I.elem_log2, values, v, lo, cnt);
+  grow_store_block<T, W>(A, I.elem_log2, ProdBuffer<T>{values, nullptr}, v, lo, cnt);
 }
 
 // The longest: one wave per LFVector grows it, then `parts` workgroups per
@@ -2792,9 +2821,6 @@ int launch_static_insert(gga_static* st, const InsertDesc& d, hipStream_t s) {
 }
 
 
-namespace {
-}  // namespace
-
 int prepare_round_item(ggarray* a, uint64_t n, uint64_t tag, uint32_t index, BatchArr* item, uint64_t* ntiles,
                        hipStream_t s, bool lookback) {
   const uint64_t chunk = n ? (n + a->V - 1) / a->V : 0;
@@ -2809,20 +2835,25 @@ int prepare_round_item(ggarray* a, uint64_t n, uint64_t tag, uint32_t index, Bat
   return GGA_OK;
 }
 
+// Workgroups of one append in launch_serve_front.
+uint64_t serve_blocks(const BatchArr& it, uint64_t ntiles) {
+  return serve_block_form(it.tpv, it.A.V) ? it.A.V : (ntiles + kServeWaves - 1) / kServeWaves;
+}
+
 int launch_serve_front(const BatchArr* items, const uint64_t* begins, uint32_t n_a, uint64_t blocks,
                        const ServeItem* sitems, uint32_t n_s, uint32_t elem_bytes, uint64_t seed, uint32_t round,
                        uint32_t shift, hipStream_t s) {
-  const uint64_t waves = blocks + n_s;
-  if (!waves) return GGA_OK;
-  if (waves > 0x7FFFFFFFull) return GGA_EINVAL;
+  const uint64_t wgs = blocks + (n_s + kServeWaves - 1) / kServeWaves;
+  if (!wgs) return GGA_OK;
+  if (wgs > 0x7FFFFFFFull) return GGA_EINVAL;
   const uint32_t te_log2 = elem_bytes == 4 ? 12u : 11u;
-  const dim3 grid((uint32_t)waves), block(64);
+  const dim3 grid((uint32_t)wgs), block(64 * kServeWaves);
   if (elem_bytes == 4)
-    hipLaunchKernelGGL(serve_front_kernel<uint32_t>, grid, block, 0, s, items, begins, n_a, blocks, sitems, te_log2,
-                       ProdKeyed<uint32_t>{seed, round, shift, 0});
+    hipLaunchKernelGGL(serve_front_kernel<uint32_t>, grid, block, 0, s, items, begins, n_a, blocks, sitems, n_s,
+                       te_log2, ProdKeyed<uint32_t>{seed, round, shift, 0});
   else
-    hipLaunchKernelGGL(serve_front_kernel<uint64_t>, grid, block, 0, s, items, begins, n_a, blocks, sitems, te_log2,
-                       ProdKeyed<uint64_t>{seed, round, shift, 0});
+    hipLaunchKernelGGL(serve_front_kernel<uint64_t>, grid, block, 0, s, items, begins, n_a, blocks, sitems, n_s,
+                       te_log2, ProdKeyed<uint64_t>{seed, round, shift, 0});
   return hip_status(hipGetLastError());
 }
 

@@ -387,7 +387,7 @@ int run_batched(RunState& R) {
           if (rc) return rc;
           items.push_back(it);
           begins.push_back(blocks);
-          blocks += ntiles;
+          blocks += serve_blocks(it, ntiles);
           sizes_changed(arr, l.s);
           grow_bound(arr, tr->length[r]);
         } else {
