@@ -152,20 +152,19 @@ int ggarray_destroy(ggarray *a, gga_stream s);
  *   are allocated on the device.  Pool exhaustion leaves every affected LFVector
  *   exactly as it was before the round, freezes it for later insertions and sets
  *   the sticky GGA_ENOMEM.  With flags, a round that gives an LFVector more than
- *   one tile of 4096 threads runs as a few launches (flag masks and tile counts,
- *   their prefix, growth, copy) in a per-array buffer of about 0.13 bytes per
- *   thread, grown when needed (under graph capture, where it cannot grow, the
- *   round runs as one launch with a per-LFVector look-back instead).  Those
- *   launches read 16-byte payload vectors when values is 16-byte aligned, flags
- *   is aligned to E = 16 / element bytes, and n_threads and every LFVector's
- *   share ceil(n_threads / V) are multiples of E; any other input gives the same
- *   result through one-element loads. */
+ *   one tile of 4096 threads runs as three launches (flag masks and tile counts,
+ *   their prefix per LFVector and its growth, copy) in a per-array buffer of about
+ *   0.13 bytes per thread, grown when needed (under graph capture, where it cannot
+ *   grow, the round runs as one launch with a per-LFVector look-back instead). */
 int ggarray_insert(ggarray *a, const void *values, const uint8_t *flags, uint64_t n_threads,
                    gga_stream s);
 
 /* ggarray_insert_counts: as ggarray_insert, but thread gid inserts
  *   values[gid * max_count + j] for j < counts[gid]; 1 <= max_count <= 16 and
- *   counts[gid] <= max_count (larger counts are clamped to max_count). */
+ *   counts[gid] <= max_count (larger counts are clamped to max_count).  A round of
+ *   more than 2048 tiles of 1024 threads that gives an LFVector several of them
+ *   runs as three launches too (tile sums, prefix and growth, copy), with one word
+ *   per tile in the same per-array buffer. */
 int ggarray_insert_counts(ggarray *a, const void *values, const uint8_t *counts,
                           uint32_t max_count, uint64_t n_threads, gga_stream s);
 
@@ -307,8 +306,8 @@ int ggarray_prefix(ggarray *a, uint64_t *dev_out, gga_stream s);
 
 /* ggarray_kernel_timing: a measurement aid.  With on != 0 the array's r/w and
  *   flatten kernels, and its insertion rounds that run as one launch (rounds of
- *   round-tag or keyed payloads, or of a buffer without flags, with one wave per
- *   LFVector), when not captured in a graph, are dispatched with a pair of HIP
+ *   round-tag or keyed payloads, or of a buffer without flags, with one wave or
+ *   workgroup per LFVector), when not captured in a graph, are dispatched with a pair of HIP
  *   events that the dispatch itself records at the kernel's start and end (the
  *   library creates and owns them; on == 0 destroys them).
  * ggarray_kernel_ms: the duration in milliseconds of the array's last timed r/w

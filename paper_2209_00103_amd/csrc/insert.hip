@@ -1082,11 +1082,12 @@ constexpr uint32_t kServeWaves = 8;
 // Front half of a served step in one launch, in workgroups of kServeWaves waves.  An
 // append of at most 8 tiles per LFVector to at most 64 LFVectors has a workgroup per
 // LFVector that allocates and stores (pieces of 1 KiB: the payloads are hashed, not
-// read); a larger one has a wave per tile, as in batch_insert_kernel.  The last waves, one per array, scan the
-// sizes of the arrays that the step's r/w and flatten requests read.  Some hundred
-// LFVectors leave the chip nearly empty, so the launch takes as long as its longest
-// serial chain (steps of some 90 appends of 1024 elements and 60 scans: 18.4 us as a
-// wave per tile with tickets, 9.3 us this way; 10.1 us with 4 waves, 9.0 with 16).
+// read); a larger one has a wave per tile, as in batch_insert_kernel.  The last waves,
+// one per array, scan the sizes of the arrays that the step's r/w and flatten requests
+// read.  Some hundred LFVectors leave the chip nearly empty, so the launch takes as
+// long as its longest serial chain (steps of some 90 appends of 1024 elements and 60
+// scans: 18.4 us as a wave per tile with tickets, 9.3 us this way; 10.1 us with 4
+// waves, 9.0 with 16).
 inline __host__ __device__ bool serve_block_form(uint64_t tpv, uint32_t V) { return tpv <= 8 && V <= 64; }
 template <typename T>
 __global__ __launch_bounds__(64 * kServeWaves) void serve_front_kernel(const BatchArr* items, const uint64_t* begins,
