@@ -517,13 +517,17 @@ __device__ __forceinline__ void stream_range(const ArrRef& A, uint64_t t0, uint6
 // Tile table of one array, built once per state of the sizes (after the prefix
 // scan): tile t, in the order of the tile prefix, gets the address of its first
 // element and its destination offset in a flatten, with its element count in the
-// top 16 bits.  One wave per LFVector, lanes over the tiles of each bucket.
+// top 16 bits.  kLanes lanes per LFVector, over the tiles of each bucket; they read the
+// bucket table's first kLanes entries at once, beside the size and the prefixes.
 // Entries from `cap` on are not written; the streaming kernels then walk the
 // buckets instead.
 // LFVector v of s elements; its first tile is t, its first element's place pv.
+template <uint32_t kLanes>
 __device__ __forceinline__ void vector_tiles(const ArrRef& A, uint32_t v, uint64_t s, uint64_t* tab, uint64_t cap,
                                              uint32_t te_log2, uint32_t elem_log2, uint64_t t, uint64_t pv) {
-  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t lane = threadIdx.x & (kLanes - 1);
+  const uint64_t* row = A.bptr + (uint64_t)v * kMaxBuckets;
+  const uint64_t mine = row[lane < (uint32_t)kMaxBuckets ? lane : 0];
   const uint32_t log2F = A.log2F;
   const uint64_t te = 1ull << te_log2;
   typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
@@ -533,8 +537,8 @@ __device__ __forceinline__ void vector_tiles(const ArrRef& A, uint32_t v, uint64
     uint64_t live = bucket_len(log2F, b);
     if (s - st < live) live = s - st;
     const uint64_t nt = (live + te - 1) >> te_log2;
-    const uint64_t base = A.bptr[(uint64_t)v * kMaxBuckets + b];
-    for (uint64_t i = lane; i < nt; i += 64) {
+    const uint64_t base = b < kLanes ? __shfl(mine, (int)b, (int)kLanes) : row[b];
+    for (uint64_t i = lane; i < nt; i += kLanes) {
       const uint64_t e0 = i << te_log2;
       const uint64_t cnt = live - e0 < te ? live - e0 : te;
       if (t + i < cap) {
@@ -546,10 +550,11 @@ __device__ __forceinline__ void vector_tiles(const ArrRef& A, uint32_t v, uint64
   }
 }
 
+template <uint32_t kLanes>
 __device__ __forceinline__ void table_vector(const ArrRef& A, uint32_t v, uint64_t* tab, uint64_t cap,
                                              uint32_t te_log2, uint32_t elem_log2, uint64_t t_base,
                                              uint64_t e_base) {
-  vector_tiles(A, v, A.size[v], tab, cap, te_log2, elem_log2, t_base + A.tprefix[v], e_base + A.prefix[v]);
+  vector_tiles<kLanes>(A, v, A.size[v], tab, cap, te_log2, elem_log2, t_base + A.tprefix[v], e_base + A.prefix[v]);
 }
 
 // The prefix scan and the tile table in one launch (up to 4 * kScanThreads
@@ -597,26 +602,33 @@ __global__ __launch_bounds__(256) void scan_table_kernel(ArrRef A, uint64_t* cop
       if (copy) copy[A.V] = e + s;
     }
   }
-  vector_tiles(A, v, s, tab, cap, te_log2, elem_log2, t, e);
+  vector_tiles<64>(A, v, s, tab, cap, te_log2, elem_log2, t, e);
 }
 
+// A wave per LFVector is as short while the waves fit the chip's wave slots at once; from
+// 16384 LFVectors on sixteen lanes each are (us, 64 against 16 lanes: V = 16384 8-10 and
+// 5, V = 65536 with 2 buckets 17 and 7, with 4 buckets 24 and 8.5, V = 131072 40 and
+// 13; V = 12000 5.4 as a wave).
+constexpr uint64_t kTableSharedMinV = 16384;
+template <uint32_t kLanes>
 __global__ __launch_bounds__(256) void tile_table_kernel(ArrRef A, uint64_t* tab, uint64_t cap, uint32_t te_log2,
                                                          uint32_t elem_log2) {
-  const uint32_t v = blockIdx.x * kVecPerBlock + (threadIdx.x >> 6);
-  if (v < A.V) table_vector(A, v, tab, cap, te_log2, elem_log2, 0, 0);
+  const uint64_t v = ((uint64_t)blockIdx.x * 256 + threadIdx.x) / kLanes;
+  if (v < A.V) table_vector<kLanes>(A, (uint32_t)v, tab, cap, te_log2, elem_log2, 0, 0);
 }
 
 // The tile table of a batch: the tiles of array i follow those of arrays before
 // it (tile_begin), and destination offsets are positions in the batch flatten
-// (elem_begin).  Wave w is LFVector w - vbegin[i] of array i.
+// (elem_begin).  Group w of kLanes lanes is LFVector w - vbegin[i] of array i = varr[w].
+template <uint32_t kLanes>
 __global__ __launch_bounds__(256) void batch_table_kernel(const BatchArr* items, const uint64_t* vbegin,
-                                                          const uint64_t* tile_begin, const uint64_t* elem_begin,
-                                                          uint32_t n, uint64_t* tab, uint64_t cap,
-                                                          uint32_t te_log2) {
-  const uint64_t w = (uint64_t)blockIdx.x * kVecPerBlock + (threadIdx.x >> 6);
-  if (w >= vbegin[n]) return;
-  const uint32_t i = wave_search(vbegin, n, w);
-  table_vector(items[i].A, (uint32_t)(w - vbegin[i]), tab, cap, te_log2, items[i].elem_log2, tile_begin[i],
+                                                          const uint32_t* varr, const uint64_t* tile_begin,
+                                                          const uint64_t* elem_begin, uint64_t total, uint64_t* tab,
+                                                          uint64_t cap, uint32_t te_log2) {
+  const uint64_t w = ((uint64_t)blockIdx.x * 256 + threadIdx.x) / kLanes;
+  if (w >= total) return;
+  const uint32_t i = varr[w];
+  table_vector<kLanes>(items[i].A, (uint32_t)(w - vbegin[i]), tab, cap, te_log2, items[i].elem_log2, tile_begin[i],
                elem_begin[i]);
 }
 
@@ -1011,8 +1023,12 @@ static int ensure_table(ggarray* a, hipStream_t s) {
   const int rc = grow_table(a, tag != 0, s);
   if (rc) return rc;
   if (a->tab_cap) {
-    hipLaunchKernelGGL(tile_table_kernel, dim3((a->V + kVecPerBlock - 1) / kVecPerBlock), dim3(256), 0, s, a->ref,
-                       a->tile_tab, a->tab_cap, 14u - a->elem_log2, a->elem_log2);
+    if (a->V >= kTableSharedMinV)
+      hipLaunchKernelGGL(tile_table_kernel<16>, dim3((a->V + 15) / 16), dim3(256), 0, s, a->ref, a->tile_tab,
+                         a->tab_cap, 14u - a->elem_log2, a->elem_log2);
+    else
+      hipLaunchKernelGGL(tile_table_kernel<64>, dim3((a->V + kVecPerBlock - 1) / kVecPerBlock), dim3(256), 0, s,
+                         a->ref, a->tile_tab, a->tab_cap, 14u - a->elem_log2, a->elem_log2);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_status(e);
   }
@@ -1202,9 +1218,15 @@ static int ensure_batch_table(gga_batch* b, hipStream_t s, const uint64_t** tab,
       }
     }
     if (b->tab_cap) {
-      hipLaunchKernelGGL(batch_table_kernel, dim3((uint32_t)((b->total_vectors + kVecPerBlock - 1) / kVecPerBlock)),
-                         dim3(256), 0, s, b->d_arrays, b->d_vbegin, b->d_tile_begin, b->d_elem_begin, b->n,
-                         b->tile_tab, b->tab_cap, te_log2);
+      const uint64_t V = b->total_vectors;
+      if (V >= kTableSharedMinV)
+        hipLaunchKernelGGL(batch_table_kernel<16>, dim3((uint32_t)((V + 15) / 16)), dim3(256), 0, s, b->d_arrays,
+                           b->d_vbegin, b->d_varr, b->d_tile_begin, b->d_elem_begin, V, b->tile_tab, b->tab_cap,
+                           te_log2);
+      else
+        hipLaunchKernelGGL(batch_table_kernel<64>, dim3((uint32_t)((V + kVecPerBlock - 1) / kVecPerBlock)), dim3(256),
+                           0, s, b->d_arrays, b->d_vbegin, b->d_varr, b->d_tile_begin, b->d_elem_begin, V,
+                           b->tile_tab, b->tab_cap, te_log2);
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return hip_status(e);
     }

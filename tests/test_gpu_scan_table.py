@@ -5,6 +5,7 @@ tile found from uneven lengths in arrays below the table's size; against the CPU
 oracle, bit for bit."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from oracle import Oracle
@@ -62,4 +63,41 @@ def test_walk_of_uneven_small_arrays(V, lens):
     o.rw(oracle.OP_MUL3ADD1)
     assert_same(a, o, lens)
     a.close()
+    pool.close()
+
+
+@pytest.mark.parametrize("V,F", [((16383,), 64), ((16384,), 1), ((16000, 383), 64), ((383, 16001), 1)])
+def test_table_of_many_lfvectors(V, F):
+    """The last LFVector count with a wave each and the first with sixteen lanes, one
+    array and a batch; empty LFVectors and one of 17 or more buckets of F = 1."""
+    print(f"case table of many V={V} F={F}", flush=True)
+    G = gg()
+    rng = np.random.default_rng(sum(V))
+    pool = G.Pool(1 << 30)
+    arrays, orcs = [G.GGArray(pool, 4, v, F) for v in V], [Oracle(4, v, F) for v in V]
+    batch = G.Batch(arrays) if len(V) > 1 else None
+    for r in range(2):
+        for a, o, v in zip(arrays, orcs, V):
+            lens = rng.integers(0, 3, size=v) * (BIG // v // (2 * r + 1))
+            lens[v // 2] += 300_000
+            prefix = np.concatenate([[0], np.cumsum(lens)]).astype(np.uint64)
+            seg, _ = wl.random_round(rng, int(prefix[-1]), 1.0, 4)
+            a.insert_segments(G.to_device(seg), G.to_device(prefix))
+            assert o.insert_segments(seg, prefix) == oracle.OK
+            o.rw(oracle.OP_MUL3ADD1)
+        if batch:
+            batch.rw(G.MUL3ADD1)
+            out = torch.empty(sum(o.size() for o in orcs), dtype=torch.int32, device="cuda")
+            batch.flatten_into(out)
+            flat = G.as_unsigned(out)
+        else:
+            arrays[0].rw(G.MUL3ADD1)
+            flat = G.as_unsigned(arrays[0].flatten())
+        np.testing.assert_array_equal(flat, np.concatenate([o.flatten() for o in orcs]))
+    if batch:
+        batch.close()
+    for a, o in zip(arrays, orcs):
+        assert a.last_error() == 0
+        a.close()
+        o.close()
     pool.close()
