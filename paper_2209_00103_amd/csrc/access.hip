@@ -194,11 +194,9 @@ constexpr uint32_t kVecPerBlock = 4;  // one wave per LFVector: 256 threads = 4 
 // kLanes lanes per LFVector.  A clear is a chain of dependent atomics per bucket.
 // While a wave per LFVector fits the chip's 8192 wave slots it is the shortest; a
 // few thousand LFVectors more come in turns, and four of them share a wave (V =
-// 8192, 13 buckets: 19.6 -> 16.6 us).  Arrays of 16384 LFVectors and more release
-// chains (below); of such a batch, whose arrays' lists differ, LFVectors of one list
-// would be in flight together from 32768 on and retry each other's swaps, so a wave
-// each it is again (V = 65536, 4 buckets: 59 us, against 89 us).
-inline bool shrink_shares_wave(uint64_t V) { return V >= 4096 && V < 32768; }
+// 8192, 13 buckets: 19.6 -> 16.6 us).  Many more would be in flight together with those
+// that share their free lists and retry each other's swaps: they release chains (below).
+inline bool shrink_shares_wave(uint64_t V) { return V >= 4096; }
 template <uint32_t kLanes>
 __global__ __launch_bounds__(256) void shrink_kernel(ArrRef A, uint32_t num, uint32_t den,
                                                      uint32_t elem_log2) {
@@ -223,25 +221,43 @@ __device__ __forceinline__ uint64_t exchange_link(uint8_t* block, uint64_t next)
                                          __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Buckets [lo, hi) of LFVector v are to go, as lo << 8 | hi (0: none).
-__device__ __forceinline__ uint32_t shrink_range(const ArrRef& A, uint64_t v, uint32_t num, uint32_t den) {
-  const bool in = v < A.V;
-  uint32_t dead = A.dead[in ? v : 0];
-  uint64_t s = A.size[in ? v : 0];
+// n > 0 linked blocks of class cls, the top one's index word `first`, go to free list
+// f; every link but the last has landed.
+__device__ __forceinline__ void push_chain(PoolHdr* H, uint32_t cls, uint32_t f, uint64_t first, uint8_t* last,
+                                           uint32_t n) {
+  uint64_t* const head = &H->heads[(uint64_t)cls * kFreeShards + f];
+  uint64_t h = ld_rlx(head);
+  for (;;) {
+    asm volatile("" ::"v"(exchange_link(last, h & kIdxMask)) : "memory");
+    if (cas_rlx(head, h, (((h >> 40) + 1) << 40) | first)) break;
+  }
+  if ((h & kIdxMask) == 0)
+    __hip_atomic_fetch_or(&H->nonempty[cls][f >> 6], 1ull << (f & 63), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  sub_nr(&free_stat(H)->in_use, (uint64_t)n << cls);
+  add_nr(&free_stat(H)->n_free, (uint64_t)n);
+}
+
+// Buckets [lo, hi) of LFVector v are to go, as lo << 8 | hi (0: none, also for !in).
+__device__ __forceinline__ uint32_t shrink_range(const ArrRef& A, uint64_t v, uint32_t num, uint32_t den, bool in) {
+  uint32_t dead = A.dead[v];
+  uint64_t s = A.size[v];
   asm volatile("" : "+v"(dead), "+v"(s));  // both loads in flight before either is looked at
   const uint32_t hi = dead ? (uint32_t)kMaxBuckets : nbuckets_for(A.log2F, s);
   const uint32_t lo = nbuckets_for(A.log2F, shrink_keep(s, num, den));
   return in ? lo << 8 | (hi < (uint32_t)kMaxBuckets ? hi : (uint32_t)kMaxBuckets) : 0;
 }
 
+__device__ __forceinline__ uint32_t shrink_range_at(const ArrRef& A, uint64_t v, uint32_t num, uint32_t den) {
+  return shrink_range(A, v < A.V ? v : 0, num, den, v < A.V);
+}
+
 __global__ __launch_bounds__(256) void shrink_chain_kernel(ArrRef A, uint32_t num, uint32_t den, uint32_t elem_log2) {
   const uint32_t l = threadIdx.x & (kChainLanes - 1);
   const uint64_t r = ((uint64_t)blockIdx.x * 256 + threadIdx.x) / kChainLanes;
   if (r >= (uint64_t)kFreeShards || r >= A.V) return;
-  PoolHdr* H = A.pool.hdr;
   uint32_t range = 0, most = 0;  // most: buckets of the residue's longest LFVector
   for (uint64_t v0 = r; v0 < A.V; v0 += kChainStep) {
-    range = shrink_range(A, v0 + (uint64_t)l * kFreeShards, num, den);
+    range = shrink_range_at(A, v0 + (uint64_t)l * kFreeShards, num, den);
     most = (range & 255u) > most ? range & 255u : most;
   }
 #pragma unroll
@@ -256,7 +272,7 @@ __global__ __launch_bounds__(256) void shrink_chain_kernel(ArrRef A, uint32_t nu
     uint32_t n = 0;
     uint8_t* last = nullptr;
     for (uint64_t v0 = r; v0 < A.V; v0 += kChainStep) {
-      if (A.V > kChainStep) range = shrink_range(A, v0 + (uint64_t)l * kFreeShards, num, den);
+      if (A.V > kChainStep) range = shrink_range_at(A, v0 + (uint64_t)l * kFreeShards, num, den);
       uint64_t p[kChainLanes];
 #pragma unroll
       for (uint32_t u = 0; u < kChainLanes; ++u) {
@@ -291,23 +307,129 @@ __global__ __launch_bounds__(256) void shrink_chain_kernel(ArrRef A, uint32_t nu
       for (uint32_t u = 0; u < kChainLanes; ++u) asm volatile("" ::"v"(landed[u]) : "memory");
     }
     if (n == 0) continue;
-    const uint32_t cls = bucket_class(A.log2F, elem_log2, b), f = pool_shard((uint32_t)r, b, A.salt);
-    uint64_t* const head = &H->heads[(uint64_t)cls * kFreeShards + f];
-    uint64_t h = ld_rlx(head);
-    for (;;) {
-      asm volatile("" ::"v"(exchange_link(last, h & kIdxMask)) : "memory");
-      if (cas_rlx(head, h, (((h >> 40) + 1) << 40) | first)) break;
-    }
-    if ((h & kIdxMask) == 0)
-      __hip_atomic_fetch_or(&H->nonempty[cls][f >> 6], 1ull << (f & 63), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    sub_nr(&free_stat(H)->in_use, (uint64_t)n << cls);
-    add_nr(&free_stat(H)->n_free, (uint64_t)n);
+    push_chain(A.pool.hdr, bucket_class(A.log2F, elem_log2, b), pool_shard((uint32_t)r, b, A.salt), first, last, n);
   }
   // Every lane of the residue has read the old sizes: one wave, program order.
   for (uint64_t v = r + (uint64_t)l * kFreeShards; v < A.V; v += kChainStep)
     A.size[v] = shrink_keep(A.size[v], num, den);
 }
 constexpr uint64_t kChainMinV = 16384;
+
+// The same for a batch.  Arrays created in a row take consecutive free lists, so every
+// 4096th LFVector of such a batch shares its lists too, as long as first bucket and
+// element size agree; where sixteen of them do not (other first buckets, an array
+// between them that is not in the batch, several pools) their blocks are released one by
+// one (81224 LFVectors of 512 arrays: 101 us as a wave each, 42 us; 30 and 8 us when
+// nothing is held).
+struct ShrinkItem {  // LFVector w of the batch, held by one lane
+  uint64_t* row;
+  uint8_t* base;
+  PoolHdr* hdr;
+  uint32_t list;   // log2 of the first bucket's bytes << 12 | its free list
+  uint32_t range;  // shrink_range
+};
+__device__ __forceinline__ ShrinkItem shrink_item(const BatchArr* items, const uint64_t* vbegin, const uint32_t* varr,
+                                                  uint64_t w, uint64_t total, uint32_t num, uint32_t den) {
+  const bool in = w < total;
+  if (!in) w = 0;
+  const uint32_t i = varr[w];
+  const ArrRef& A = items[i].A;
+  const uint32_t v = (uint32_t)(w - vbegin[i]);
+  return ShrinkItem{A.bptr + (uint64_t)v * kMaxBuckets, A.pool.base, A.pool.hdr,
+                    (A.log2F + items[i].elem_log2) << 12 | pool_shard(v, 0, A.salt),
+                    shrink_range(A, v, num, den, in)};
+}
+
+__global__ __launch_bounds__(256) void batch_shrink_chain_kernel(const BatchArr* items, const uint64_t* vbegin,
+                                                                 const uint32_t* varr, uint64_t total, uint32_t num,
+                                                                 uint32_t den) {
+  const uint32_t l = threadIdx.x & (kChainLanes - 1);
+  const uint64_t r = ((uint64_t)blockIdx.x * 256 + threadIdx.x) / kChainLanes;
+  if (r >= (uint64_t)kFreeShards || r >= total) return;
+  ShrinkItem it{};
+  uint32_t most = 0;
+  for (uint64_t w0 = r; w0 < total; w0 += kChainStep) {
+    it = shrink_item(items, vbegin, varr, w0 + (uint64_t)l * kFreeShards, total, num, den);
+    most = (it.range & 255u) > most ? it.range & 255u : most;
+  }
+#pragma unroll
+  for (uint32_t d = 1; d < kChainLanes; d <<= 1) {
+    const uint32_t o = (uint32_t)__shfl_xor((int)most, (int)d, (int)kChainLanes);
+    most = o > most ? o : most;
+  }
+  for (uint32_t b0 = 0; b0 < most; b0 += kChainLanes) {
+    const uint32_t b = b0 + l, bb = b < (uint32_t)kMaxBuckets ? b : 0;
+    uint64_t first = 0;
+    uint32_t n = 0, list = 0;  // of the chain
+    PoolHdr* hdr = nullptr;
+    uint8_t* last = nullptr;
+    for (uint64_t w0 = r; w0 < total; w0 += kChainStep) {
+      if (total > kChainStep) it = shrink_item(items, vbegin, varr, w0 + (uint64_t)l * kFreeShards, total, num, den);
+      uint64_t p[kChainLanes];
+#pragma unroll
+      for (uint32_t u = 0; u < kChainLanes; ++u)
+        p[u] = reinterpret_cast<const uint64_t*>(__shfl((uint64_t)it.row, (int)u, (int)kChainLanes))[bb];
+#pragma unroll
+      for (uint32_t u = 0; u < kChainLanes; ++u) {
+        asm volatile("" : "+v"(p[u]));
+        uint64_t* const slot = reinterpret_cast<uint64_t*>(__shfl((uint64_t)it.row, (int)u, (int)kChainLanes)) + bb;
+        const uint32_t g = (uint32_t)__shfl((int)it.range, (int)u, (int)kChainLanes);
+        if (b < (g >> 8) || b >= (g & 255u)) p[u] = 0;
+        if (p[u]) *slot = 0;
+        if (p[u] <= kFailedPtr) p[u] = 0;
+      }
+      const uint32_t list0 = (uint32_t)__shfl((int)it.list, 0, (int)kChainLanes);
+      uint8_t* const base = reinterpret_cast<uint8_t*>(__shfl((uint64_t)it.base, 0, (int)kChainLanes));
+      PoolHdr* const hdr0 = reinterpret_cast<PoolHdr*>(__shfl((uint64_t)it.hdr, 0, (int)kChainLanes));
+      const uint64_t odd = __ballot(it.range && (it.list != list0 || it.hdr != hdr0));
+      const bool one = ((odd >> (threadIdx.x & 48u)) & 0xFFFFull) == 0;
+      if (n && (!one || list != list0 || hdr != hdr0)) {
+        push_chain(hdr, bucket_class(list >> 12, 0, b), pool_shard(list, b, 0), first, last, n);
+        n = 0;
+      }
+      if (one) {
+        list = list0;
+        hdr = hdr0;
+        uint64_t landed[kChainLanes];
+#pragma unroll
+        for (uint32_t u = 0; u < kChainLanes; ++u) {
+          landed[u] = 0;
+          if (p[u] == 0) continue;
+          uint8_t* const block = reinterpret_cast<uint8_t*>(p[u]);
+          const uint64_t idx = ((uint64_t)(block - base) >> kMinClassLog2) + 1;
+          if (n)
+            landed[u] = exchange_link(last, idx);
+          else
+            first = idx;
+          last = block;
+          ++n;
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kChainLanes; ++u) asm volatile("" ::"v"(landed[u]) : "memory");
+      } else {
+#pragma unroll 1
+        for (uint32_t u = 0; u < kChainLanes; ++u) {
+          const uint64_t q = p[0];
+#pragma unroll
+          for (uint32_t k = 0; k + 1 < kChainLanes; ++k) p[k] = p[k + 1];
+          const uint32_t lu = (uint32_t)__shfl((int)it.list, (int)u, (int)kChainLanes);
+          PoolRef P{};
+          P.base = reinterpret_cast<uint8_t*>(__shfl((uint64_t)it.base, (int)u, (int)kChainLanes));
+          P.hdr = reinterpret_cast<PoolHdr*>(__shfl((uint64_t)it.hdr, (int)u, (int)kChainLanes));
+          if (q)
+            pool_free(P, reinterpret_cast<uint8_t*>(q), bucket_class(lu >> 12, 0, b), pool_shard(lu, b, 0));
+        }
+      }
+    }
+    if (n) push_chain(hdr, bucket_class(list >> 12, 0, b), pool_shard(list, b, 0), first, last, n);
+  }
+  for (uint64_t w = r + (uint64_t)l * kFreeShards; w < total; w += kChainStep) {
+    const uint32_t i = varr[w];
+    uint64_t* const size = items[i].A.size + (w - vbegin[i]);
+    *size = shrink_keep(*size, num, den);
+  }
+}
+constexpr uint64_t kBatchChainMinV = 32768;
 
 // Returns every bucket of the array to the pool (destroy).
 __global__ __launch_bounds__(256) void free_all_kernel(ArrRef A, uint32_t elem_log2) {
@@ -1243,7 +1365,10 @@ int launch_batch_shrink(gga_batch* b, uint32_t num, uint32_t den, hipStream_t s)
   if (num == den)
     for (uint32_t i = 0; i < b->n; ++i) b->arrays[i]->size_ub = 0;
   const uint64_t V = b->total_vectors;
-  if (shrink_shares_wave(V))
+  if (V >= kBatchChainMinV)
+    hipLaunchKernelGGL(batch_shrink_chain_kernel, dim3(kFreeShards * kChainLanes / 256), dim3(256), 0, s,
+                       b->d_arrays, b->d_vbegin, b->d_varr, V, num, den);
+  else if (shrink_shares_wave(V))
     hipLaunchKernelGGL(batch_shrink_kernel<16>, dim3((uint32_t)((V + 15) / 16)), dim3(256), 0, s, b->d_arrays,
                        b->d_vbegin, b->d_varr, V, num, den);
   else

@@ -1,6 +1,6 @@
 """Clears and partial shrinks at the edges of the release kernel's forms (a wave per
 LFVector below 4096 LFVectors, 16 lanes each up to 16383, from there on one chain per
-free list; batches: 16 lanes from 4096 to 32767), single array and batch, with more buckets than a group has lanes; sizes, contents, capacity and the
+free list; batches: chains from 32768), single array and batch, with more buckets than a group has lanes; sizes, contents, capacity and the
 pool's counts against the CPU oracle."""
 import numpy as np
 import pytest
@@ -87,3 +87,43 @@ def test_shrink_group_many_buckets_and_batch():
     for a in arrays:
         a.close()
     pool.close()
+
+
+@pytest.mark.parametrize("kind", ["row", "below", "mixed", "pools", "many"])
+def test_shrink_batch_chains(kind):
+    """Batches around the chain form's first LFVector count (32768): arrays created in a
+    row, mixed first buckets, one left out of the batch, two pools, more LFVectors than
+    one pass of a residue takes; uneven and empty LFVectors, partial shrinks and clears.
+    The pools' counts say that every block went back once."""
+    G = gg()
+    rng = np.random.default_rng(len(kind))
+    pools = [G.Pool(1 << 30) for _ in range(2 if kind == "pools" else 1)]
+    shapes = {"row": [(30000, 2), (2768, 2)], "below": [(30000, 2), (2767, 2)], "many": [(40000, 64), (33333, 64)],
+              "mixed": [(20000, 1), (7000, 64), (9000, 2)], "pools": [(20000, 2), (20000, 2)]}[kind]
+    arrays, orcs = [], []
+    for k, (V, F) in enumerate(shapes):
+        arrays.append(G.GGArray(pools[k % len(pools)], 4, V, F))
+        orcs.append(Oracle(4, V, F))
+        if kind == "mixed":
+            G.GGArray(pools[0], 4, 77, 4).close()  # shifts the next array's free lists
+    batch = G.Batch(arrays)
+    for r, (num, den) in enumerate(((1, 3), (1, 1), (2, 3), (1, 1))):
+        for a, o, (V, F) in zip(arrays, orcs, shapes):
+            n = rng.integers(0, 9, V) * (rng.random(V) < 0.7)
+            n[(r * 7919) % V] += 150_000
+            pre = np.concatenate([[0], np.cumsum(n)]).astype(np.uint64)
+            vals = rng.integers(0, 1 << 31, int(pre[-1])).astype(np.uint32)
+            a.insert_segments(dev(vals), dev(pre))
+            o.insert_segments(vals, pre)
+        batch.shrink(num, den)
+        for a, o in zip(arrays, orcs):
+            o.shrink(num, den)
+            assert_same(a, o, f"{kind} round {r}")
+    for p in pools:
+        st = p.stats()
+        assert st["in_use"] == 0 and st["allocs"] == st["frees"]
+    batch.close()
+    for a in arrays:
+        a.close()
+    for p in pools:
+        p.close()
