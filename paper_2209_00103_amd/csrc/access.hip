@@ -218,7 +218,7 @@ constexpr uint64_t kChainStep = (uint64_t)kFreeShards * kChainLanes;
 
 __device__ __forceinline__ uint64_t exchange_link(uint8_t* block, uint64_t next) {
   return __hip_atomic_exchange(gmem(reinterpret_cast<uint64_t*>(block)), next, __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_AGENT);
+                               __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // n > 0 linked blocks of class cls, the top one's index word `first`, go to free list
