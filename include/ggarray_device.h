@@ -450,9 +450,10 @@ struct MixRun {
     c1 = (hi ^ (hi >> 30)) * kLo;
     flat = (z0 & 0xFFFFFFFFull) + span <= 0x100000000ull;
   }
-  __device__ __forceinline__ uint64_t operator()(uint64_t off) const {  // off < span
+  template <bool kFlat>  // kFlat: only where flat
+  __device__ __forceinline__ uint64_t at(uint64_t off) const {  // off < span
     uint64_t z;
-    if (__builtin_expect(flat, 1)) {
+    if constexpr (kFlat) {
       uint32_t lo = (uint32_t)z0 + (uint32_t)off;
       lo ^= __builtin_amdgcn_alignbit(hi, lo, 30);  // z ^ (z >> 30), lower half
       z = (uint64_t)lo * kLo + ((uint64_t)c1 << 32) + ((uint64_t)(lo * kHi) << 32);
@@ -462,6 +463,9 @@ struct MixRun {
     }
     z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
     return z ^ (z >> 31);
+  }
+  __device__ __forceinline__ uint64_t operator()(uint64_t off) const {
+    return __builtin_expect(flat, 1) ? at<true>(off) : at<false>(off);
   }
 };
 

@@ -453,14 +453,24 @@ __device__ __forceinline__ void dense_store(T* dst, const Prod& prod, uint64_t g
   if (lane < head) d[lane] = run(lane);
   const uint32_t nv = (n - head) / VPL;
   if constexpr (Prod::kDense) {  // generated payloads: no loads in the loop
-    for (uint32_t q = lane; q < nv; q += 64) {
-      const uint32_t e = head + q * VPL;
-      T tmp[VPL];
+    const auto fill = [&](auto one) {
+      for (uint32_t q = lane; q < nv; q += 64) {
+        const uint32_t e = head + q * VPL;
+        T tmp[VPL];
 #pragma unroll
-      for (uint32_t k = 0; k < VPL; ++k) tmp[k] = run(e + k);
-      u32x4 x;
-      __builtin_memcpy(&x, tmp, 16);
-      store_nt_sc1(reinterpret_cast<gptr<u32x4>>(d + e), x);
+        for (uint32_t k = 0; k < VPL; ++k) tmp[k] = one(e + k);
+        u32x4 x;
+        __builtin_memcpy(&x, tmp, 16);
+        store_nt_sc1(reinterpret_cast<gptr<u32x4>>(d + e), x);
+      }
+    };
+    if constexpr (Prod::kMixed) {
+      // The hash's form is chosen once per run: a branch at each output kept a vector's
+      // hashes from overlapping (a round of 956 LFVectors: 23.4 -> 20.2 us).
+      if (run.mix.flat) fill([&](uint32_t e) { return run.template at<true>(e); });
+      else fill([&](uint32_t e) { return run.template at<false>(e); });
+    } else {
+      fill([&](uint32_t e) { return run(e); });
     }
   } else {
     // Payloads from memory: kU vectors per lane are loaded (clamped to the last

@@ -64,6 +64,7 @@ struct ProdRoundTag {  // insert (round << shift) | gid
   static constexpr bool kMulti = false;
   static constexpr bool kDense = true;  // every thread inserts
   static constexpr bool kLoads = false;
+  static constexpr bool kMixed = false;
   uint32_t round;
   uint32_t shift;
   __device__ __forceinline__ bool flag(uint64_t) const { return true; }
@@ -86,6 +87,7 @@ struct ProdKeyed {  // every thread inserts K(seed, (tag << shift) | gid, round)
   static constexpr bool kMulti = false;
   static constexpr bool kDense = true;
   static constexpr bool kLoads = false;
+  static constexpr bool kMixed = true;  // Run holds a MixRun
   uint64_t seed;
   uint32_t round;
   uint32_t shift;
@@ -99,6 +101,8 @@ struct ProdKeyed {  // every thread inserts K(seed, (tag << shift) | gid, round)
   struct Run {
     MixRun mix;
     __device__ __forceinline__ T operator()(uint32_t d) const { return (T)mix((uint64_t)d << 8); }
+    template <bool kFlat>
+    __device__ __forceinline__ T at(uint32_t d) const { return (T)mix.template at<kFlat>((uint64_t)d << 8); }
     __device__ __forceinline__ bool take(uint32_t d, T& v) const {
       v = (T)mix((uint64_t)d << 8);
       return true;
