@@ -263,6 +263,9 @@ __device__ __forceinline__ uint8_t* global_bump(PoolRef P, uint64_t bytes) {
   return P.base + old;
 }
 
+// The arena word of a shard whose next chunk did not fit the region (chunks of cap units).
+__device__ __forceinline__ uint64_t past_end(uint64_t cap) { return (kNoChunk << 32) | (cap + 1); }
+
 __device__ __forceinline__ uint8_t* arena_alloc(PoolRef P, uint32_t s, uint64_t bytes, uint32_t clog) {
   PoolHdr* H = P.hdr;
   const uint64_t units = bytes >> kMinClassLog2;
@@ -274,6 +277,10 @@ __device__ __forceinline__ uint8_t* arena_alloc(PoolRef P, uint32_t s, uint64_t 
     const uint64_t old = fetch_add(word, units);
     const uint64_t cid = old >> 32, used = old & 0xFFFFFFFFull;
     if (cid == kNoChunk) {
+      // Every allocation that misses its free list from then on adds to the word.  Long
+      // before the sum could carry into the id (and the word name a chunk again), the
+      // word is put back.
+      if (used >> 31) __hip_atomic_exchange(word, past_end(cap), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       open = 0;
     } else if (cid && used + units <= cap) {
       got = P.base + ((cid - 1) << kMinClassLog2) + (used << kMinClassLog2);
@@ -281,9 +288,9 @@ __device__ __forceinline__ uint8_t* arena_alloc(PoolRef P, uint32_t s, uint64_t 
     } else if (cid ? used <= cap : used == 0) {  // this add crossed the end: it installs the next chunk
       got = global_bump(P, 1ull << clog);
       // The region can only run out once (the bump pointer never goes back): then
-      // the word says so, past its end for every later add.
-      const uint64_t next = got ? ((((uint64_t)(got - P.base) >> kMinClassLog2) + 1) << 32) | units
-                                : (kNoChunk << 32) | (cap + 1);
+      // the word says so for good.
+      const uint64_t next =
+          got ? ((((uint64_t)(got - P.base) >> kMinClassLog2) + 1) << 32) | units : past_end(cap);
       __hip_atomic_exchange(word, next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       open = 0;
     }
