@@ -27,7 +27,7 @@ struct ProdBuffer {
   __device__ __forceinline__ T value(uint64_t g) const { return values[g]; }
   struct Run {
     const T* p;
-    __device__ __forceinline__ T operator()(uint32_t d) const { return p[d]; }
+    __device__ __forceinline__ T operator()(uint64_t d) const { return p[d]; }
   };
   __device__ __forceinline__ Run run(uint64_t g0, uint64_t) const { return {values + g0}; }
 };

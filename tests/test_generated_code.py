@@ -1,0 +1,41 @@
+"""What the compiler makes of the insertion kernels, where their speed hangs on it."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2209_00103_amd import build as B
+
+pytestmark = pytest.mark.skipif(not os.path.exists(B.HIPCC) and not shutil.which("hipcc"),
+                                reason="hipcc not available")
+
+
+@pytest.fixture(scope="module")
+def insert_asm(tmp_path_factory):
+    asm = str(tmp_path_factory.mktemp("asm") / "insert.s")
+    r = subprocess.run([B.HIPCC, *B.CFLAGS, "-S", "--cuda-device-only", os.path.join(B.CSRC, "insert.hip"), "-o", asm],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    with open(asm) as f:
+        return f.read()
+
+
+def _kernels(asm, name):
+    """(symbol, code) of the kernels whose mangled name holds `name` (a pattern)."""
+    found = re.findall(r"^(_ZN\S*\d+%s\S*):\s*;.*?\n(.*?)\n\.Lfunc_end" % name, asm, re.S | re.M)
+    assert found, name
+    return found
+
+
+@pytest.mark.parametrize("kernel", [
+    "segments_kernel", "segments_block_kernel", "segments_store_kernel", "grow_store_block_kernel",
+    r"grow_store_kernelI\wNS_10ProdBuffer", r"dense_insert_kernelI\wNS_10ProdBuffer",
+    r"static_dense_kernelI\wNS_10ProdBuffer",
+])
+def test_buffer_copies_load_vectors(insert_asm, kernel):
+    """A run of a buffer's elements is copied through four 16-byte loads a lane, not a load per element."""
+    for name, code in _kernels(insert_asm, kernel):
+        n = len(re.findall(r"\bglobal_load_dwordx4\b", code))
+        assert n >= 4, f"{name}: {n} 16-byte loads"
