@@ -247,6 +247,11 @@ struct SizeItem {
   uint64_t V;
 };
 
+// Eight waves of a kernel fit a SIMD with at most 80 scalar registers each: its 800
+// are given out in sixteens, and sixteen more per wave are kept for the trap handler.
+// (With 82 of them seven fit: appends to 2^20 LFVectors 351 us, 323 with 80.)
+#define GGA_EIGHT_WAVES __attribute__((amdgpu_num_sgpr(80)))
+
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // The r/w operation on the elements of one 16-byte vector.

@@ -39,3 +39,13 @@ def test_buffer_copies_load_vectors(insert_asm, kernel):
     for name, code in _kernels(insert_asm, kernel):
         n = len(re.findall(r"\bglobal_load_dwordx4\b", code))
         assert n >= 4, f"{name}: {n} 16-byte loads"
+
+
+@pytest.mark.parametrize("kernel", ["grow_store_kernel", "segments_kernel"])
+def test_eight_waves_of_a_kernel_fit_a_simd(insert_asm, kernel):
+    """Short rounds of many LFVectors wait for memory with every wave a CU can hold: 80 scalar and 64 vector
+    registers are the most that eight waves of a SIMD may have."""
+    for name, _ in _kernels(insert_asm, kernel):
+        info = insert_asm[insert_asm.index(f".amdhsa_kernel {name}\n"):]
+        assert int(re.search(r"; TotalNumSgprs: (\d+)", info).group(1)) <= 80, name
+        assert int(re.search(r"; NumVgprs: (\d+)", info).group(1)) <= 64, name
