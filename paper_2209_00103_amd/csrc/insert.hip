@@ -2295,6 +2295,14 @@ bool multi_mode(uint32_t mode) { return mode == kModeCounts || mode == kModePois
 // and stores it (else a grow launch, then one workgroup per tile).
 inline bool wave_per_vector(const TileArgs& I, uint32_t V) { return I.tpv <= 8 || V >= 512; }
 
+// Waves of a workgroup that copies one LFVector's share of `bytes`: as many as let all
+// V workgroups be on the chip (8192 waves) at once, which long shares do not need (V =
+// 1024, 390 KiB: 193 us with 8 waves, 186 with 16); V > kFewWorkgroups comes in turns.
+constexpr uint32_t kFewWorkgroups = 2048;
+inline uint32_t block_waves(uint32_t V, uint64_t bytes) {
+  return V <= 512 || (V <= 1024 && bytes > 32 * kSpanBytes) ? 16 : V <= 1024 ? 8 : 4;
+}
+
 template <typename T>
 int launch_dense(const ArrRef& A, const TileArgs& I, const InsertDesc& d, uint64_t ntiles, hipStream_t s,
                  hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr) {
@@ -2302,16 +2310,23 @@ int launch_dense(const ArrRef& A, const TileArgs& I, const InsertDesc& d, uint64
     const dim3 grid((A.V + 3) / 4), block(256);
     switch (d.mode) {
       case kModeBuffer: {
-        // Shares of at most one load round (4 KiB): a wave each.  Longer ones: 16
-        // waves while that many LFVectors leave the chip short of waves (V <= 1024
-        // fills its 8192), else 4.
+        // A wave per LFVector for shares of at most one load round (4 KiB), and up to
+        // three where the waves alone fill the chip; else a workgroup of block_waves
+        // (us a round by a wave, 4, 8 and 16 waves: V = 1024, 4.2 KiB 11.1, 11.0, 10.9,
+        // 15.4, 64 KiB 39.8, 32.7, 33.0, 36.1; by a wave and 4: V = 4096, 4.2 KiB 16.0,
+        // 18.1, 24 KiB 57.7, 52.4; V = 65536, 4.2 KiB 179, 234, 8 KiB 257, 277, 12 KiB
+        // 356, 341).
         const T* values = static_cast<const T*>(d.values);
-        if (I.chunk * sizeof(T) <= kSpanBytes)
+        const uint64_t rounds = A.V > kFewWorkgroups ? 3 : 1;
+        const uint32_t waves = block_waves(A.V, I.chunk * sizeof(T));
+        if (I.chunk * sizeof(T) <= rounds * kSpanBytes)
           hipExtLaunchKernelGGL(grow_store_kernel<T, ProdBuffer<T>>, grid, block, 0, s, e0, e1, 0, A, I,
                                 ProdBuffer<T>{values, nullptr});
-        else if (A.V <= 1024)
+        else if (waves == 16)
           hipExtLaunchKernelGGL((grow_store_block_kernel<T, 16>), dim3(A.V), dim3(1024), 0, s, e0, e1, 0, A, I,
                                 values);
+        else if (waves == 8)
+          hipExtLaunchKernelGGL((grow_store_block_kernel<T, 8>), dim3(A.V), dim3(512), 0, s, e0, e1, 0, A, I, values);
         else
           hipExtLaunchKernelGGL((grow_store_block_kernel<T, 4>), dim3(A.V), block, 0, s, e0, e1, 0, A, I, values);
         break;

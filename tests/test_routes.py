@@ -1,0 +1,37 @@
+"""Which kernels a call launches, by size and state: the library's host side on the CPU
+with its launches recorded."""
+import os
+import shutil
+
+import pytest
+
+from tests import hip_routes
+
+pytestmark = pytest.mark.skipif(not shutil.which("gcc") or not shutil.which("c++filt")
+                                or not os.path.exists(hip_routes.LIB), reason="needs gcc and the built library")
+
+
+@pytest.fixture(scope="module")
+def record(tmp_path_factory):
+    return hip_routes.build_record(tmp_path_factory.mktemp("record"))
+
+
+def test_dense_buffer_rounds_by_share_and_count(record):
+    """A wave per LFVector while the share is short or the waves alone fill the chip, else a workgroup of as many
+    waves as leave every workgroup room on the chip at once."""
+    out = hip_routes.run("""
+p, out = R.pool(), []
+for V, kb in ((1, 4), (1, 5), (512, 5), (513, 5), (1024, 5), (1024, 128), (1024, 129), (1025, 5), (2048, 5), (2049, 5), (2049, 12), (2049, 13),
+              (65536, 12), (65536, 13)):
+    for elem in (4, 8):
+        a = R.array(p, elem, V)
+        R.insert(a, V * (kb * 1024 // elem))
+        out += R.launches()
+""", record)
+    want = {(1, 4): 1, (1, 5): 16, (512, 5): 16, (513, 5): 8, (1024, 5): 8, (1024, 128): 8, (1024, 129): 16,
+            (1025, 5): 4, (2048, 5): 4, (2049, 5): 1,
+            (2049, 12): 1, (2049, 13): 4, (65536, 12): 1, (65536, 13): 4}
+    exp = []
+    for (V, _), w in want.items():
+        exp += 2 * [["grow_store_kernel", (V + 3) // 4, 256] if w == 1 else ["grow_store_block_kernel", V, 64 * w]]
+    assert out == exp
