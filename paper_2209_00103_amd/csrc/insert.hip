@@ -2541,23 +2541,42 @@ template <typename T>
 static void queue_segments(const ArrRef& A, const TileArgs& I, const T* values, const uint64_t* prefix,
                            uint64_t n_values, hipStream_t s) {
   const dim3 grid((A.V + 3) / 4), block(256);
-  // One launch, with a wave per LFVector while the segments average at most one load
-  // round of a wave, or a workgroup per LFVector up to eight; above that, and with
-  // too many LFVectors for workgroups of sixteen waves, the store launch is worth
-  // its 5 us for the balance (lognormal segments, workgroups against two launches:
-  // 8.0e6 u32 elements in 512 26.6 and 21 us, 1.5e7 in 4096 45 and 39 us).
+  // By what the segments average, in load rounds of a wave (4 KiB).  A wave per
+  // LFVector up to one round, or two where workgroups come in turns; then a workgroup
+  // per LFVector up to eight; above that the store launch is worth its 5 us for the
+  // balance.  The host does not know the lengths, so a form has to serve equal and
+  // uneven ones.  us, equal lengths / lognormal ones (sigma 1):
+  //   V       average   wave         workgroup (waves)          grow + store
+  //   512     32 KiB    18 / 84      13 / 21 (16)               17 / 29
+  //   512     64 KiB    24 / 157     17 / 34 (16)               21 / 32
+  //   1024    4.2 KiB   11.5 / 30    11.3 / 13.8 (8), 16.5 (16) 14.5 / 20.6
+  //   2048    8 KiB     14.9 / 28    13.3 / 18 (4)              17.7 / 22
+  //   2048    32 KiB    36 / 141     34 / 72 (4), 37 / 54 (8)   38 / 55
+  //   4096    6 KiB     17.7 / 31    19.9 / 22 (4)              21.7 / 25
+  //   4096    16 KiB    38 / 103     39 / 59 (4), 46 / 56 (8)   41 / 69
+  //   4096    24 KiB    57 / 268     53 / 121 (4), 59 / 93 (8)  63 / 99
+  //   16384   24 KiB    195 / 342    182 / 216 (4), 195 / 217 (8)  220 / 238
+  //   65536   8 KiB     260 / 299    322 / 327 (4)              291 / 305
+  //   65536   24 KiB    678 / 832    657 / 710 (4), 728 / 786 (8)  724 / 757
   const uint64_t spans = n_values * sizeof(T) / kSpanBytes;
-  if (spans <= A.V) {
+  if (spans <= (A.V <= kFewWorkgroups ? 1ull : 2ull) * A.V) {
     hipLaunchKernelGGL(segments_kernel<T>, grid, block, 0, s, A, I, values, prefix, n_values);
     return;
   }
-  if (A.V <= 1024 && spans <= 8ull * A.V) {
-    hipLaunchKernelGGL((segments_block_kernel<T, 16>), dim3(A.V), dim3(1024), 0, s, A, I, values, prefix, n_values);
+  if (spans <= 8ull * A.V) {
+    uint32_t waves = block_waves(A.V, 0);
+    if (waves == 4 && A.V <= 16384 && spans > 4ull * A.V) waves = 8;
+    if (waves == 16)
+      hipLaunchKernelGGL((segments_block_kernel<T, 16>), dim3(A.V), dim3(1024), 0, s, A, I, values, prefix, n_values);
+    else if (waves == 8)
+      hipLaunchKernelGGL((segments_block_kernel<T, 8>), dim3(A.V), dim3(512), 0, s, A, I, values, prefix, n_values);
+    else
+      hipLaunchKernelGGL((segments_block_kernel<T, 4>), dim3(A.V), block, 0, s, A, I, values, prefix, n_values);
     return;
   }
-  // Twice the workgroups that equal segments would need, so that a segment of
-  // several times the average still finishes with the others, up to 128 per CU.
-  uint64_t parts = (2 * spans / kW + A.V - 1) / A.V;
+  // Workgroups enough for a load round per wave in equal segments, up to 128 per CU (twice
+  // as many: 1024 segments of 64 KiB 46 us, 37 this way, 51 and 47 uneven).
+  uint64_t parts = (spans / kW + A.V - 1) / A.V;
   const uint64_t most = (32768 + A.V - 1) / A.V;
   if (parts > most) parts = most;
   hipLaunchKernelGGL(segments_grow_kernel, grid, block, 0, s, A, I, prefix, n_values);

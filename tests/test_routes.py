@@ -21,17 +21,41 @@ def test_dense_buffer_rounds_by_share_and_count(record):
     waves as leave every workgroup room on the chip at once."""
     out = hip_routes.run("""
 p, out = R.pool(), []
-for V, kb in ((1, 4), (1, 5), (512, 5), (513, 5), (1024, 5), (1024, 128), (1024, 129), (1025, 5), (2048, 5), (2049, 5), (2049, 12), (2049, 13),
-              (65536, 12), (65536, 13)):
+for V, kb in ((1, 4), (1, 5), (512, 5), (513, 5), (1024, 5), (1024, 128), (1024, 129), (1025, 5), (2048, 5),
+              (2049, 5), (2049, 12), (2049, 13), (65536, 12), (65536, 13)):
     for elem in (4, 8):
         a = R.array(p, elem, V)
         R.insert(a, V * (kb * 1024 // elem))
         out += R.launches()
 """, record)
     want = {(1, 4): 1, (1, 5): 16, (512, 5): 16, (513, 5): 8, (1024, 5): 8, (1024, 128): 8, (1024, 129): 16,
-            (1025, 5): 4, (2048, 5): 4, (2049, 5): 1,
-            (2049, 12): 1, (2049, 13): 4, (65536, 12): 1, (65536, 13): 4}
+            (1025, 5): 4, (2048, 5): 4, (2049, 5): 1, (2049, 12): 1, (2049, 13): 4, (65536, 12): 1, (65536, 13): 4}
     exp = []
     for (V, _), w in want.items():
         exp += 2 * [["grow_store_kernel", (V + 3) // 4, 256] if w == 1 else ["grow_store_block_kernel", V, 64 * w]]
+    assert out == exp
+
+
+def test_segments_by_average_and_count(record):
+    out = hip_routes.run("""
+p, out = R.pool(), []
+for V, kb in ((1, 4), (1, 8), (512, 8), (512, 32), (512, 36), (1024, 8), (1024, 32), (2048, 16), (2048, 20), (2048, 36),
+              (2049, 8), (2049, 12), (2049, 16), (2049, 20), (16385, 20), (16385, 36)):
+    for elem in (4, 8):
+        a = R.array(p, elem, V)
+        R.segments(a, V * (kb * 1024 // elem))
+        out.append(R.launches())
+""", record)
+    # waves per LFVector (0: a wave without a workgroup of its own), or the store launch's workgroups per LFVector
+    want = [(1, 0), (1, 16), (512, 16), (512, 16), (512, "3"), (1024, 8), (1024, 8), (2048, 4), (2048, 8), (2048, "3"),
+            (2049, 0), (2049, 4), (2049, 4), (2049, 8), (16385, 4), (16385, "2")]
+    exp = []
+    for V, w in want:
+        if w == 0:
+            form = [["segments_kernel", (V + 3) // 4, 256]]
+        elif isinstance(w, str):
+            form = [["segments_grow_kernel", (V + 3) // 4, 256], ["segments_store_kernel", V * int(w), 256]]
+        else:
+            form = [["segments_block_kernel", V, 64 * w]]
+        exp += [form, form]
     assert out == exp
