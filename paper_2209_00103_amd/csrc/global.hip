@@ -37,13 +37,17 @@ __device__ __forceinline__ gptr<T> element_at(const ArrRef& A, uint64_t i) {
 
 // One thread per element (small arrays, few reads).
 template <typename T>
-__global__ __launch_bounds__(kGlobalThreads) void rw_element_kernel(ArrRef A, uint32_t op) {
-  const uint64_t n = A.prefix[A.V];
+__device__ __forceinline__ void rw_elements(const ArrRef& A, uint32_t op, uint64_t n) {
   const uint64_t stride = (uint64_t)gridDim.x * kGlobalThreads;
   for (uint64_t i = (uint64_t)blockIdx.x * kGlobalThreads + threadIdx.x; i < n; i += stride) {
     const gptr<T> p = element_at<T>(A, i);
     *p = apply_op<T>(op, *p);
   }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kGlobalThreads) void rw_element_kernel(ArrRef A, uint32_t op) {
+  rw_elements<T>(A, op, A.prefix[A.V]);
 }
 
 template <typename T>
@@ -91,9 +95,8 @@ __device__ __forceinline__ void wave_rw_run(gptr<T> p, uint32_t n, uint32_t op) 
 // side, each search limited to the LFVectors that the span reaches.
 constexpr uint32_t kRunVectors = 4;
 template <typename T, uint32_t kU>
-__global__ __launch_bounds__(kGlobalThreads) void rw_global_kernel(ArrRef A, uint32_t op) {
+__device__ __forceinline__ void rw_spans(const ArrRef& A, uint32_t op, uint64_t n) {
   constexpr uint32_t kPer = kU * (16 / sizeof(T)), kSpan = 64 * kPer, kE = kPer < 8 ? kPer : 8;
-  const uint64_t n = A.prefix[A.V];
   const uint64_t waves = (uint64_t)gridDim.x * (kGlobalThreads / 64);
   const uint32_t lane = threadIdx.x & 63u;
   for (uint64_t w = (uint64_t)blockIdx.x * (kGlobalThreads / 64) + (threadIdx.x >> 6); w * kSpan < n; w += waves) {
@@ -151,6 +154,27 @@ __global__ __launch_bounds__(kGlobalThreads) void rw_global_kernel(ArrRef A, uin
         if (i + 64 * u < i1) gmem(reinterpret_cast<T*>(row[u]))[off[u]] = apply_op<T>(op, x[u]);
     }
   }
+}
+
+// Where one thread per element gives way to spans: at 4 MiB (us, element against span
+// form: V = 512, 1.0e5 u32 elements 4.3 and 6.7, 3.0e6 27 and 14; V = 4096, 1.0e6 u32
+// 14.6 and 16.0, 2.0e6 24 and 15.5, 6.0e5 u64 13.2 and 13.2).  Spans of 8 KiB once they
+// fill the chip's 8192 wave slots (64 MiB of elements), 2 KiB below.
+constexpr uint64_t kSpanMinBytes = 1ull << 22;
+constexpr uint64_t kWideMinBytes = 1ull << 26;
+
+// The host's bound of the size, which chooses the launch, may be far above it (rounds
+// that inserted little, shrinks): the form follows the size itself (V = 512, 30000
+// elements under a bound of 6e7: 32 us in spans of 8 KiB, 7 us as elements).
+template <typename T, bool kWide>
+__global__ __launch_bounds__(kGlobalThreads) void rw_global_kernel(ArrRef A, uint32_t op) {
+  const uint64_t n = A.prefix[A.V];
+  if (n * sizeof(T) < kSpanMinBytes)
+    rw_elements<T>(A, op, n);
+  else if (kWide && n * sizeof(T) >= kWideMinBytes)
+    rw_spans<T, 8>(A, op, n);
+  else
+    rw_spans<T, 2>(A, op, n);
 }
 
 // Every workgroup keeps P[0], P[2^k], P[2 2^k], ... in LDS, k the smallest that
@@ -217,30 +241,27 @@ __global__ __launch_bounds__(kGlobalThreads) void gather_kernel(ArrRef A, const 
 
 }  // namespace
 
-// Where one thread per element gives way to the kernels above (us, element against
-// span or LDS form): updates at V = 512 of 1.0e5 elements 4.3 against 6.7, at V =
-// 4096 of 5.0e5 9.3 against 9.4, at V = 512 of 3.0e6 26 against 12; reads at V = 4096,
-// 1.6e5 7.8 against 10.7, 2.0e6 60 against 44, at V = 32, 2.0e6 40 against 36.
-constexpr uint64_t kSpanMinElems = 1ull << 19;
+// Where one thread per read gives way to the LDS form (us, element against LDS form): at
+// V = 4096, 1.6e5 reads 7.8 against 10.7, 2.0e6 60 against 44, at V = 32, 2.0e6 40
+// against 36.
 constexpr uint64_t kGatherMinReads = 1ull << 20;
 
 template <typename T>
 static void queue_rw_global(const ggarray* a, uint32_t op, hipStream_t s) {
   const dim3 block(kGlobalThreads);
-  if (a->size_ub < kSpanMinElems) {
+  if (a->size_ub < kSpanMinBytes >> a->elem_log2) {
     const uint64_t blocks = a->size_ub / kGlobalThreads + 1;
     hipLaunchKernelGGL(rw_element_kernel<T>, dim3((uint32_t)blocks), block, 0, s, a->ref, op);
     return;
   }
-  // A wave per span of the host's bound of the size, looping beyond.  Spans of 8
-  // KiB once they fill the chip's 8192 wave slots (64 MiB of elements), 2 KiB below.
-  const bool wide = a->size_ub >> (26u - a->elem_log2) != 0;
+  // A wave per span of the host's bound of the size, looping beyond.
+  const bool wide = a->size_ub >= kWideMinBytes >> a->elem_log2;
   const uint64_t spans = (a->size_ub >> ((wide ? 13u : 11u) - a->elem_log2)) + 1, per = kGlobalThreads / 64;
   const dim3 grid((uint32_t)(spans < kGlobalBlocks * per ? (spans + per - 1) / per : kGlobalBlocks));
   if (wide)
-    hipLaunchKernelGGL((rw_global_kernel<T, 8>), grid, block, 0, s, a->ref, op);
+    hipLaunchKernelGGL((rw_global_kernel<T, true>), grid, block, 0, s, a->ref, op);
   else
-    hipLaunchKernelGGL((rw_global_kernel<T, 2>), grid, block, 0, s, a->ref, op);
+    hipLaunchKernelGGL((rw_global_kernel<T, false>), grid, block, 0, s, a->ref, op);
 }
 
 int launch_rw_global(ggarray* a, uint32_t op, hipStream_t s) {
