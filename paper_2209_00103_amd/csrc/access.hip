@@ -1077,7 +1077,7 @@ static bool streams_by_table(const ggarray* a) { return (a->size_ub >> (14u - a-
 int launch_scan(ggarray* a, hipStream_t s, uint64_t* copy, ScanTable table) {
   const uint32_t te_log2 = 14u - a->elem_log2;
   const uint64_t tag = stream_capture_tag(s);
-  bool with_table = table != kScanOnly && a->V <= 4 * kScanThreads && streams_by_table(a);
+  bool with_table = table != kScanOnly && a->V <= 4 * kScanThreads && streams_by_table(a) && capture_reuse(a, tag, tag);
   if (with_table && table == kScanGrowTable) {
     const int rc = grow_table(a, tag != 0, s);
     if (rc) return rc;

@@ -435,7 +435,8 @@ int launch_static_insert_atomic(gga_static* st, const InsertDesc& d, hipStream_t
 // The prefix scan (copy: also write the prefix there), with the tile table in the
 // same launch where the array streams through one and has few enough LFVectors:
 // grown for an r/w or flatten that follows, only if it is large enough already for
-// other readers of the prefix.
+// other readers of the prefix.  (Not where a graph changes the sizes: the streaming
+// call builds its table anew then.)
 enum ScanTable : uint32_t { kScanOnly = 0, kScanKeepTable = 1, kScanGrowTable = 2 };
 int launch_scan(ggarray* a, hipStream_t s, uint64_t* copy = nullptr, ScanTable table = kScanOnly);
 // *word (may be null) and the sticky error into host[0] and host[1] (pinned).

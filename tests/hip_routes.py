@@ -41,10 +41,15 @@ def check(rc, want=0):
     assert rc == want, f"status {rc}, not {want}"
 
 
+def memory(n):
+    p = ctypes.c_void_p()
+    check(rec.hipMalloc(ctypes.byref(p), ctypes.c_size_t(n)))
+    return p
+
+
 def pool():
-    p, mem = ctypes.c_void_p(), ctypes.c_void_p()
-    check(rec.hipMalloc(ctypes.byref(mem), ctypes.c_size_t(4 << 20)))
-    check(lib.gga_pool_create(ctypes.byref(p), mem, u64(4 << 20), None))
+    p = ctypes.c_void_p()
+    check(lib.gga_pool_create(ctypes.byref(p), memory(4 << 20), u64(4 << 20), None))
     return p
 
 

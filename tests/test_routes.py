@@ -59,3 +59,31 @@ for V, kb in ((1, 4), (1, 8), (512, 8), (512, 32), (512, 36), (1024, 8), (1024, 
             form = [["segments_block_kernel", V, 64 * w]]
         exp += [form, form]
     assert out == exp
+
+
+SETUP = """
+p, out = R.pool(), []
+a, offsets = R.array(p, 4, 512), R.memory(8 * 513)
+def prefix():
+    R.check(R.lib.ggarray_prefix(a, offsets, None))
+def rw():
+    R.check(R.lib.ggarray_rw(a, 0, None))
+def insert():  # the same size again, so that a table once built is large enough
+    R.check(R.lib.ggarray_shrink(a, 1, 1, None))
+    R.insert(a, 1 << 24)
+    R.launches()
+def seen():
+    out.append([k for k, _, _ in R.launches()])
+"""
+APART = ["scan_kernel", "tile_table_kernel", "stream_table_kernel"]
+
+
+def test_sizes_changed_by_graphs_scan_and_build_apart(record):
+    """Once a graph changes the sizes, no eager call may rely on a table built before it: one build a call, not two."""
+    out = hip_routes.run(SETUP + """
+insert(); rw(); seen()
+R.rec.rec_capture(7); R.insert(a, 512); rw(); seen(); R.rec.rec_capture(0)
+rw(); seen(); rw(); seen(); prefix(); seen()
+""", record)
+    assert out == [["scan_table_kernel", "stream_table_kernel"],
+                   ["grow_store_kernel", "scan_table_kernel", "stream_table_kernel"], APART, APART, ["scan_kernel"]]
