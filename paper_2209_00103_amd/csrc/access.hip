@@ -1163,6 +1163,7 @@ static int ensure_table(ggarray* a, hipStream_t s) {
 static int stream_source(ggarray* a, hipStream_t s, const uint64_t** tab, uint64_t* cap) {
   *tab = nullptr;
   *cap = 0;
+  if (a->prefix_gen == a->sizes_gen + 1) a->prefix_streamed = true;
   if (!streams_by_table(a)) return GGA_OK;
   const int rc = ensure_table(a, s);
   if (rc) return rc;

@@ -266,6 +266,8 @@ int ggarray_create(ggarray** out, gga_pool* p, uint32_t elem_bytes, uint32_t n_v
   a->tab_gen = ~0ull;
   a->n_retired = 0;
   a->last_rw_gen = 0;
+  a->prefix_gen = 0;
+  a->prefix_streamed = false;
   a->scan_tag = 0;
   a->tab_tag = 0;
   a->graph_sized = false;
@@ -477,8 +479,16 @@ int ggarray_vector_sizes(ggarray* a, uint64_t* dev_out, gga_stream s) {
 
 int ggarray_prefix(ggarray* a, uint64_t* dev_out, gga_stream s) {
   if (!a || !dev_out) return GGA_EINVAL;
-  if (!a->prefix_valid || !capture_reuse(a, a->scan_tag, stream_capture_tag(S(s))))
-    return launch_scan(a, S(s), dev_out, kScanKeepTable);  // the scan writes both
+  if (!a->prefix_valid || !capture_reuse(a, a->scan_tag, stream_capture_tag(S(s)))) {
+    // The scan writes both.  With the tile table in its launch the r/w or flatten that
+    // comes next saves a launch (4 us), while a caller of the offsets alone would pay for
+    // a table that nobody reads (6 us without it; 7 with it at V = 512, 49 at V = 1, 2^27
+    // elements): the last scan's use tells which caller this is.
+    const ScanTable table = a->prefix_streamed ? kScanKeepTable : kScanOnly;
+    a->prefix_streamed = false;
+    a->prefix_gen = a->sizes_gen + 1;
+    return launch_scan(a, S(s), dev_out, table);
+  }
   return hip_status(hipMemcpyAsync(dev_out, a->ref.prefix, 8ull * (a->V + 1), hipMemcpyDeviceToDevice, S(s)));
 }
 

@@ -37,6 +37,8 @@ struct ggarray {
   uint32_t n_retired;
   uint64_t* scan_tot;     // device: per 1024 LFVectors, their total size and tiles
   uint64_t last_rw_gen;   // sizes_gen + 1 when the last streaming call was an r/w (0: not)
+  uint64_t prefix_gen;    // sizes_gen + 1 when ggarray_prefix last scanned
+  bool prefix_streamed;   // an r/w or flatten followed that scan on the same sizes
   uint64_t scan_tag;      // capture tag (stream_capture_tag) the current prefix was built under
   uint64_t tab_tag;       // capture tag the current tile table was built under
   bool graph_sized;       // a captured call changes the sizes (replays do so unseen)

@@ -78,6 +78,18 @@ def seen():
 APART = ["scan_kernel", "tile_table_kernel", "stream_table_kernel"]
 
 
+def test_the_offsets_alone_build_no_tile_table(record):
+    """ggarray_prefix writes the tile table in its launch only where the last sizes it was asked for were streamed."""
+    out = hip_routes.run(SETUP + """
+insert(); prefix(); seen(); insert(); prefix(); seen()          # offsets alone
+insert(); prefix(); rw(); seen(); insert(); prefix(); rw(); seen()  # offsets, then an r/w
+insert(); prefix(); seen(); insert(); prefix(); seen()          # alone again: one table too many, then none
+insert(); rw(); prefix(); seen()
+""", record)
+    assert out == [["scan_kernel"], ["scan_kernel"], APART, ["scan_table_kernel", "stream_table_kernel"],
+                   ["scan_table_kernel"], ["scan_kernel"], ["scan_table_kernel", "stream_table_kernel"]]
+
+
 def test_sizes_changed_by_graphs_scan_and_build_apart(record):
     """Once a graph changes the sizes, no eager call may rely on a table built before it: one build a call, not two."""
     out = hip_routes.run(SETUP + """
