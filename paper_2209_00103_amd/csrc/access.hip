@@ -643,13 +643,19 @@ __device__ __forceinline__ void stream_range(const ArrRef& A, uint64_t t0, uint6
 // bucket table's first kLanes entries at once, beside the size and the prefixes.
 // Entries from `cap` on are not written; the streaming kernels then walk the
 // buckets instead.
-// LFVector v of s elements; its first tile is t, its first element's place pv.
+template <uint32_t kLanes>
+__device__ __forceinline__ uint64_t table_entry(const ArrRef& A, uint32_t v) {
+  const uint32_t lane = threadIdx.x & (kLanes - 1);
+  return A.bptr[(uint64_t)v * kMaxBuckets + (lane < (uint32_t)kMaxBuckets ? lane : 0)];
+}
+// LFVector v of s elements; its first tile is t, its first element's place pv, the lane's
+// entry of its bucket table `mine`.
 template <uint32_t kLanes>
 __device__ __forceinline__ void vector_tiles(const ArrRef& A, uint32_t v, uint64_t s, uint64_t* tab, uint64_t cap,
-                                             uint32_t te_log2, uint32_t elem_log2, uint64_t t, uint64_t pv) {
+                                             uint32_t te_log2, uint32_t elem_log2, uint64_t t, uint64_t pv,
+                                             uint64_t mine) {
   const uint32_t lane = threadIdx.x & (kLanes - 1);
   const uint64_t* row = A.bptr + (uint64_t)v * kMaxBuckets;
-  const uint64_t mine = row[lane < (uint32_t)kMaxBuckets ? lane : 0];
   const uint32_t log2F = A.log2F;
   const uint64_t te = 1ull << te_log2;
   typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
@@ -672,11 +678,35 @@ __device__ __forceinline__ void vector_tiles(const ArrRef& A, uint32_t v, uint64
   }
 }
 
-template <uint32_t kLanes>
-__device__ __forceinline__ void table_vector(const ArrRef& A, uint32_t v, uint64_t* tab, uint64_t cap,
-                                             uint32_t te_log2, uint32_t elem_log2, uint64_t t_base,
-                                             uint64_t e_base) {
-  vector_tiles<kLanes>(A, v, A.size[v], tab, cap, te_log2, elem_log2, t_base + A.tprefix[v], e_base + A.prefix[v]);
+// An LFVector for the tile table: of array A, with the table's and the flatten's place
+// of that array's first tile and element.
+struct TableItem {
+  const ArrRef* A;
+  uint32_t v, elem_log2;
+  uint64_t tile, elem;
+};
+
+// Tiles of LFVector w (of `total`) by kLanes lanes; item(w) says where it is.  One of
+// more than kLongTiles tiles is left to its whole wave (with sixteen lanes of it for the
+// one long LFVector of 16384, 2^28 u32 elements, table and r/w took 759 us, 495 this way).
+constexpr uint64_t kLongTiles = 256;
+template <uint32_t kLanes, class Item>
+__device__ __forceinline__ void table_vector(Item item, uint64_t w, uint64_t total, uint64_t* tab, uint64_t cap,
+                                             uint32_t te_log2) {
+  const bool in = w < total;
+  const TableItem it = item(in ? w : 0);
+  const uint64_t s = it.A->size[it.v], t = it.tile + it.A->tprefix[it.v], e = it.elem + it.A->prefix[it.v];
+  const uint64_t mine = table_entry<kLanes>(*it.A, it.v);
+  const bool whole = kLanes < 64 && s >> te_log2 > kLongTiles;
+  if (in && !whole) vector_tiles<kLanes>(*it.A, it.v, s, tab, cap, te_log2, it.elem_log2, t, e, mine);
+  if constexpr (kLanes < 64) {
+    for (uint64_t m = __ballot(in && whole && (threadIdx.x & (kLanes - 1)) == 0); m; m &= m - 1) {
+      const int l = __ffsll((unsigned long long)m) - 1;
+      const TableItem long_it = item(__shfl(w, l, 64));
+      vector_tiles<64>(*long_it.A, long_it.v, __shfl(s, l, 64), tab, cap, te_log2, long_it.elem_log2,
+                       __shfl(t, l, 64), __shfl(e, l, 64), table_entry<64>(*long_it.A, long_it.v));
+    }
+  }
 }
 
 // The prefix scan and the tile table in one launch (up to 4 * kScanThreads
@@ -713,7 +743,7 @@ __global__ __launch_bounds__(256) void scan_table_kernel(ArrRef A, uint64_t* cop
     t += tiles_for(A.log2F, s, te_log2);
   }
   if (v >= A.V) return;
-  const uint64_t s = A.size[v];
+  const uint64_t s = A.size[v], mine = table_entry<64>(A, v);
   if (lane == 0) {
     A.prefix[v] = e;
     A.tprefix[v] = t;
@@ -724,7 +754,7 @@ __global__ __launch_bounds__(256) void scan_table_kernel(ArrRef A, uint64_t* cop
       if (copy) copy[A.V] = e + s;
     }
   }
-  vector_tiles<64>(A, v, s, tab, cap, te_log2, elem_log2, t, e);
+  vector_tiles<64>(A, v, s, tab, cap, te_log2, elem_log2, t, e, mine);
 }
 
 // A wave per LFVector is as short while the waves fit the chip's wave slots at once; from
@@ -735,8 +765,8 @@ constexpr uint64_t kTableSharedMinV = 16384;
 template <uint32_t kLanes>
 __global__ __launch_bounds__(256) void tile_table_kernel(ArrRef A, uint64_t* tab, uint64_t cap, uint32_t te_log2,
                                                          uint32_t elem_log2) {
-  const uint64_t v = ((uint64_t)blockIdx.x * 256 + threadIdx.x) / kLanes;
-  if (v < A.V) table_vector<kLanes>(A, (uint32_t)v, tab, cap, te_log2, elem_log2, 0, 0);
+  const auto item = [&](uint64_t v) { return TableItem{&A, (uint32_t)v, elem_log2, 0, 0}; };
+  table_vector<kLanes>(item, ((uint64_t)blockIdx.x * 256 + threadIdx.x) / kLanes, A.V, tab, cap, te_log2);
 }
 
 // The tile table of a batch: the tiles of array i follow those of arrays before
@@ -747,11 +777,11 @@ __global__ __launch_bounds__(256) void batch_table_kernel(const BatchArr* items,
                                                           const uint32_t* varr, const uint64_t* tile_begin,
                                                           const uint64_t* elem_begin, uint64_t total, uint64_t* tab,
                                                           uint64_t cap, uint32_t te_log2) {
-  const uint64_t w = ((uint64_t)blockIdx.x * 256 + threadIdx.x) / kLanes;
-  if (w >= total) return;
-  const uint32_t i = varr[w];
-  table_vector<kLanes>(items[i].A, (uint32_t)(w - vbegin[i]), tab, cap, te_log2, items[i].elem_log2, tile_begin[i],
-               elem_begin[i]);
+  const auto item = [&](uint64_t w) {
+    const uint32_t i = varr[w];
+    return TableItem{&items[i].A, (uint32_t)(w - vbegin[i]), items[i].elem_log2, tile_begin[i], elem_begin[i]};
+  };
+  table_vector<kLanes>(item, ((uint64_t)blockIdx.x * 256 + threadIdx.x) / kLanes, total, tab, cap, te_log2);
 }
 
 // Load policy of r/w.  Non-temporal loads (kNtLoad) serve an r/w that directly
