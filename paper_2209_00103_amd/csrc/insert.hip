@@ -1836,9 +1836,8 @@ __global__ __launch_bounds__(kB) void packed_copy_kernel(ArrRef A, TileArgs I, c
 // with its size unchanged) and hands the pointers to the other threads through LDS;
 // the stores follow.  The prefix is known, so counts asking for more values than
 // given are refused before anything grows.  The tile's chain of allocations and
-// loads, not its bytes, sets its time, so short tiles take one wave each (32 on a
-// CU, against 8 workgroups of four waves; V = 65536, 770 8-byte elements each: 325
-// -> 183 us, 4.4 TB/s).
+// loads, not its bytes, sets its time, so short tiles take one wave each (V = 65536,
+// 770 8-byte elements each: 325 -> 183 us, 4.4 TB/s).
 template <typename T, uint32_t NT>
 __global__ __launch_bounds__(NT) void packed_grow_copy_kernel(ArrRef A, TileArgs I, const T* values,
                                                               const uint64_t* tile_off, uint64_t ntiles,
@@ -1915,6 +1914,108 @@ __global__ __launch_bounds__(NT) void packed_grow_copy_kernel(ArrRef A, TileArgs
     r.store(reinterpret_cast<T*>(s_bp[b]));
     i += run;
   }
+}
+
+// A wave per LFVector, four to a workgroup, where a few tiles may be far longer than
+// the others: one of more than kLongRun bytes would hold its wave for a trip to memory
+// per 8 KiB, so it is grown by its wave and copied by the whole workgroup afterwards (V =
+// 2048 of up to 1000 threads, one of them 2.6e5 u32 elements: 148 us by waves of their
+// own, 79 by a workgroup each, 67 this way; none of them: 21, 40 and 21 us).
+constexpr uint32_t kLongRun = 32768;
+
+// n elements from local index s0 on, by nthr threads; bucket(b) gives the pointer of
+// bucket b.
+template <typename T, class Bucket>
+__device__ __forceinline__ void copy_runs(uint32_t log2F, uint64_t s0, uint32_t n, const T* src, uint32_t tid,
+                                          uint32_t nthr, Bucket bucket) {
+  for (uint32_t i = 0; i < n;) {
+    const uint64_t idx = s0 + i;
+    const uint32_t b = bucket_of(log2F, idx);
+    const uint64_t bs = bucket_start(log2F, b);
+    const uint64_t room = bs + bucket_len(log2F, b) - idx;
+    const uint32_t run = (uint64_t)(n - i) < room ? n - i : (uint32_t)room;
+    RunCopy<T> r;
+    r.load(src + i, idx - bs, run, tid, nthr);
+    r.store(reinterpret_cast<T*>(bucket(b)));
+    i += run;
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kB) void packed_grow_copy_waves_kernel(ArrRef A, TileArgs I, const T* values,
+                                                                    const uint64_t* tile_off, uint64_t ntiles,
+                                                                    uint64_t n_values) {
+  __shared__ uint64_t s_bp[kW][kMaxBuckets];
+  __shared__ uint64_t s_off[kW], s_s0[kW];
+  __shared__ uint32_t s_n[kW];  // elements of a long tile
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, w = tid >> 6, v = blockIdx.x * kW + w;
+  const uint32_t log2F = A.log2F;
+  if (packed_offset(tile_off, ntiles, ntiles) > n_values) {
+    if (blockIdx.x == 0 && tid == 0) set_error(A.err, kErrRange);
+    return;
+  }
+  if (lane == 0) s_n[w] = 0;
+  if (v < A.V) {
+    const uint64_t off = packed_offset(tile_off, ntiles, v);
+    const uint64_t end = packed_offset(tile_off, ntiles, (uint64_t)v + 1);
+    const uint64_t s0 = A.size[v];
+    const uint32_t dead = A.dead[v], n = (uint32_t)(end - off);
+    if (n && !dead) {
+      const T* src = values + off;
+      const uint32_t b0 = bucket_of(log2F, s0), b1 = bucket_of(log2F, s0 + n - 1);
+      const uint32_t lo = nbuckets_for(log2F, s0), hi = nbuckets_for(log2F, s0 + n), b = lo + lane;
+      const bool later = (uint64_t)n * sizeof(T) > kLongRun, two = b1 == b0 + 1;
+      const uint32_t na = two ? (uint32_t)(bucket_start(log2F, b1) - s0) : n;
+      const bool second = two && lane >= 32;
+      RunCopy<T> rc;  // as in packed_grow_copy_kernel
+      if (!later && b1 <= b0 + 1)
+        rc.load(second ? src + na : src, second ? 0 : s0 - bucket_start(log2F, b0), second ? n - na : na,
+                second ? lane - 32 : lane, two ? 32 : 64);
+      const uint64_t held = lane < lo ? A.bptr[(uint64_t)v * kMaxBuckets + lane] : 0;
+      uint64_t q = kFailedPtr;  // bucket b, if the round reaches it
+      bool failed = false;
+      if (b < hi) {
+        if (b >= (uint32_t)kMaxBuckets) {
+          failed = true;
+        } else {
+          uint8_t* p = pool_alloc(A.pool, bucket_class(log2F, I.elem_log2, b), pool_shard(v, b, A.salt));
+          q = p ? (uint64_t)p : kFailedPtr;
+          A.bptr[(uint64_t)v * kMaxBuckets + b] = q;
+          failed = !p;
+        }
+      }
+      const auto bucket = [&](uint32_t k) {
+        return k < lo ? __shfl(held, (int)k, 64) : __shfl(q, (int)(k - lo), 64);
+      };
+      if (__ballot(failed)) {
+        if (lane == 0) {
+          set_error(A.err, kErrNoMem);
+          A.dead[v] = 1u;
+        }
+      } else {
+        if (lane == 0) A.size[v] = s0 + n;
+        if (later) {
+          if (lane < lo) s_bp[w][lane] = held;
+          if (b < hi) s_bp[w][b] = q;
+          if (lane == 0) {
+            s_off[w] = off;
+            s_s0[w] = s0;
+            s_n[w] = n;
+          }
+        } else if (b1 <= b0 + 1) {
+          const uint64_t p0 = bucket(b0), p1 = bucket(b1);
+          rc.store(reinterpret_cast<T*>(second ? p1 : p0));
+        } else {
+          copy_runs(log2F, s0, n, src, lane, 64, bucket);
+        }
+      }
+    }
+  }
+  __syncthreads();
+  for (uint32_t u = 0; u < (uint32_t)kW; ++u)
+    if (s_n[u])
+      copy_runs(log2F, s_s0[u], s_n[u], values + s_off[u], tid, (uint32_t)kB,
+                [u](uint32_t k) { return s_bp[u][k]; });
 }
 
 // ------------------------------------------- flagged rounds in two passes --
@@ -2618,14 +2719,21 @@ static int ensure_packed_offsets(ggarray* a, uint64_t words, hipStream_t s) {
 
 // One tile per LFVector: a wave each while the values average at most one pass of
 // a wave's loads (8 KiB) and the LFVectors give every CU several, else a workgroup.
+// Four waves to a workgroup unless the other LFVectors outlast the longest tile that the
+// counts allow (255 values a thread, some 1.2 us per 8 KiB of it, against some 3 ns per
+// LFVector): waves of their own do not wait for each other's end (V = 65536, 256 threads
+// of up to 6 u32 values: 151 us, 185 as four to a workgroup).
 template <typename T>
 static void launch_grow_copy(const ArrRef& A, const TileArgs& I, const T* values, const uint64_t* off,
                              uint64_t ntiles, uint64_t n_values, hipStream_t s) {
-  if (A.V >= kCountWaveMinV && n_values * sizeof(T) <= (uint64_t)A.V << 13)
+  if (A.V < kCountWaveMinV || n_values * sizeof(T) > (uint64_t)A.V << 13)
+    hipLaunchKernelGGL((packed_grow_copy_kernel<T, kB>), dim3((uint32_t)ntiles), dim3(kB), 0, s, A, I, values, off,
+                       ntiles, n_values);
+  else if (8 * I.chunk * sizeof(T) <= A.V)
     hipLaunchKernelGGL((packed_grow_copy_kernel<T, 64>), dim3((uint32_t)ntiles), dim3(64), 0, s, A, I, values, off,
                        ntiles, n_values);
   else
-    hipLaunchKernelGGL((packed_grow_copy_kernel<T, kB>), dim3((uint32_t)ntiles), dim3(kB), 0, s, A, I, values, off,
+    hipLaunchKernelGGL(packed_grow_copy_waves_kernel<T>, dim3((A.V + kW - 1) / kW), dim3(kB), 0, s, A, I, values, off,
                        ntiles, n_values);
 }
 

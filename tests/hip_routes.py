@@ -89,6 +89,10 @@ def counts(a, n, most=4, want=0):
     check(lib.ggarray_insert_counts(a, ptr(SOMEWHERE), ptr(SOMEWHERE), most, u64(n), None), want)
 
 
+def packed(a, n, n_values):
+    check(lib.ggarray_insert_packed(a, ptr(SOMEWHERE), u64(n_values), ptr(SOMEWHERE), u64(n), None))
+
+
 def run(body, record):
     prog = (f"import sys, json; sys.path.insert(0, {ROOT!r})\n"
             f"from tests import hip_routes as R\nR.load({record!r})\n{body}\nprint(json.dumps(out))")

@@ -99,3 +99,19 @@ rw(); seen(); rw(); seen(); prefix(); seen()
 """, record)
     assert out == [["scan_table_kernel", "stream_table_kernel"],
                    ["grow_store_kernel", "scan_table_kernel", "stream_table_kernel"], APART, APART, ["scan_kernel"]]
+
+
+def test_packed_rounds_of_one_tile_by_count_and_length(record):
+    """A workgroup per LFVector for few of them or long tiles; a wave each, four to a workgroup that copies a tile of
+    up to 255 values a thread together; waves of their own where the other LFVectors outlast such a tile."""
+    out = hip_routes.run("""
+p, out = R.pool(), []
+for V, elem, chunk, kb in ((2047, 4, 100, 1), (2048, 4, 100, 1), (2048, 4, 1024, 8), (2048, 4, 1024, 9), (2048, 4, 64, 1),
+                           (2048, 4, 65, 1), (2048, 8, 33, 1), (65536, 8, 1024, 8), (16384, 8, 257, 2)):
+    a = R.array(p, elem, V)
+    R.packed(a, V * chunk, V * kb * 1024 // elem)
+    out.append(R.launches()[-1])
+""", record)
+    one, four, own = "packed_grow_copy_kernel", "packed_grow_copy_waves_kernel", "packed_grow_copy_kernel"
+    assert out == [[one, 2047, 256], [four, 512, 256], [four, 512, 256], [one, 2048, 256], [own, 2048, 64],
+                   [four, 512, 256], [four, 512, 256], [own, 65536, 64], [four, 4096, 256]]
