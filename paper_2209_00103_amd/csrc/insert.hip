@@ -1523,12 +1523,32 @@ __global__ __launch_bounds__(64) void insert_count_wave_kernel(ArrRef A, TileArg
 // waves in the first form (512 threads per LFVector, workgroup against wave: 12.6
 // against 16.0 us at V = 512, 23.6 against 19.4 us at V = 2048; 256 threads: 11.2
 // against 10.7 us at V = 512, 22.0 against 13.3 us at V = 2048).
+//
+// A wave takes some 5 ns an output, so a share of thousands holds the launch unless the
+// other LFVectors outlast it.  The host does not know the counts of a buffer, only the
+// most they can be (us, workgroup against wave, one LFVector of a thousand full, the
+// others at 0.1: V = 2048, 256 threads of up to 4 12.1 and 10.2, of up to 16 14.7 and
+// 18.9, 512 of up to 16 17.8 and 38; V = 8192, 512 of up to 16 44 and 55; V = 32768 151
+// and 131); generated counts are alike for all LFVectors (V = 2048, 512 threads of 3 and
+// 8 on average 25 and 22, 32 and 44; V = 65536, of 8 598 and 455).
 constexpr uint32_t kCountWaveMinV = 2048;
+template <typename T>
+bool waves_suit(const ProdCounts<T>& p, uint64_t chunk, uint32_t V) {
+  const uint64_t most = chunk * p.max_count;
+  return most <= V / 2 && (most <= 4096 || V >= 32768);
+}
+template <typename T>
+bool waves_suit(const ProdPoisson<T>& p, uint64_t chunk, uint32_t V) {
+  double mean = 0;  // a uniform 64-bit draw reaches threshold k with probability 1 - thr / 2^64
+  for (uint32_t k = 0; k < p.max_count; ++k) mean += 1.0 - (double)p.thr[k] * 0x1p-64;
+  return chunk <= 256 || (double)chunk * mean <= 2048.0 + V / 4;
+}
+
 template <typename T, class Prod, bool kStatic>
 void launch_counts(const ArrRef& A, const StaticRef& S, const TileArgs& I, const Prod& p, uint64_t ntiles,
                    hipStream_t s) {
   if constexpr (!kStatic) {
-    if (I.tpv == 1 && I.chunk <= 512 && A.V >= kCountWaveMinV) {
+    if (I.tpv == 1 && I.chunk <= 512 && A.V >= kCountWaveMinV && waves_suit<T>(p, I.chunk, A.V)) {
       if (I.chunk <= 256)
         hipLaunchKernelGGL((insert_count_wave_kernel<T, Prod, 4>), dim3(A.V), dim3(64), 0, s, A, I, p);
       else

@@ -93,6 +93,14 @@ def packed(a, n, n_values):
     check(lib.ggarray_insert_packed(a, ptr(SOMEWHERE), u64(n_values), ptr(SOMEWHERE), u64(n), None))
 
 
+def poisson(a, n, each):
+    """A round whose draws all pass `each` of sixteen thresholds, so that each thread inserts that many."""
+    g = Gen(kind=3, round=1, seed=3, max_count=16)
+    for k in range(16):
+        g.thresholds[k] = 0 if k < each else (1 << 64) - 1
+    check(lib.ggarray_insert_gen(a, ctypes.byref(g), u64(n), None))
+
+
 def run(body, record):
     prog = (f"import sys, json; sys.path.insert(0, {ROOT!r})\n"
             f"from tests import hip_routes as R\nR.load({record!r})\n{body}\nprint(json.dumps(out))")

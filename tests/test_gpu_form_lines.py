@@ -3,6 +3,7 @@ for many LFVectors; against the CPU oracle, bit for bit."""
 import numpy as np
 import pytest
 
+import oracle
 from paper_2209_00103_amd import workloads as wl
 from tests.gpu_util import assert_same, both, dev, gg
 
@@ -48,6 +49,32 @@ def test_segment_lines(elem, V, F, kb):
         a.insert_segments(dev(vals), dev(prefix))
         o.insert_segments(vals, prefix)
         assert_same(a, o, f"segments {r}")
+    a.close()
+    o.close()
+    pool.close()
+
+
+@pytest.mark.parametrize("V,chunk,mc", [(8192, 256, 16), (8192, 512, 8), (2048, 257, 4)])
+def test_counts_lines(V, chunk, mc):
+    """A wave's largest shares (two owner-map passes), and the workgroup form just past the line."""
+    print(f"case counts lines V={V} chunk={chunk} max={mc}", flush=True)
+    rng = np.random.default_rng(V + chunk)
+    pool = gg().Pool(1 << 30)
+    a, o = both(4, V, 16, pool)
+    n = V * chunk - 5
+    counts = rng.integers(0, 2, size=n, dtype=np.uint8)
+    counts.reshape(-1)[: 3 * chunk] = mc  # three full shares, the rest sparse
+    counts[n // 2: n // 2 + chunk] = mc
+    vals, _ = wl.random_round(rng, n * mc, 1.0, 4)
+    a.insert_counts(dev(vals), dev(counts), mc)
+    o.insert_counts(vals, counts, mc)
+    assert_same(a, o, "counts")
+    thr = [0] * 15 + [1 << 63]  # fifteen or sixteen elements a thread
+    g = gg().make_gen(gg().GEN_POISSON, seed=7, round=3, max_count=16, thresholds=thr)
+    m = V * min(chunk, 100)
+    a.insert_gen(g, m)
+    o.insert_gen(oracle.GEN_POISSON, m, seed=7, round=3, max_count=16, thresholds=thr)
+    assert_same(a, o, "generated")
     a.close()
     o.close()
     pool.close()

@@ -115,3 +115,20 @@ for V, elem, chunk, kb in ((2047, 4, 100, 1), (2048, 4, 100, 1), (2048, 4, 1024,
     one, four, own = "packed_grow_copy_kernel", "packed_grow_copy_waves_kernel", "packed_grow_copy_kernel"
     assert out == [[one, 2047, 256], [four, 512, 256], [four, 512, 256], [one, 2048, 256], [own, 2048, 64],
                    [four, 512, 256], [four, 512, 256], [own, 65536, 64], [four, 4096, 256]]
+
+
+def test_counts_rounds_of_one_tile_by_what_a_share_may_hold(record):
+    """A wave per LFVector where no share can hold the launch, else a workgroup."""
+    out = hip_routes.run("""
+p, out = R.pool(), []
+for V, chunk, most in ((2047, 64, 4), (2048, 256, 4), (2048, 257, 4), (2048, 64, 16), (2048, 65, 16), (8192, 256, 16),
+                       (8192, 512, 8), (8192, 512, 9), (16384, 512, 16), (32768, 512, 16), (65536, 513, 2)):
+    a = R.array(p, 4, V)
+    R.counts(a, V * chunk, most)
+    out.append(R.launches()[-1][2])
+for V, chunk, each in ((2048, 256, 16), (2048, 512, 5), (2048, 512, 6), (8192, 512, 8), (8192, 512, 9), (65536, 512, 16)):
+    a = R.array(p, 8, V)
+    R.poisson(a, V * chunk, each)
+    out.append(R.launches()[-1][2])
+""", record)
+    assert out == [256, 64, 256, 64, 256, 64, 64, 256, 256, 64, 256] + [64, 64, 256, 64, 256, 64]
