@@ -1379,9 +1379,14 @@ __device__ __forceinline__ void store_owned_run(T* dst_, const uint16_t* own, ui
   }
 }
 
-template <typename T, class Prod, bool kStatic>
+// kRuns: with the producer's RunTile.
+template <typename T, class Prod, bool kStatic, bool kRuns = false>
 __global__ __launch_bounds__(kB) void insert_count_kernel(ArrRef A, StaticRef S, TileArgs I,
                                                           Prod prod) {
+  const auto tile_at = [&prod](uint64_t g) {
+    if constexpr (kRuns) return prod.run_tile(g);
+    else return prod.tile(g);
+  };
   __shared__ uint16_t s_own[kOwnWindow];  // output -> (thread, logical thread, element)
   __shared__ TileShared sh;
   const uint32_t tid = threadIdx.x, lane = tid & 63u, w = tid >> 6;
@@ -1398,7 +1403,7 @@ __global__ __launch_bounds__(kB) void insert_count_kernel(ArrRef A, StaticRef S,
     tile_range(I, v, t, kCountTile, g0, gend);
   }
   uint32_t cnt[kCountK];
-  typename Prod::Tile tile = prod.tile(g0);
+  auto tile = tile_at(g0);
   uint32_t c = produce_counts(tile, tid * kCountK, g0 < gend ? gend - g0 : 0, cnt);
   if (ticketed && tid == 0) {
     sh.tile = k;
@@ -1409,7 +1414,7 @@ __global__ __launch_bounds__(kB) void insert_count_kernel(ArrRef A, StaticRef S,
   if (ticketed && (sh.tile & 0xFFFFFFFFull) != t) {  // dispatched out of order: produce for the ticket
     t = sh.tile & 0xFFFFFFFFull;
     tile_range(I, v, t, kCountTile, g0, gend);
-    tile = prod.tile(g0);
+    tile = tile_at(g0);
     c = produce_counts(tile, tid * kCountK, g0 < gend ? gend - g0 : 0, cnt);
   }
   if (g0 >= gend) return;
@@ -1488,8 +1493,8 @@ __global__ __launch_bounds__(64) void insert_count_wave_kernel(ArrRef A, TileArg
   if (g0 >= gend || A.dead[v]) return;
   const uint64_t size0 = A.size[v];
   uint32_t cnt[K];
-  const typename Prod::Tile tile = prod.tile(g0);
-  const uint32_t c = produce_counts<typename Prod::Tile, K>(tile, lane * K, gend - g0, cnt);
+  const typename Prod::RunTile tile = prod.run_tile(g0);
+  const uint32_t c = produce_counts<typename Prod::RunTile, K>(tile, lane * K, gend - g0, cnt);
   const uint32_t incl = wave_incl_scan(c), n_t = __shfl(incl, 63, 64);
   const WaveRes r = resolve_wave(A, I, v, 0, 0, true, n_t, size0, 0);
   const uint32_t log2F = A.log2F;
@@ -1511,7 +1516,7 @@ __global__ __launch_bounds__(64) void insert_count_wave_kernel(ArrRef A, TileArg
       const uint32_t run = (uint64_t)(w1 - i) < room ? w1 - i : (uint32_t)room;
       const uint64_t p = __shfl(r.bp, (int)(b - r.b_lo), 64);
       if (p > kFailedPtr)
-        store_owned_run<T, typename Prod::Tile, 64>(reinterpret_cast<T*>(p) + (idx - bs), s_own + (i - w0), run, tile);
+        store_owned_run<T, typename Prod::RunTile, 64>(reinterpret_cast<T*>(p) + (idx - bs), s_own + (i - w0), run, tile);
       i += run;
     }
     __syncthreads();  // the window is read before the next one is written
@@ -1553,6 +1558,13 @@ void launch_counts(const ArrRef& A, const StaticRef& S, const TileArgs& I, const
         hipLaunchKernelGGL((insert_count_wave_kernel<T, Prod, 4>), dim3(A.V), dim3(64), 0, s, A, I, p);
       else
         hipLaunchKernelGGL((insert_count_wave_kernel<T, Prod, 8>), dim3(A.V), dim3(64), 0, s, A, I, p);
+      return;
+    }
+  }
+  if constexpr (Prod::kRuns && !kStatic) {
+    if (ntiles > 8192) {  // four times what the chip holds at once
+      hipLaunchKernelGGL((insert_count_kernel<T, Prod, false, true>), dim3((uint32_t)ntiles), dim3(kB), 0, s, A, S, I,
+                         p);
       return;
     }
   }

@@ -116,6 +116,7 @@ struct ProdKeyed {  // every thread inserts K(seed, (tag << shift) | gid, round)
 template <typename T>
 struct ProdCounts {  // insert values[gid * max + j], j < counts[gid]
   static constexpr bool kMulti = true;
+  static constexpr bool kRuns = false;  // RunTile is Tile
   const T* values;
   const uint8_t* counts;
   uint32_t max_count;
@@ -134,27 +135,47 @@ struct ProdCounts {  // insert values[gid * max + j], j < counts[gid]
     }
   };
   __device__ __forceinline__ Tile tile(uint64_t g0) const { return {*this, g0}; }
+  typedef Tile RunTile;
+  __device__ __forceinline__ RunTile run_tile(uint64_t g0) const { return tile(g0); }
 };
 template <typename T>
 struct ProdPoisson {  // c = #{k : K(seed,gid,0x80|round) >= thr[k]}; insert K(seed,gid,16 round + j)
   static constexpr bool kMulti = true;
+  static constexpr bool kRuns = true;
   uint64_t seed;
   uint32_t round;
   uint32_t max_count;
   uint64_t thr[16];
+  // How many of the thresholds a draw reaches.
+  __device__ __forceinline__ uint32_t reached(uint64_t u) const {
+    uint32_t c = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) c += (k < (int)max_count && u >= thr[k]) ? 1u : 0u;
+    return c;
+  }
+  // With the whole hash for each draw and element: in a round of few tiles each one's
+  // chain hides the product that a run of states saves, and fetching both forms of the
+  // hash costs more than it gains (1000 threads 13.2 us with runs, 12.4 us so).
   struct Tile {
     const ProdPoisson* prod;
-    MixRun draws, mix;
+    uint64_t g0;
     __device__ __forceinline__ uint32_t count(uint32_t d) const {
-      const uint64_t u = draws((uint64_t)d << 8);
-      uint32_t c = 0;
-#pragma unroll
-      for (int k = 0; k < 16; ++k) c += (k < (int)prod->max_count && u >= prod->thr[k]) ? 1u : 0u;
-      return c;
+      return prod->reached(K(prod->seed, g0 + d, 0x80u | prod->round));
     }
+    __device__ __forceinline__ T value(uint32_t d, uint32_t r) const {
+      return (T)K(prod->seed, g0 + d, 16u * prod->round + r);
+    }
+  };
+  __device__ __forceinline__ Tile tile(uint64_t g0) const { return {this, g0}; }
+  // For rounds bound by issuing: a wave per LFVector (65536 of them 2% shorter), many tiles
+  // (16384 of them 180 us as above, 174 so).
+  struct RunTile {
+    const ProdPoisson* prod;
+    MixRun draws, mix;
+    __device__ __forceinline__ uint32_t count(uint32_t d) const { return prod->reached(draws((uint64_t)d << 8)); }
     __device__ __forceinline__ T value(uint32_t d, uint32_t r) const { return (T)mix(((uint64_t)d << 8) + r); }
   };
-  __device__ __forceinline__ Tile tile(uint64_t g0) const {
+  __device__ __forceinline__ RunTile run_tile(uint64_t g0) const {
     const uint64_t first = (seed << 56) + (g0 << 8);
     return {this, MixRun(first + (0x80u | round), 1024u << 8), MixRun(first + 16u * round, 1024u << 8)};
   }

@@ -49,3 +49,13 @@ def test_eight_waves_of_a_kernel_fit_a_simd(insert_asm, kernel):
         info = insert_asm[insert_asm.index(f".amdhsa_kernel {name}\n"):]
         assert int(re.search(r"; TotalNumSgprs: (\d+)", info).group(1)) <= 80, name
         assert int(re.search(r"; NumVgprs: (\d+)", info).group(1)) <= 64, name
+
+
+def test_small_generated_counts_rounds_fetch_one_form_of_the_hash(insert_asm):
+    """A small round fetches each instruction anew: the workgroup kernel of drawn counts holds one form of its hashes
+    (86 quarter-rate products for 4-byte elements, 74 for 8-byte ones; both forms make 114 and 98)."""
+    seen = 0
+    for name, code in _kernels(insert_asm, r"insert_count_kernelI\wNS_11ProdPoissonI\wEELb0ELb0"):
+        assert len(re.findall(r"\bv_(?:mul_hi_u32|mul_lo_u32|mad_u64_u32)\b", code)) <= 90, name
+        seen += 1
+    assert seen == 2
