@@ -2098,11 +2098,11 @@ __device__ __forceinline__ uint64_t mask_pass(const uint8_t* flags, uint64_t g0,
     for (uint32_t c = 0; c < C; ++c) m |= (uint64_t)nonzero_bytes<E>(f[c]) << (c * E);
     return m;
   }
+  const uint32_t len = (uint32_t)(te - g0);
+  const int32_t room = tile_room(g0, n);
 #pragma unroll
-  for (uint32_t c = 0; c < C; ++c) {
-    const uint64_t g = g0 + c * 64 * E + lane * E;
-    f[c] = *reinterpret_cast<gptr<const W_a1>>(src + (g + E <= n ? g : n - E));
-  }
+  for (uint32_t c = 0; c < C; ++c)
+    f[c] = *reinterpret_cast<gptr<const W_a1>>(src + g0 + tile_vector<E>(c * 64 * E + lane * E, len, room));
 #pragma unroll
   for (uint32_t c = 0; c < C; ++c) {
     const uint64_t g = g0 + c * 64 * E + lane * E;
@@ -2200,23 +2200,24 @@ __global__ __launch_bounds__(1024) void flag_grow_long_kernel(ArrRef A, TileArgs
 // elements all land in one bucket, at dst1 on.
 constexpr uint32_t kChunkBatch = 8;
 template <typename T, bool kOne>
-__device__ __forceinline__ void copy_blocked(const T* values, uint64_t g0, uint64_t n, uint64_t word, gptr<T> dst1,
-                                             uint64_t base, uint32_t log2F, uint32_t b_lo, uint64_t bp, T* s_keep) {
+__device__ __forceinline__ void copy_blocked(const T* values, uint64_t g0, uint64_t te, uint64_t n, uint64_t word,
+                                             gptr<T> dst1, uint64_t base, uint32_t log2F, uint32_t b_lo, uint64_t bp,
+                                             T* s_keep) {
   typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
   constexpr uint32_t E = 16 / sizeof(T), C = 64 / E;
   static_assert(kMaskWords == 1 && C % kChunkBatch == 0, "one 64-bit mask word per lane");
   const uint32_t lane = lane_id();
   const gptr<const T> src = gmem(values);
-  const bool at_end = g0 + kWaveTile > n;  // some vector would run past the buffer
+  const uint32_t len = (uint32_t)(te - g0);
+  const int32_t room = tile_room(g0, n);
+  const bool at_end = room < kWaveTile;  // some vector would run past the buffer
   uint32_t run = 0;
 #pragma unroll 1
   for (uint32_t c0 = 0; c0 < C; c0 += kChunkBatch) {
     u32x4 x[kChunkBatch];
 #pragma unroll
-    for (uint32_t u = 0; u < kChunkBatch; ++u) {
-      const uint64_t g = g0 + (uint64_t)(c0 + u) * 64 * E + lane * E;
-      x[u] = *reinterpret_cast<gptr<const u32x4_a4>>(src + (g + E <= n ? g : n - E));
-    }
+    for (uint32_t u = 0; u < kChunkBatch; ++u)
+      x[u] = *reinterpret_cast<gptr<const u32x4_a4>>(src + g0 + tile_vector<E>((c0 + u) * 64 * E + lane * E, len, room));
     const uint32_t first = run;  // the batch's first position in the tile
 #pragma unroll
     for (uint32_t u = 0; u < kChunkBatch; ++u) {
@@ -2274,6 +2275,7 @@ __global__ __launch_bounds__(64) void flag_copy_kernel(ArrRef A, TileArgs I, con
   const uint32_t v = (uint32_t)(tile / I.tpv);
   uint64_t g0, gend;
   tile_range(I, v, tile - (uint64_t)v * I.tpv, kWaveTile, g0, gend);
+  const uint64_t te = tile_end(g0, gend);
   const uint64_t at = tiles[tile], word = masks[tile * 64 + lane];
   const uint32_t n_t = (uint32_t)at & 0xFFFFu;
   if (n_t == 0 || A.dead[v]) return;
@@ -2283,9 +2285,9 @@ __global__ __launch_bounds__(64) void flag_copy_kernel(ArrRef A, TileArgs I, con
   const uint64_t bp = b_lo + lane <= b_hi ? A.bptr[(uint64_t)v * kMaxBuckets + b_lo + lane] : 0;
   if (b_lo == b_hi) {
     const gptr<T> dst1 = gmem(reinterpret_cast<T*>(__shfl(bp, 0, 64)) + offset_in(log2F, base, b_lo));
-    copy_blocked<T, true>(values, g0, I.n_threads, word, dst1, base, log2F, b_lo, bp, s_keep);
+    copy_blocked<T, true>(values, g0, te, I.n_threads, word, dst1, base, log2F, b_lo, bp, s_keep);
   } else {
-    copy_blocked<T, false>(values, g0, I.n_threads, word, gptr<T>{}, base, log2F, b_lo, bp, s_keep);
+    copy_blocked<T, false>(values, g0, te, I.n_threads, word, gptr<T>{}, base, log2F, b_lo, bp, s_keep);
   }
 }
 
