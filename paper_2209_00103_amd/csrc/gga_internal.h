@@ -418,7 +418,7 @@ constexpr uint32_t kInsertTile = 64u * kInsertSlots;
 // tile's first: the tile has len threads, and room of them and the following lie in the
 // buffers.  Lanes past the tile's end share its first vector, so that a share's short last
 // tile does not read what the next share's tiles read too (16384 shares of 4097 u32
-// threads: 272 MB fetched by the copy without that, 157 MB with it, 179 -> 160 us a
+// threads: 215 MB fetched by the copy without that, 148 MB with it, 179 -> 160 us a
 // round); one that would run past the buffers starts before it (d may turn negative).
 template <uint32_t E>
 __host__ __device__ __forceinline__ int32_t tile_vector(uint32_t d, uint32_t len, int32_t room) {
