@@ -2138,7 +2138,10 @@ __global__ __launch_bounds__(kB) void flag_mask_kernel(TileArgs I, const uint8_t
 
 // The tiles' words become offset in the LFVector's round << 16 | count, and the
 // LFVector grows by their sum.  Up to 256 tiles: one wave per LFVector, four tiles
-// per lane; more: one workgroup, in passes of 4096 tiles.
+// per lane; more: one workgroup, in passes of 4096 tiles, or, past 4096, of 16384, each
+// a trip to memory and back of lanes that read words side by side (one LFVector of 2^28
+// u32 threads, 65536 tiles, 417 us a round, 439 in passes of 4096, 455 with 16
+// consecutive words a lane).
 constexpr uint32_t kGrowWaveTiles = 256;
 __global__ __launch_bounds__(256) void flag_grow_kernel(ArrRef A, TileArgs I, uint64_t* tiles) {
   const uint32_t v = blockIdx.x * 4u + (threadIdx.x >> 6), lane = lane_id();
@@ -2160,32 +2163,33 @@ __global__ __launch_bounds__(256) void flag_grow_kernel(ArrRef A, TileArgs I, ui
   grow_vector_by(A, I.elem_log2, v, __shfl(incl, 63, 64));
 }
 
+template <uint32_t kPer>  // words per thread and pass
 __global__ __launch_bounds__(1024) void flag_grow_long_kernel(ArrRef A, TileArgs I, uint64_t* tiles) {
   __shared__ uint32_t s_sum[16];
   const uint32_t v = blockIdx.x, tid = threadIdx.x, lane = tid & 63u, wv = tid >> 6;
   uint64_t* w = tiles + (uint64_t)v * I.tpv;
   uint64_t carry = 0;
-  for (uint64_t t0 = 0; t0 < I.tpv; t0 += 4096) {
-    uint32_t c[4], sum = 0;
-    const uint64_t t = t0 + tid * 4;
+  for (uint64_t t0 = 0; t0 < I.tpv; t0 += 1024 * kPer) {
+    uint32_t c[kPer], before[kPer], sum = 0;  // before: of the wave's words ahead of this one
+    const uint64_t t = t0 + wv * (64 * kPer) + lane;
 #pragma unroll
-    for (uint32_t k = 0; k < 4; ++k) {
-      c[k] = t + k < I.tpv ? (uint32_t)w[t + k] : 0u;
-      sum += c[k];
+    for (uint32_t k = 0; k < kPer; ++k) c[k] = t + 64 * k < I.tpv ? (uint32_t)w[t + 64 * k] : 0u;
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k) {
+      const uint32_t incl = wave_incl_scan(c[k]);
+      before[k] = sum + incl - c[k];
+      sum += __builtin_amdgcn_readlane(incl, 63);
     }
-    const uint32_t incl = wave_incl_scan(sum);
-    if (lane == 63) s_sum[wv] = incl;
+    if (lane == 0) s_sum[wv] = sum;
     __syncthreads();
-    uint64_t at = carry + incl - sum;
+    uint64_t at = carry;
     for (uint32_t q = 0; q < 16; ++q) {
       at += q < wv ? s_sum[q] : 0u;
       carry += s_sum[q];
     }
 #pragma unroll
-    for (uint32_t k = 0; k < 4; ++k) {
-      if (t + k < I.tpv) w[t + k] = at << 16 | c[k];
-      at += c[k];
-    }
+    for (uint32_t k = 0; k < kPer; ++k)
+      if (t + 64 * k < I.tpv) w[t + 64 * k] = (at + before[k]) << 16 | c[k];
     __syncthreads();  // s_sum is rewritten by the next pass
   }
   if (tid < 64) grow_vector_by(A, I.elem_log2, v, carry);
@@ -2803,8 +2807,10 @@ static int queue_packed(ggarray* a, uint64_t* off, const void* values, const uin
 static void queue_flag_grow(const ArrRef& A, const TileArgs& I, uint64_t* tiles, hipStream_t s) {
   if (I.tpv <= kGrowWaveTiles)
     hipLaunchKernelGGL(flag_grow_kernel, dim3((A.V + 3) / 4), dim3(256), 0, s, A, I, tiles);
+  else if (I.tpv <= 4096)
+    hipLaunchKernelGGL(flag_grow_long_kernel<4>, dim3(A.V), dim3(1024), 0, s, A, I, tiles);
   else
-    hipLaunchKernelGGL(flag_grow_long_kernel, dim3(A.V), dim3(1024), 0, s, A, I, tiles);
+    hipLaunchKernelGGL(flag_grow_long_kernel<16>, dim3(A.V), dim3(1024), 0, s, A, I, tiles);
 }
 
 // A buffer round with flags over LFVectors of several tiles: masks and tile

@@ -132,3 +132,16 @@ for V, chunk, each in ((2048, 256, 16), (2048, 512, 5), (2048, 512, 6), (8192, 5
     out.append(R.launches()[-1][2])
 """, record)
     assert out == [256, 64, 256, 64, 256, 64, 64, 256, 256, 64, 256] + [64, 64, 256, 64, 256, 64]
+
+
+def test_long_growth_passes_by_tiles(record):
+    """Tile words of one LFVector: a wave to 256 tiles, then a workgroup in passes of 4096, past 4096 of 16384."""
+    out = hip_routes.run("""
+p, out = R.pool(), []
+for tiles in (256, 257, 4096, 4097, 65536):
+    a = R.array(p, 4, 1)
+    R.insert(a, tiles * 4096, flags=True)
+    out.append([R.rec.rec_name(i).decode() for i in range(R.rec.rec_count())][1])
+""", record)
+    assert ["flag_grow_kernel" in n for n in out] == [True, False, False, False, False]
+    assert ["flag_grow_long_kernelILj%dE" % k in n for n, k in zip(out[1:], (4, 4, 16, 16))] == [True] * 4
