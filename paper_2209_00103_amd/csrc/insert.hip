@@ -58,7 +58,7 @@ struct TileArgs {
   uint64_t tpv;          // tiles per LFVector
   uint32_t elem_log2;
   uint32_t sh_num = 0;   // a shrink num / den fused after the round (sh_den 0: none;
-  uint32_t sh_den = 0;   // honoured by the one-wave-per-LFVector grow + store only)
+  uint32_t sh_den = 0;   // honoured by grow_store_kernel only, not by the block and two-launch forms)
   uint32_t reuse = 0;    // a clear came first in the same launch: buckets still in the table are taken again
 };
 
@@ -2634,7 +2634,8 @@ int launch_insert(ggarray* a, const InsertDesc& d, hipStream_t s, uint32_t sh_nu
   grow_bound(a, d.n_threads * (multi_mode(d.mode) ? d.max_count : 1u));
   const bool dense = d.mode == kModeRoundTag || d.mode == kModeKeyed || (d.mode == kModeBuffer && !d.flags);
   if (dense) {
-    const bool fused = sh_den && wave_per_vector(I, a->V);
+    // Payload buffers choose their form by bytes as well, and none of theirs shrinks.
+    const bool fused = sh_den && d.mode != kModeBuffer && wave_per_vector(I, a->V);
     if (fused) {
       I.sh_num = sh_num;
       I.sh_den = sh_den;

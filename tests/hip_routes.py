@@ -101,6 +101,19 @@ def poisson(a, n, each):
     check(lib.ggarray_insert_gen(a, ctypes.byref(g), u64(n), None))
 
 
+class Desc(ctypes.Structure):  # gga::InsertDesc
+    _fields_ = [("mode", ctypes.c_uint32), ("values", ctypes.c_void_p), ("flags", ctypes.c_void_p),
+                ("max_count", ctypes.c_uint32), ("n_threads", ctypes.c_uint64), ("seed", ctypes.c_uint64),
+                ("round", ctypes.c_uint32), ("tag_shift", ctypes.c_uint32), ("thresholds", ctypes.c_uint64 * 16),
+                ("tag", ctypes.c_uint64)]
+
+
+def insert_shrink(a, n, mode, num, den):
+    """launch_insert with a shrink after the round, which the C entry points ask for with generated payloads only."""
+    f = lib._ZN3gga13launch_insertEP7ggarrayRKNS_10InsertDescEP12ihipStream_tjj
+    check(f(a, ctypes.byref(Desc(mode=mode, values=SOMEWHERE, n_threads=n, round=1)), None, num, den))
+
+
 def run(body, record):
     prog = (f"import sys, json; sys.path.insert(0, {ROOT!r})\n"
             f"from tests import hip_routes as R\nR.load({record!r})\n{body}\nprint(json.dumps(out))")

@@ -145,3 +145,19 @@ for tiles in (256, 257, 4096, 4097, 65536):
 """, record)
     assert ["flag_grow_kernel" in n for n in out] == [True, False, False, False, False]
     assert ["flag_grow_long_kernelILj%dE" % k in n for n, k in zip(out[1:], (4, 4, 16, 16))] == [True] * 4
+
+
+def test_a_shrink_after_a_dense_round_is_queued_or_in_its_launch(record):
+    """Only the one-wave-per-LFVector round of generated payloads shrinks by itself: from a buffer, of every form,
+    the shrink is a launch of its own."""
+    out = hip_routes.run("""
+p, out = R.pool(), []
+for mode in (0, 1):
+    for V, chunk in ((512, 100), (512, 5000), (2048, 5000), (16384, 2000), (16, 1 << 20)):
+        a = R.array(p, 4, V)
+        R.insert_shrink(a, V * chunk, mode, 1, 2)
+        out.append([k for k, _, _ in R.launches()])
+""", record)
+    for names in out[:5]:
+        assert [n.startswith("shrink") for n in names] == [False] * (len(names) - 1) + [True]
+    assert out[5:9] == [["grow_store_kernel"]] * 4 and out[9][-1].startswith("shrink")
