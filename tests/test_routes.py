@@ -152,7 +152,7 @@ def test_a_shrink_after_a_dense_round_is_queued_or_in_its_launch(record):
     the shrink is a launch of its own."""
     out = hip_routes.run("""
 p, out = R.pool(), []
-for mode in (0, 1):
+for mode in (0, 3):  # from a buffer, round tags
     for V, chunk in ((512, 100), (512, 5000), (2048, 5000), (16384, 2000), (16, 1 << 20)):
         a = R.array(p, 4, V)
         R.insert_shrink(a, V * chunk, mode, 1, 2)
