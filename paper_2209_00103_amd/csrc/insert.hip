@@ -2531,16 +2531,18 @@ int ensure_status(ggarray* a, uint64_t ntiles, hipStream_t s) {
 
 static int queue_flag_rounds(ggarray* a, const InsertDesc& d, const TileArgs& I, uint64_t ntiles, hipStream_t s);
 static int queue_counts_rounds(ggarray* a, const InsertDesc& d, const TileArgs& I, uint64_t ntiles, hipStream_t s);
+static int ensure_packed_offsets(ggarray* a, uint64_t words, hipStream_t s);
 
 // Words of a flagged round in two passes: the masks, then a word per tile; never fewer
 // than a packed round of as many tiles, so that one runs in a graph after the other.
 // (A round of counts: a word per tile.)
 static uint64_t flag_round_words(uint64_t ntiles) { return ntiles * 64 + ntiles + packed_groups(ntiles) + 1; }
 
-// Whether a two-pass form can run: its buffer is large enough or can be grown (not
-// while the stream is capturing; a captured round then takes the one-launch form).
-static bool two_pass_fits(const ggarray* a, uint64_t words, hipStream_t s) {
-  return words <= a->pk_cap || !stream_capturing(s);
+// Whether a two-pass form can run: its buffer is large enough or could be grown (not
+// while the stream is capturing, nor when memory is short; such a round takes the
+// one-launch form).
+static bool two_pass_fits(ggarray* a, uint64_t words, hipStream_t s) {
+  return words <= a->pk_cap || ensure_packed_offsets(a, words, s) == GGA_OK;
 }
 
 // Rounds ds[0..n) of one generated producer, each followed by the shrink
@@ -2746,11 +2748,15 @@ static int ensure_packed_offsets(ggarray* a, uint64_t words, hipStream_t s) {
   if (stream_capturing(s)) return GGA_EINVAL;
   uint64_t cap = a->pk_cap ? a->pk_cap : 4096;
   while (cap < words) cap *= 2;
-  if (retire_buffer(a, a->pk_off, s) != GGA_OK) return GGA_EHIP;
-  a->pk_off = nullptr;
-  a->pk_cap = 0;
-  void* p = nullptr;
-  if (hipMallocAsync(&p, cap * sizeof(uint64_t), s) != hipSuccess) return GGA_EHIP;
+  void* p = nullptr;  // before the old one goes: a caller may do with that
+  if (hipMallocAsync(&p, cap * sizeof(uint64_t), s) != hipSuccess) {
+    (void)hipGetLastError();
+    return GGA_EHIP;
+  }
+  if (retire_buffer(a, a->pk_off, s) != GGA_OK) {
+    (void)hipFreeAsync(p, s);
+    return GGA_EHIP;
+  }
   a->pk_off = static_cast<uint64_t*>(p);
   a->pk_cap = cap;
   return GGA_OK;
@@ -2828,8 +2834,6 @@ static void queue_flag_kernels(const ArrRef& A, const InsertDesc& d, const TileA
 }
 
 static int queue_flag_rounds(ggarray* a, const InsertDesc& d, const TileArgs& I, uint64_t ntiles, hipStream_t s) {
-  const int rc = ensure_packed_offsets(a, flag_round_words(ntiles), s);
-  if (rc) return rc;
   if (a->elem_bytes == 4)
     queue_flag_kernels<uint32_t>(a->ref, d, I, a->pk_off, ntiles, s);
   else
@@ -2852,8 +2856,6 @@ static void queue_counts_kernels(const ArrRef& A, const InsertDesc& d, const Til
 }
 
 static int queue_counts_rounds(ggarray* a, const InsertDesc& d, const TileArgs& I, uint64_t ntiles, hipStream_t s) {
-  const int rc = ensure_packed_offsets(a, ntiles, s);
-  if (rc) return rc;
   if (a->elem_bytes == 4)
     queue_counts_kernels<uint32_t>(a->ref, d, I, a->pk_off, ntiles, s);
   else

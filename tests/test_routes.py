@@ -161,3 +161,25 @@ for mode in (0, 3):  # from a buffer, round tags
     for names in out[:5]:
         assert [n.startswith("shrink") for n in names] == [False] * (len(names) - 1) + [True]
     assert out[5:9] == [["grow_store_kernel"]] * 4 and out[9][-1].startswith("shrink")
+
+
+def test_rounds_in_two_passes_fall_back_when_memory_is_short(record):
+    """Without room for the tiles' words a counts round takes the one-launch form, as it does in a capture; the words
+    of an earlier round stay, and the next round with room takes two passes again."""
+    out = hip_routes.run("""
+p, out = R.pool(), []
+def seen():
+    out.append([k for k, _, _ in R.launches()])
+n = 1024 * 2049  # tiles of one LFVector
+a = R.array(p, 4, 1)
+R.rec.rec_fail(2); R.counts(a, n); seen()  # the look-back words fit, the two passes' do not
+R.counts(a, n); seen()
+R.rec.rec_fail(2); R.counts(a, 4 * n); seen()
+R.rec.rec_fail(0)
+R.rec.rec_capture(5); R.counts(a, n); seen(); R.rec.rec_capture(0)
+R.counts(a, 4 * n); seen()
+b = R.array(p, 4, 1)
+R.rec.rec_fail(1); R.counts(b, n, want=-4); R.rec.rec_fail(0)
+""", record)
+    one, two = ["insert_count_kernel"], ["counts_sum_kernel", "flag_grow_long_kernel", "counts_copy_kernel"]
+    assert out == [one, two, one, two, two]
