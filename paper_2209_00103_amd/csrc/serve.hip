@@ -551,15 +551,15 @@ int gga_server_create(gga_server** out, ggarray* const* arrays, uint32_t n, void
   const TableLayout L = layout(m, m);
   sv->table_bytes = align_up(L.used, kAlign);
   const uint64_t block = sv->table_bytes + 2ull * (m + 1) * sizeof(uint64_t) + kAlign;
-  bool ok = hipHostMalloc(reinterpret_cast<void**>(&sv->h_sizes), sizeof(uint64_t) * n, hipHostMallocDefault) ==
+  bool ok = hipHostMalloc(reinterpret_cast<void**>(&sv->h_sizes), sizeof(SizeItem) * n, hipHostMallocDefault) ==
             hipSuccess &&
             hipMalloc(reinterpret_cast<void**>(&sv->d_size_items), (sizeof(SizeItem) + sizeof(uint64_t)) * n) ==
             hipSuccess;
   if (ok) {
     sv->d_sizes = reinterpret_cast<uint64_t*>(sv->d_size_items + n);
-    std::vector<SizeItem> items(n);
+    SizeItem* items = reinterpret_cast<SizeItem*>(sv->h_sizes);  // later the sums' n words
     for (uint32_t i = 0; i < n; ++i) items[i] = SizeItem{arrays[i]->ref.size, arrays[i]->V};
-    ok = hipMemcpy(sv->d_size_items, items.data(), sizeof(SizeItem) * n, hipMemcpyHostToDevice) == hipSuccess;
+    ok = hipMemcpy(sv->d_size_items, items, sizeof(SizeItem) * n, hipMemcpyHostToDevice) == hipSuccess;
   }
   sv->lanes.resize(nl);
   for (Lane& l : sv->lanes) {

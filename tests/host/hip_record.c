@@ -32,6 +32,18 @@ void rec_clear(void) { n_l = 0; }
 void rec_capture(uint64_t id) { capture_id = id; }
 void rec_fail(int calls) { fail_in = calls; }
 
+/* operator new, which throws where memory is short: the largest request since rec_new_largest() was last asked. */
+static size_t new_largest;
+void *_Znwm(size_t n) {
+  if (n > new_largest) new_largest = n;
+  return malloc(n ? n : 1);
+}
+size_t rec_new_largest(void) {
+  const size_t n = new_largest;
+  new_largest = 0;
+  return n;
+}
+
 void **__hipRegisterFatBinary(const void *data) { (void)data; return (void **)calloc(1, 64); }
 void __hipUnregisterFatBinary(void **m) { (void)m; }
 void __hipRegisterVar(void **m, void *v, char *a, char *b, int e, size_t s, int c, int g) {

@@ -183,3 +183,20 @@ R.rec.rec_fail(1); R.counts(b, n, want=-4); R.rec.rec_fail(0)
 """, record)
     one, two = ["insert_count_kernel"], ["counts_sum_kernel", "flag_grow_long_kernel", "counts_copy_kernel"]
     assert out == [one, two, one, two, two]
+
+
+def test_server_creation_stages_its_items_without_throwing(record):
+    """Of what grows with the arrays, only the list of handles comes from an operator new that throws."""
+    out = hip_routes.run("""
+import ctypes
+from paper_2209_00103_amd.ggarray import ServerConfig
+p, n = R.pool(), 512
+arrays = (ctypes.c_void_p * n)(*[R.array(p, 4, 1).value for _ in range(n)])
+cfg = ServerConfig(mode=1, seed=1, append_shift=20, rw_op=0, append_round=1, lanes=1, max_step=4, depth=4)
+sv = ctypes.c_void_p()
+R.rec.rec_new_largest.restype = ctypes.c_size_t
+R.rec.rec_new_largest()
+R.check(R.lib.gga_server_create(ctypes.byref(sv), arrays, n, None, R.u64(0), ctypes.byref(cfg)))
+out = R.rec.rec_new_largest()
+""", record)
+    assert 0 < out <= 8 * 512
