@@ -2716,11 +2716,17 @@ static void queue_segments(const ArrRef& A, const TileArgs& I, const T* values, 
       hipLaunchKernelGGL((segments_block_kernel<T, 4>), dim3(A.V), block, 0, s, A, I, values, prefix, n_values);
     return;
   }
-  // Workgroups enough for a load round per wave in equal segments, up to 128 per CU (twice
-  // as many: 1024 segments of 64 KiB 46 us, 37 this way, 51 and 47 uneven).
-  uint64_t parts = (spans / kW + A.V - 1) / A.V;
+  // Twice the workgroups of a load round per wave in equal segments, so that a segment of
+  // several times the average finishes with the others, up to 128 per CU.  An odd number
+  // to a segment: workgroups go round robin over the 8 XCDs, and with 8 or 16 to a segment
+  // those that find work share a few of them (us, equal / lognormal lengths, once the
+  // workgroups, twice, twice and odd: V = 1024, 64 KiB 32 / 42, 38 / 44, 32 / 35; V = 512,
+  // 234 KiB 62 / 73, 61 / 66, 61 / 67; V = 2048, 128 KiB 125 / 159, 125 / 169, 128 / 132).
+  // Where equal segments give every workgroup several rounds it costs (V = 2048, 512 KiB 450,
+  // odd 483 / 480, odd 476).
+  uint64_t parts = (2 * spans / kW + A.V - 1) / A.V;
   const uint64_t most = (32768 + A.V - 1) / A.V;
-  if (parts > most) parts = most;
+  parts = parts >= 2 * most ? most : (parts < most ? parts : most) | 1;
   hipLaunchKernelGGL(segments_grow_kernel, grid, block, 0, s, A, I, prefix, n_values);
   hipLaunchKernelGGL(segments_store_kernel<T>, dim3((uint32_t)(parts * A.V)), dim3(kB), 0, s, A, values, prefix,
                      n_values, (uint32_t)parts);

@@ -47,7 +47,7 @@ for V, kb in ((1, 4), (1, 8), (512, 8), (512, 32), (512, 36), (1024, 8), (1024, 
         out.append(R.launches())
 """, record)
     # waves per LFVector (0: a wave without a workgroup of its own), or the store launch's workgroups per LFVector
-    want = [(1, 0), (1, 16), (512, 16), (512, 16), (512, "3"), (1024, 8), (1024, 8), (2048, 4), (2048, 8), (2048, "3"),
+    want = [(1, 0), (1, 16), (512, 16), (512, 16), (512, "5"), (1024, 8), (1024, 8), (2048, 4), (2048, 8), (2048, "5"),
             (2049, 0), (2049, 4), (2049, 4), (2049, 8), (16385, 4), (16385, "2")]
     exp = []
     for V, w in want:
@@ -200,3 +200,16 @@ R.check(R.lib.gga_server_create(ctypes.byref(sv), arrays, n, None, R.u64(0), cty
 out = R.rec.rec_new_largest()
 """, record)
     assert 0 < out <= 8 * 512
+
+
+def test_long_segments_workgroups_are_odd(record):
+    """An odd number of workgroups a segment, so that no XCD gets the idle ones of each; the most there may be where
+    equal segments give each several rounds."""
+    out = hip_routes.run("""
+p, out = R.pool(), []
+for V, kb in ((1024, 64), (512, 128), (512, 234), (2048, 128), (2048, 248), (2048, 256), (4096, 100), (1, 1 << 18)):
+    a = R.array(p, 4, V)
+    R.segments(a, V * kb * 256)
+    out.append(R.launches()[-1][1] // V)
+""", record)
+    assert out == [9, 17, 31, 17, 17, 16, 9, 32769]
