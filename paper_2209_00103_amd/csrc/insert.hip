@@ -485,10 +485,15 @@ __device__ __forceinline__ void dense_store(T* dst, const Prod& prod, uint64_t g
       for (uint32_t u = 0; u < kU; ++u) {
         const uint32_t q = q0 + u * 64 + lane;
         const uint64_t e = head + (q < nv ? q : nv - 1) * VPL;
-        T tmp[VPL];
+        if constexpr (std::is_same_v<Prod, ProdBufferOnce<T>>) {
+          typedef u32x4 vec __attribute__((aligned(4)));  // an element's alignment at least
+          x[u] = __builtin_nontemporal_load(reinterpret_cast<const vec*>(run.p + e));
+        } else {
+          T tmp[VPL];
 #pragma unroll
-        for (uint32_t k = 0; k < VPL; ++k) tmp[k] = run(e + k);
-        __builtin_memcpy(&x[u], tmp, 16);
+          for (uint32_t k = 0; k < VPL; ++k) tmp[k] = run(e + k);
+          __builtin_memcpy(&x[u], tmp, 16);
+        }
       }
 #pragma unroll
       for (uint32_t u = 0; u < kU; ++u) {
@@ -1192,7 +1197,11 @@ __global__ __launch_bounds__(256) void segments_grow_kernel(ArrRef A, TileArgs I
   grow_vector_by(A, I.elem_log2, v, cnt);
 }
 
-template <typename T>
+//
+// Payloads that the 256 MiB Infinity Cache cannot hold are loaded past it (kOnce; us, 512
+// segments of equal lengths, payloads last touched long ago / just written / just read:
+// 320 MiB 151 / 161 / 129, 130 / 132 / 127 this way; 160 MiB 89 / 57 / 57, 69 / 67 / 68).
+template <typename T, bool kOnce>
 __global__ __launch_bounds__(kB) void segments_store_kernel(ArrRef A, const T* values, const uint64_t* prefix,
                                                             uint64_t n_values, uint32_t parts) {
   constexpr uint64_t kSpan = kSpanBytes / sizeof(T), kLine = 128 / sizeof(T);
@@ -1204,7 +1213,9 @@ __global__ __launch_bounds__(kB) void segments_store_kernel(ArrRef A, const T* v
   const uint64_t wave = (uint64_t)(blockIdx.x - v * parts) * kW + (threadIdx.x >> 6);
   for (uint64_t a = al + wave * kSpan; a < s1; a += (uint64_t)parts * kW * kSpan) {
     const uint64_t i0 = a < s0 ? s0 : a, i1 = a + kSpan < s1 ? a + kSpan : s1;
-    store_span<T>(A, ProdBuffer<T>{values, nullptr}, i0, i1, lo + (i0 - s0), [row](uint32_t b) { return row[b]; });
+    const auto bucket = [row](uint32_t b) { return row[b]; };
+    if constexpr (kOnce) store_span<T>(A, ProdBufferOnce<T>{values}, i0, i1, lo + (i0 - s0), bucket);
+    else store_span<T>(A, ProdBuffer<T>{values, nullptr}, i0, i1, lo + (i0 - s0), bucket);
   }
 }
 
@@ -2728,8 +2739,9 @@ static void queue_segments(const ArrRef& A, const TileArgs& I, const T* values, 
   const uint64_t most = (32768 + A.V - 1) / A.V;
   parts = parts >= 2 * most ? most : (parts < most ? parts : most) | 1;
   hipLaunchKernelGGL(segments_grow_kernel, grid, block, 0, s, A, I, prefix, n_values);
-  hipLaunchKernelGGL(segments_store_kernel<T>, dim3((uint32_t)(parts * A.V)), dim3(kB), 0, s, A, values, prefix,
-                     n_values, (uint32_t)parts);
+  const auto store = n_values * sizeof(T) > (256ull << 20) ? segments_store_kernel<T, true> : segments_store_kernel<T, false>;
+  hipLaunchKernelGGL(store, dim3((uint32_t)(parts * A.V)), dim3(kB), 0, s, A, values, prefix, n_values,
+                     (uint32_t)parts);
 }
 
 int launch_insert_segments(ggarray* a, const void* values, const uint64_t* prefix, uint64_t n_values,

@@ -31,6 +31,14 @@ struct ProdBuffer {
   };
   __device__ __forceinline__ Run run(uint64_t g0, uint64_t) const { return {values + g0}; }
 };
+// A payload buffer larger than the cache, copied by dense_store: its lines are not kept.
+template <typename T>
+struct ProdBufferOnce {
+  static constexpr bool kDense = false;
+  const T* values;
+  using Run = typename ProdBuffer<T>::Run;
+  __device__ __forceinline__ Run run(uint64_t g0, uint64_t) const { return {values + g0}; }
+};
 template <typename T>
 struct ProdBernoulli {  // h = K(seed, gid, round); insert (T)h iff top bit
   static constexpr bool kMulti = false;

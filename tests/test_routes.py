@@ -213,3 +213,15 @@ for V, kb in ((1024, 64), (512, 128), (512, 234), (2048, 128), (2048, 248), (204
     out.append(R.launches()[-1][1] // V)
 """, record)
     assert out == [9, 17, 31, 17, 17, 16, 9, 32769]
+
+
+def test_segments_larger_than_the_cache_are_loaded_past_it(record):
+    out = hip_routes.run("""
+p, out = R.pool(), []
+for elem in (4, 8):
+    for n in ((256 << 20) // elem, (256 << 20) // elem + 1):
+        a = R.array(p, elem, 512)
+        R.segments(a, n)
+        out.append(R.rec.rec_name(R.rec.rec_count() - 1).decode())
+""", record)
+    assert ["segments_store_kernelI" in n and "Lb1E" in n for n in out] == [False, True, False, True]
