@@ -192,8 +192,8 @@ __device__ __forceinline__ uint32_t bucket_class(uint32_t log2F, uint32_t elem_l
 //    the end in the meantime look for it a few times (bounded) and only then take
 //    their block from the global bump pointer, one word that thousands of waves
 //    would otherwise meet on, some 45 ns each (the first round of 65536 LFVectors
-//    on a fresh pool, 310 -> 150 us; of 8192 with five buckets each, 257 -> 45 us).  Larger blocks always come from the global bump
-//    pointer.
+//    on a fresh pool, 310 -> 150 us; of 8192 with five buckets each, 257 -> 45 us).
+//    Larger blocks always come from the global bump pointer.
 //  * Only when the region is exhausted does an allocation look through the other
 //    free lists (steal), guided by the hint masks.
 //

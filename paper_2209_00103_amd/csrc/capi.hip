@@ -33,7 +33,9 @@ int hip_fail(hipError_t e, const char* what) {
   return GGA_EHIP;
 }
 
-// Per-array host scratch for synchronising reads (pinned, so copies are async).
+// Per-array host words for synchronising reads: copies into them are asynchronous, and
+// report_kernel writes them itself, so the memory is pinned, mapped for the device and
+// coherent (hipHostMalloc's default).
 struct Pinned {
   uint64_t* p = nullptr;
   int init() { return hipHostMalloc(reinterpret_cast<void**>(&p), 64, hipHostMallocDefault) == hipSuccess ? GGA_OK : GGA_EHIP; }

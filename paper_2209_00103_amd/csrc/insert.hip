@@ -2,9 +2,19 @@
 // growth (Alg. 2), for the GGArray and for the static-array baseline.
 //
 // The logical threads of a round are cut into tiles, numbered in (LFVector,
-// position) order.  For the 0/1 producers (at most one element per thread) one
-// wavefront handles one tile of kInsertTile threads; the multi-element producers
-// use 256-thread workgroups over 1024-thread tiles.  Per tile:
+// position) order: of kInsertTile threads, a wave each, for the 0/1 producers (at most
+// one element per thread), of 1024 threads, a 256-thread workgroup each, for the
+// multi-element producers.  The forms:
+//   - dense rounds (every thread inserts) and appended segments have closed-form
+//     positions: a wave or a workgroup per LFVector grows and stores it in one launch, or a
+//     grow launch comes before a store launch;
+//   - packed rounds, and rounds from buffers with flags or with many tiles of counts, of
+//     several tiles per LFVector: sums of the tiles, growth of every LFVector by them, copy;
+//   - rounds of one tile per LFVector: a wave or a workgroup each, no tile waits for another;
+//   - the others (generated rounds of several tiles per LFVector, few tiles of counts, and
+//     any round whose two passes have no memory for their words) in one launch with
+//     tickets and look-back.
+// That last form, per tile:
 //   1. the producer's flags (or counts) are evaluated and counted: a wave ballot
 //      per candidate slot (mbcnt gives each kept candidate its rank), or a scan
 //      of the per-thread counts;
@@ -1184,7 +1194,7 @@ __global__ __launch_bounds__(64 * W) void segments_block_kernel(ArrRef A, TileAr
 // LFVector store its segment in pieces of 4 KiB that start on whole lines of the
 // bucket.  One wave copying a segment waits for a round trip to memory per 4 KiB
 // and the longest segment holds the launch (3.0e7 u32 elements in 512 segments of
-// lognormal lengths: 654 us as one wave each, 5 + 50 us, 4.8 TB/s, in this form).
+// lognormal lengths: 654 us as one wave each, 5 + 43 us, 5.6 TB/s, in this form).
 __global__ __launch_bounds__(256) void segments_grow_kernel(ArrRef A, TileArgs I, const uint64_t* prefix,
                                                             uint64_t n_values) {
   const uint32_t v = blockIdx.x * 4u + (threadIdx.x >> 6);

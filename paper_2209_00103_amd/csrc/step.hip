@@ -622,7 +622,7 @@ __device__ void wave_copy(T* dst_, const T* src_, uint64_t n) {
 }  // namespace
 
 // Three waves per SIMD for 4-byte elements: one more than the 168 registers that
-// allow them leaves two (512 arrays of configuration 4's sizes, a whole step: 4026
+// allow them leaves two (512 arrays of configuration 4's sizes, a whole step: 3984
 // against 4140 us).
 template <typename T>
 __global__ __launch_bounds__(kSB, sizeof(T) == 4 ? 3 : 2) void step_wave_kernel(const BatchArr* arrs, const uint32_t* varr,
