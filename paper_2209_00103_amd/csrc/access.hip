@@ -429,7 +429,6 @@ __global__ __launch_bounds__(256) void batch_shrink_chain_kernel(const BatchArr*
     *size = shrink_keep(*size, num, den);
   }
 }
-constexpr uint64_t kBatchChainMinV = 32768;
 
 // Returns every bucket of the array to the pool (destroy).
 __global__ __launch_bounds__(256) void free_all_kernel(ArrRef A, uint32_t elem_log2) {
@@ -1392,11 +1391,35 @@ static int ensure_batch_table(gga_batch* b, hipStream_t s, const uint64_t** tab,
   return GGA_OK;
 }
 
+// Whether a batch's clears and shrinks run as chains: from 32768 LFVectors on, where the 16
+// of a residue and pass share their lists in at least half of the batch (arrays created in a
+// row with one first bucket, or long arrays).  Where they differ the chain kernel releases
+// bucket by bucket, and an LFVector each for 16 lanes is faster (16 arrays of 5001
+// LFVectors with others created between: 69 us, 48 that way; 4 of 20000 in a row: 31, 50).
+constexpr uint64_t kBatchChainMinV = 32768;
+bool batch_chains_suit(ggarray* const* arrays, const uint64_t* vbegin, const uint32_t* varr, uint64_t total) {
+  if (total < kBatchChainMinV) return false;
+  const auto same = [&](uint64_t w, uint64_t x) {
+    const ggarray *a = arrays[varr[w]], *b = arrays[varr[x]];
+    const uint64_t d = (w - vbegin[varr[w]] + a->ref.salt) - (x - vbegin[varr[x]] + b->ref.salt);
+    return a->ref.pool.hdr == b->ref.pool.hdr && a->ref.log2F == b->ref.log2F && d % kFreeShards == 0;
+  };
+  uint64_t alike = 0;
+  for (uint64_t w0 = 0; w0 < total; w0 += kChainStep)
+    for (uint64_t w = w0; w < w0 + kFreeShards && w < total; ++w) {
+      uint64_t n = 1;
+      for (uint64_t x = w + kFreeShards; n && x < w0 + kChainStep && x < total; x += kFreeShards)
+        n = same(w, x) ? n + 1 : 0;
+      alike += n;
+    }
+  return 2 * alike >= total;
+}
+
 int launch_batch_shrink(gga_batch* b, uint32_t num, uint32_t den, hipStream_t s) {
   if (num == den)
     for (uint32_t i = 0; i < b->n; ++i) b->arrays[i]->size_ub = 0;
   const uint64_t V = b->total_vectors;
-  if (V >= kBatchChainMinV)
+  if (b->chains)
     hipLaunchKernelGGL(batch_shrink_chain_kernel, dim3(kFreeShards * kChainLanes / 256), dim3(256), 0, s,
                        b->d_arrays, b->d_vbegin, b->d_varr, V, num, den);
   else if (shrink_shares_wave(V))

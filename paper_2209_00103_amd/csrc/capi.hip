@@ -578,6 +578,7 @@ int gga_batch_create(gga_batch** out, ggarray* const* arrays, uint32_t n, gga_st
       ok = varr != nullptr;
       for (uint32_t i = 0; ok && i < n; ++i)
         for (uint64_t w = vb[i]; w < vb[i + 1]; ++w) varr[w] = i;
+      if (ok) b->chains = batch_chains_suit(arrays, vb, varr, vb[n]);
     }
     // barrier words, chunk totals, per-LFVector sizes
     const size_t step_bytes = 256 + sizeof(uint64_t) * kStepChunkMax + sizeof(uint64_t) * (ok ? vb[n] : 0);

@@ -123,6 +123,7 @@ struct gga_batch {
   uint32_t* d_err;           // device: sticky batch error (flatten output too small)
   uint64_t* d_vbegin;        // device: n + 1 exclusive prefix of the arrays' LFVector counts
   uint64_t total_vectors;
+  bool chains;               // how a shrink releases buckets: see batch_chains_suit
   uint32_t stream_blocks;    // workgroups of the r/w and flatten launches (0: default)
   uint64_t* h_pin;           // pinned host scratch
   // Round tables uploaded so far (descriptors + block offsets), reused when the
@@ -480,6 +481,7 @@ int launch_batch_step(gga_batch* b, const StepDesc& D, const uint64_t* d_counts,
                       uint64_t out_cap, hipStream_t s);
 int launch_batch_scan(gga_batch* b, hipStream_t s);
 int launch_batch_shrink(gga_batch* b, uint32_t num, uint32_t den, hipStream_t s);
+bool batch_chains_suit(ggarray* const* arrays, const uint64_t* vbegin, const uint32_t* varr, uint64_t total);
 int launch_batch_stream(gga_batch* b, uint32_t op, void* out, uint64_t cap, bool flatten, hipStream_t s);
 
 // Served steps.  prepare_round_item fills the descriptor of one insertion round of

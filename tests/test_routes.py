@@ -225,3 +225,31 @@ for elem in (4, 8):
         out.append(R.rec.rec_name(R.rec.rec_count() - 1).decode())
 """, record)
     assert ["segments_store_kernelI" in n and "Lb1E" in n for n in out] == [False, True, False, True]
+
+
+def test_batch_shrinks_by_whether_the_arrays_lists_line_up(record):
+    """Chains from 32768 LFVectors on where the LFVectors of a residue share their free lists, else 16 lanes each."""
+    out = hip_routes.run("""
+import ctypes
+p, q, out = R.pool(), R.pool(), []
+def batch(shapes, gap=0, pools=(p, p)):
+    arrays = []
+    for k, (V, F) in enumerate(shapes):
+        arrays.append(R.array(pools[k % 2], 4, V, F))
+        if gap: R.array(p, 4, gap, 64)
+    h, b = (ctypes.c_void_p * len(arrays))(*[a.value for a in arrays]), ctypes.c_void_p()
+    R.check(R.lib.gga_batch_create(ctypes.byref(b), h, len(arrays), None))
+    R.launches()
+    R.check(R.lib.gga_batch_shrink(b, 1, 1, None))
+    out.append(R.launches()[-1][0])
+batch([(20000, 64)] * 4)
+batch([(131, 64)] * 512)
+batch([(30000, 64), (2767, 64)])
+batch([(5001, 64)] * 16, gap=77)
+batch([(20000, 64), (20000, 128)])
+batch([(20000, 64)] * 2, pools=(p, q))
+batch([(70000, 64), (20000, 64)], gap=77)   # most of it is one array
+batch([(33000, 64), (70000, 128)], gap=4096)
+""", record)
+    chain, apart = "batch_shrink_chain_kernel", "batch_shrink_kernel"
+    assert out == [chain, chain, apart, apart, apart, apart, chain, apart]
