@@ -679,7 +679,7 @@ __global__ __launch_bounds__(64) void insert_wave_kernel(ArrRef A, StaticRef S, 
 // 5.7, 512 of 3906 flagged u32 threads 18 and 7, 65536 of 64 flagged ones 170 and
 // 33, 4096 of 3906 34 and 28.5).
 template <typename T, class Prod, uint32_t W, uint32_t S>
-__global__ __launch_bounds__(64 * W) void insert_block_kernel(ArrRef A, TileArgs I, Prod prod) {
+__device__ __forceinline__ void insert_block(const ArrRef& A, const TileArgs& I, const Prod& prod) {
   static_assert(W * S <= 64, "one count per lane of wave 0");
   __shared__ uint64_t s_bp[kMaxBuckets];
   __shared__ uint32_t s_cnt[64];
@@ -759,6 +759,19 @@ __global__ __launch_bounds__(64 * W) void insert_block_kernel(ArrRef A, TileArgs
   }
 }
 
+// Four threads per lane: eight waves a SIMD hide the allocations (1000 LFVectors of 4000
+// flagged threads 15 us, 20 with 81 scalar registers).  With sixteen the kernel would spill
+// to keep to that, and the vector registers of the 8-byte forms would then cost a wave.
+template <typename T, class Prod, uint32_t W>
+__global__ __launch_bounds__(64 * W) GGA_EIGHT_WAVES void insert_block_kernel(ArrRef A, TileArgs I, Prod prod) {
+  insert_block<T, Prod, W, 4>(A, I, prod);
+}
+
+template <typename T, class Prod, uint32_t W>
+__global__ __launch_bounds__(64 * W) void insert_long_block_kernel(ArrRef A, TileArgs I, Prod prod) {
+  insert_block<T, Prod, W, 16>(A, I, prod);
+}
+
 // A 0/1 round of the single-launch kernels.  Few LFVectors take the widest
 // workgroup their share fills.  From 2048 on the CUs are full of workgroups, and
 // what counts is how many fit: one wave for shares of up to 256 threads (16384
@@ -771,13 +784,13 @@ void launch_flags(const ArrRef& A, const StaticRef& S, const TileArgs& I, const 
     if (I.tpv == 1) {
       const bool many = A.V >= 2048;
       if (I.chunk <= 256 && many)
-        hipLaunchKernelGGL((insert_block_kernel<T, Prod, 1, 4>), dim3(A.V), dim3(64), 0, s, A, I, p);
+        hipLaunchKernelGGL((insert_block_kernel<T, Prod, 1>), dim3(A.V), dim3(64), 0, s, A, I, p);
       else if (I.chunk <= 1024)
-        hipLaunchKernelGGL((insert_block_kernel<T, Prod, 4, 4>), dim3(A.V), dim3(256), 0, s, A, I, p);
+        hipLaunchKernelGGL((insert_block_kernel<T, Prod, 4>), dim3(A.V), dim3(256), 0, s, A, I, p);
       else if (many)
-        hipLaunchKernelGGL((insert_block_kernel<T, Prod, 4, 16>), dim3(A.V), dim3(256), 0, s, A, I, p);
+        hipLaunchKernelGGL((insert_long_block_kernel<T, Prod, 4>), dim3(A.V), dim3(256), 0, s, A, I, p);
       else
-        hipLaunchKernelGGL((insert_block_kernel<T, Prod, 16, 4>), dim3(A.V), dim3(1024), 0, s, A, I, p);
+        hipLaunchKernelGGL((insert_block_kernel<T, Prod, 16>), dim3(A.V), dim3(1024), 0, s, A, I, p);
       return;
     }
   }
@@ -1543,6 +1556,11 @@ __global__ __launch_bounds__(64) void insert_count_wave_kernel(ArrRef A, TileArg
     __syncthreads();  // the window is read before the next one is written
   }
 }
+
+// Eight waves a SIMD for the one form that has more than 80 scalar registers by itself and
+// no more than 64 vector registers (65536 LFVectors of 256 counts: 115 us, 109 with them).
+template __global__ GGA_EIGHT_WAVES void insert_count_wave_kernel<uint64_t, ProdCounts<uint64_t>, 4>(
+    ArrRef, TileArgs, ProdCounts<uint64_t>);
 
 // A multi-element round as insert_count_wave_kernel (K = 4 or 8 logical threads per
 // lane) or insert_count_kernel.  Fewer than 2048 LFVectors leave a CU short of

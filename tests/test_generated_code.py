@@ -47,7 +47,8 @@ def test_eight_waves_of_a_kernel_fit_a_simd(insert_asm, kernel):
     registers are the most that eight waves of a SIMD may have."""
     for name, _ in _kernels(insert_asm, kernel):
         info = insert_asm[insert_asm.index(f".amdhsa_kernel {name}\n"):]
-        assert int(re.search(r"; TotalNumSgprs: (\d+)", info).group(1)) <= 80, name
+        if int(re.search(r"; NumVgprs: (\d+)", info).group(1)) <= 64:
+            assert int(re.search(r"; TotalNumSgprs: (\d+)", info).group(1)) <= 80, name
         assert int(re.search(r"; NumVgprs: (\d+)", info).group(1)) <= 64, name
 
 
@@ -59,3 +60,12 @@ def test_small_generated_counts_rounds_fetch_one_form_of_the_hash(insert_asm):
         assert len(re.findall(r"\bv_(?:mul_hi_u32|mul_lo_u32|mad_u64_u32)\b", code)) <= 90, name
         seen += 1
     assert seen == 2
+
+
+@pytest.mark.parametrize("kernel", ["insert_block_kernel", "insert_count_wave_kernelI[jm]NS_1[01]Prod(?:CountsIm|Poisson)"])
+def test_scalar_registers_of_the_allocating_rounds_leave_eight_waves(insert_asm, kernel):
+    """More than 80 scalar registers cost a wave of every SIMD (1000 LFVectors of 4000 flagged threads: 15 -> 20 us)."""
+    for name, _ in _kernels(insert_asm, kernel):
+        info = insert_asm[insert_asm.index(f".amdhsa_kernel {name}\n"):]
+        if int(re.search(r"; NumVgprs: (\d+)", info).group(1)) <= 64:
+            assert int(re.search(r"; TotalNumSgprs: (\d+)", info).group(1)) <= 80, name
